@@ -36,16 +36,17 @@ extern "C" {
  * tau: device, elpa_hh_num_reflectors(n, nbw) elements.
  * dtype: ELPA_R64 or ELPA_C64 (ELPA_R32 is not provided: single-precision
  *    solves keep the reduction in double precision); 1 <= nbw <= 512.
- * Asynchronous on `stream` (a hipStream_t; NULL = the null stream); about
+ * Asynchronous on `stream` (a hipStream_t; NULL = the null stream).  Bands
+ * with nbw <= 64 run the chase in one launch, a workgroup per sweep in order
+ * of a ticket, each step's blocks held in registers; only A's lower triangle
+ * is read and updated (the two-sided update of the diagonal block as a rank-2
+ * update), the upper triangle is written once at the end, and a small
+ * workspace comes from the library's workspace cache.  Wider bands take about
  * 3 n kernel launches, each a bounded set of independent chase steps (steps
- * that touch disjoint entries), in an order equal to the sequential one.
- * Real bands with nbw <= 64 hold each step's blocks in registers and update only
- * the lower triangle (the symmetric two-sided update of the diagonal block
- * as a rank-2 update), reading only A's lower triangle; the upper triangle
- * is written once at the end.  Complex bands and wider real bands update
- * both triangles step by step.
- * Returns ELPA_OK or ELPA_ERR_ARG / _DTYPE / _ALIGN / _DEVICE (elpa_hh.h);
- * arguments are checked before anything is enqueued; n == 1 writes d only.
+ * that touch disjoint entries), and update both triangles step by step.
+ * Both orders equal the sequential one.
+ * Returns ELPA_OK or ELPA_ERR_ARG / _DTYPE / _ALIGN / _NOMEM / _DEVICE
+ * (elpa_hh.h); arguments are checked before anything is enqueued; n == 1 writes d only.
  */
 int elpa_band_to_tridiag(int64_t n, int64_t nbw, void *A, int64_t lda, double *d, double *e,
                          void *hh, void *tau, int32_t dtype, void *stream);

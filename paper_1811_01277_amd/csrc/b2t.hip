@@ -1,7 +1,8 @@
 // Band -> tridiagonal reduction by bulge chasing (C ABI in
 // include/elpa_b2t.h; Kus et al., Sec. 2), one column per chase step, with
 // the reflectors written in the slot layout of the tridiagonal -> band
-// back-transformation.
+// back-transformation.  Bands up to 64 wide run the whole chase in one launch
+// (k_chase_sweeps below); wider ones run the launch schedule described here.
 //
 // Schedule.  Chase step (s, j) (row r = s+1+j*nbw, length L <= nbw) reads and
 // writes only entries of the square [r-nbw, r+L+nbw)^2 that lie in rows
@@ -32,6 +33,7 @@
 #include "../../include/elpa_b2t.h"
 #include "../../include/elpa_hh.h"
 #include "hh_common.h"
+#include "hh_sched.h"
 
 namespace eb2t {
 
@@ -246,150 +248,344 @@ __global__ __launch_bounds__(512) void k_chase(E* __restrict__ A, int64_t lda, i
   if (tid == 0) tau[slot] = tv;
 }
 
-// Real band, nb <= 64: the same steps on the lower triangle only, every value
-// a step touches held in registers (the upper triangle is rebuilt at the end
-// from the tridiagonal result).  A step (s, j) with H = I - tau v v^T on the
-// indices [r, r+L) changes three lower-triangle blocks:
-//   R = rows [r, r+L) x columns [c0, r)   <- H R   (c0 = s for j = 0: the
-//       columns left of s are already reduced and zero in these rows; else
-//       r - nb, the bulge columns)
-//   D = rows and columns [r, r+L)         <- H D H (symmetric; with y = D v,
-//       mu = v^T y and w = tau y - tau^2 mu / 2 v: D <- D - w v^T - v w^T)
-//   C = rows [r+L, hi) x columns [r, r+L) <- C H   (hi = min(r+L+nb, n))
-// Lane i of every wave holds row i of each block, wave w of the NW waves the
-// columns w, w+NW, ..., so each block is one coalesced load per column, all
-// issued before any value is used, and one store.  Column sums (v^T R, the
-// strictly-lower part of D^T v) are wave reductions; row sums (the lower part
-// of D v, C v) add the waves' partial sums through LDS.  Two barriers per
-// step.  With eight waves each wave's chain of column reductions is half as
-// long as with four (n = 20000, nbw = 64: 0.80 s against 1.04 s; sixteen
-// waves gave 0.81 s).  The
-// lower-triangle entries the steps touch are a subset of the two-sided form's,
-// so the launch schedule's disjointness holds unchanged.
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_chase_reg(double* __restrict__ A, int64_t lda, int64_t n,
-                                                   int64_t nb, int64_t t, int64_t s_lo,
-                                                   double* __restrict__ hh,
-                                                   double* __restrict__ tau) {
-  __shared__ double vs[64], ys2[64], py[NW][64], pu[NW][64];
-  __shared__ double sh_tau;
-  const int64_t s = s_lo + blockIdx.x;
-  const int64_t j = t - kLag * s;
-  const int64_t r = s + 1 + j * nb;
-  const int L = (int)((nb < n - r) ? nb : n - r);
-  const int64_t c0 = (j == 0) ? s : r - nb;
-  const int nR = (int)(r - c0);                       // 1 for j = 0, else nb
-  const int nC = (int)(((r + L + nb < n) ? r + L + nb : n) - r - L);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  auto at = [&](int64_t i, int64_t k) -> double& { return A[i + k * lda]; };
+// ---------------------------------------------------------------------------
+// nb <= 64: the whole chase in one launch, lower triangle only, every block a
+// step touches held in registers.
+//
+// A step (s, j) with H = I - tau v v^H on the indices [r, r+L) changes three
+// lower-triangle blocks:
+//   R = rows [r, r+L) x columns [r-nb, r)  <- H^H R  (column s alone for j = 0)
+//   D = rows and columns [r, r+L)          <- H^H D H (with y = D v, mu = v^H y
+//       and w = tau y - |tau|^2 mu / 2 v: D <- D - w v^H - v w^H)
+//   C = rows [r+L, hi) x columns [r, r+L)  <- C H    (hi = min(r+L+nb, n))
+// and C is the next step's R.  A workgroup carries one sweep from its first
+// step to its last, so C passes on in registers: a step loads D and C, and
+// stores R and D.
+//
+// Order between sweeps.  Step (s, j) reads what sweep s-1 wrote in its steps
+// up to j+1 and one entry of step j+2, the subdiagonal value beta that its
+// reflector leaves (row r+2nb-1, column r+nb-1).  So a workgroup forms the
+// next step's reflector at the end of each step, stores beta and the zeros
+// below it with the step's R and D, and then raises its progress count; sweep
+// s may load step j once sweep s-1 has counted min(j+2, J(s-1)) steps.  What
+// sweep s stores in step j lies in rows below r+nb, which sweep s-1 no longer
+// reads or writes at that count.
+//
+// Waiting always ends: sweeps are handed out in order by a ticket counter, so
+// the sweep a workgroup waits for is held by a workgroup that started
+// earlier, is running and waits only for a still earlier sweep; sweep 0 waits
+// for none.  (Should a wait last longer than kWaitTicks all the same, it is
+// given up and d is set to NaN.)  Matrix entries that pass between workgroups
+// are read and written with device-scope accesses, stores are acknowledged
+// before the count is raised.
+//
+// Bound: the chain of two steps and one hand-over per sweep, all latency.
+// One launch per step (3 n launches, 12.1 us each at any size) took 34 ms at
+// n = 1000 and 148 ms at n = 4000 (nbw = 64, fp64); the one-launch chase takes
+// 8.7 and 36 ms, about 9 us per sweep.
+//
+// Layout: lane i of each wave holds row i of the blocks, wave w of NW the
+// columns w, w + NW, ... (8 per wave): each block is one coalesced access per
+// column.  Row sums (the lower part of D v, C v) add the waves' partials
+// through LDS.  Column sums (v^H R, the strictly lower part of D^H v) halve
+// the eight values per lane with each exchange, so the eight sums of a wave
+// take 15 exchanges and not 48, and lane 8 q ends with column q's.
+constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // 20 s of the 100 MHz clock
+constexpr int kProgStride = 16;                          // counts 64 bytes apart
 
-  constexpr int NQ = 64 / NW;  // columns per wave
-  double xr[NQ], xd[NQ], xc[NQ];
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kRor8 = 0x128;
+
+// a, b -> (a over the lower half of each pair of lane groups) + (...): lanes of
+// even groups get a summed over the pair, lanes of odd groups b
+__device__ __forceinline__ double pair32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a),
+                                                  (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a),
+                                                  (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double pair16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a),
+                                                  (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a),
+                                                  (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+// sum over the wave, the same bits in every lane
+__device__ __forceinline__ double wave_sum_dpp(double x) {
+  x += dpp_mov<kXor1>(x);
+  x += dpp_mov<kXor2>(x);
+  x += dpp_mov<kHalfMirror>(x);
+  x += dpp_mov<kMirror>(x);
+  x = pair16(x, x);
+  return pair32(x, x);
+}
+// x[0..7] per lane -> lane l returns the wave's sum of x[l / 8]
+__device__ __forceinline__ double wave_sum8(const double (&x)[8]) {
+  double y[4];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int k = wave + NW * q;
-    xr[q] = (lane < L && k < nR) ? at(r + lane, c0 + k) : 0.0;
-    xd[q] = (lane < L && k < L && lane >= k) ? at(r + lane, r + k) : 0.0;
-    xc[q] = (lane < nC && k < L) ? at(r + L + lane, r + k) : 0.0;
+  for (int i = 0; i < 4; ++i) y[i] = pair32(x[i], x[i + 4]);
+  const double z0 = pair16(y[0], y[2]), z1 = pair16(y[1], y[3]);
+  const bool up = (threadIdx.x & 8) != 0;
+  double t = (up ? z1 : z0) + dpp_mov<kRor8>(up ? z0 : z1);
+  t += dpp_mov<kXor1>(t);
+  t += dpp_mov<kXor2>(t);
+  return t + dpp_mov<kHalfMirror>(t);
+}
+__device__ __forceinline__ z64 wave_sum8(const z64 (&x)[8]) {
+  double a[8], b[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    a[i] = x[i].re;
+    b[i] = x[i].im;
   }
-  // reflector from column 0 of R (column c0, the column this step reduces;
-  // wave 0's first column)
-  if (wave == 0) {
-    const double x = xr[0];
-    const double ss = wave_sum(lane >= 1 ? x * x : 0.0);
-    const double alpha = __shfl(x, 0, 64);
-    double tv = 0.0, beta = alpha, sc = 0.0;
-    if (ss != 0.0) {
-      const double h = sqrt(alpha * alpha + ss);
-      beta = alpha >= 0.0 ? -h : h;
-      tv = (beta - alpha) / beta;
-      sc = 1.0 / (alpha - beta);
-    }
-    vs[lane] = lane == 0 ? 1.0 : (lane < L ? x * sc : 0.0);
-    xr[0] = lane == 0 ? beta : 0.0;   // the reduced column, exactly
-    if (lane == 0) sh_tau = tv;
+  return z64{wave_sum8(a), wave_sum8(b)};
+}
+__device__ __forceinline__ double read_lane(double x, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                          __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+__device__ __forceinline__ z64 read_lane(z64 x, int l) {
+  return z64{read_lane(x.re, l), read_lane(x.im, l)};
+}
+// device-scope accesses of matrix entries
+__device__ __forceinline__ double load_dev(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ z64 load_dev(const z64* p) {
+  return z64{load_dev(&p->re), load_dev(&p->im)};
+}
+__device__ __forceinline__ void store_dev(double* p, double x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_dev(z64* p, z64 x) {
+  store_dev(&p->re, x.re);
+  store_dev(&p->im, x.im);
+}
+// the eliminated diagonal block stays exactly Hermitian
+__device__ __forceinline__ double real_part(double a) { return a; }
+__device__ __forceinline__ z64 real_part(z64 a) { return z64{a.re, 0.0}; }
+
+// progress counts, ticket and failure word of one call
+struct ChaseState {
+  int* prog;  // [n - 1] counts, kProgStride apart
+  int* ticket;
+  int* failed;
+};
+
+__global__ __launch_bounds__(256) void k_chase_clear(ChaseState c, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n - 1) c.prog[i * kProgStride] = 0;
+  if (i == 0) {
+    *c.ticket = 0;
+    *c.failed = 0;
   }
-  __syncthreads();
-  const double tv = sh_tau;
-  const double vl = vs[lane];
-  double vk[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) vk[q] = vs[wave + NW * q];
-  if (tv != 0.0) {
-    // column sums: v^T R (R's update) and the strictly lower part of D^T v;
-    // row sums: the lower part of D v and C v, per wave
-    double wr[NQ];
-    double ry = 0.0, ru = 0.0;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int k = wave + NW * q;
-      wr[q] = (k >= 1) ? tv * wave_sum(vl * xr[q]) : 0.0;
-      const double cs = wave_sum(lane > k ? vl * xd[q] : 0.0);
-      if (lane == 0) ys2[k] = cs;
-      ry += xd[q] * vk[q];
-      ru += xc[q] * vk[q];
-    }
-    py[wave][lane] = ry;
-    pu[wave][lane] = ru;
-    __syncthreads();
-    // y = D v, u = tau C v, mu = v^T y, w = tau y - tau^2 mu / 2 v (every
-    // wave forms the values of its own rows and columns)
-    double yl = ys2[lane], us = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      yl += py[w][lane];
-      us += pu[w][lane];
-    }
-    const double ul = tv * us;
-    const double mu = wave_sum(vl * yl);
-    const double h2 = 0.5 * tv * tv * mu;
-    const double wl = tv * yl - h2 * vl;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int k = wave + NW * q;
-      double yk = ys2[k];
-#pragma unroll
-      for (int w = 0; w < NW; ++w) yk += py[w][k];
-      const double wk = tv * yk - h2 * vk[q];
-      if (k >= 1) xr[q] -= vl * wr[q];
-      xd[q] -= wl * vk[q] + vl * wk;
-      xc[q] -= ul * vk[q];
-    }
-  }
-  // store R, D (lower), C; the reflector in its slot
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int k = wave + NW * q;
-    if (lane < L && k < nR) at(r + lane, c0 + k) = xr[q];
-    if (lane < L && k < L && lane >= k) at(r + lane, r + k) = xd[q];
-    if (lane < nC && k < L) at(r + L + lane, r + k) = xc[q];
-  }
-  const int64_t slot = ehh::slot_offset(n, nb, s) + j;
-  if (tid < nb) hh[slot * nb + tid] = tid < L ? vs[tid] : 0.0;
-  if (tid == 0) tau[slot] = tv;
 }
 
-// The upper triangle of the result (the register chase updates only the
+// waits until *p >= need; false when the wait was given up
+__device__ __forceinline__ bool wait_for(const int* p, int need, int* failed) {
+  if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need) return true;
+  const int64_t t0 = (int64_t)wall_clock64();
+  for (;;) {
+#pragma unroll 1
+    for (int k = 0; k < 64; ++k) {
+      if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need) return true;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (__hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
+    if ((int64_t)wall_clock64() - t0 > kWaitTicks) {
+      __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }
+  }
+}
+
+// nb <= 8 NW
+template <typename E, int NW>
+__global__ __launch_bounds__(64 * NW) void k_chase_sweeps(E* __restrict__ A, int64_t lda,
+                                                          int64_t n, int64_t nb, ChaseState st,
+                                                          E* __restrict__ hh,
+                                                          E* __restrict__ tau) {
+  constexpr int NQ = 8;
+  __shared__ E vs[64], ys[64], py[NW][64], pu[NW][64];
+  __shared__ E sh_tau;
+  __shared__ int sh_s, sh_arrived, sh_ok[NW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // row i0 + lane of column k: a wave-uniform base and a 32-bit lane offset
+  auto at = [&](int64_t i0, int64_t k) -> E* { return A + (i0 + k * lda) + (unsigned)lane; };
+
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) {
+      sh_s = __hip_atomic_fetch_add(st.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sh_arrived = 0;
+    }
+    __syncthreads();
+    const int64_t s = __builtin_amdgcn_readfirstlane(sh_s);
+    if (s >= n - 1) return;
+    const int64_t J = (n - 1 - s + nb - 1) / nb, Jp = (n - s + nb - 1) / nb;
+    const int64_t slot0 = ehh::slot_offset(n, nb, s);
+    const int* before = st.prog + (s - 1) * kProgStride;
+    E xr[NQ], xd[NQ], xc[NQ];
+
+    // reflector of the column x (wave 0; rows r .. r+L-1 in its lanes, the
+    // column at c): v into LDS, beta and zeros into the matrix
+    auto reflect = [&](E x, int64_t r, int L, int64_t c, int64_t j) {
+      const double ss = wave_sum_dpp(lane >= 1 && lane < L ? abs2(x) : 0.0);
+      const E alpha = read_lane(x, 0);
+      const double ar = re(alpha), ai = im(alpha);
+      E tv = zero<E>(), sc = zero<E>();
+      double beta = ar;
+      if (ss != 0.0 || ai != 0.0) {
+        const double h = sqrt(ar * ar + ai * ai + ss);
+        beta = ar >= 0.0 ? -h : h;
+        if constexpr (std::is_same<E, double>::value) {
+          tv = (beta - ar) / beta;
+          sc = 1.0 / (ar - beta);
+        } else {
+          tv = z64{(beta - ar) / beta, -ai / beta};
+          const double dr = ar - beta, dd = dr * dr + ai * ai;
+          sc = z64{dr / dd, -ai / dd};
+        }
+      }
+      const E v = lane == 0 ? from_re<E>(1.0) : (lane < L ? mul(x, sc) : zero<E>());
+      vs[lane] = v;
+      if (lane == 0) sh_tau = tv;
+      xr[0] = lane == 0 ? from_re<E>(beta) : zero<E>();
+      if (lane < L) store_dev(at(r, c), xr[0]);
+      if (lane < nb) hh[(slot0 + j) * nb + lane] = v;
+      if (lane == 0) tau[slot0 + j] = tv;
+    };
+
+    for (int64_t j = 0; j < J; ++j) {
+      const int64_t r = s + 1 + j * nb;
+      const int L = (int)((nb < n - r) ? nb : n - r);
+      const int nR = j == 0 ? 1 : (int)nb;
+      const int nC = (int)(((r + L + nb < n) ? r + L + nb : n) - r - L);
+      bool ok = true;
+      if (s > 0) ok = wait_for(before, (int)(j + 2 < Jp ? j + 2 : Jp), st.failed);
+      asm volatile("" ::: "memory");
+      if (lane == 0) sh_ok[wave] = ok ? 1 : 0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int k = wave + NW * q;
+        xd[q] = (k < L && lane < L && lane >= k) ? load_dev(at(r, r + k)) : zero<E>();
+        xc[q] = (k < L && lane < nC) ? load_dev(at(r + L, r + k)) : zero<E>();
+      }
+      if (j == 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) xr[q] = zero<E>();
+        if (wave == 0) reflect(lane < L ? load_dev(at(r, s)) : zero<E>(), r, L, s, 0);
+      }
+      __syncthreads();
+      {
+        int all = 1;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) all &= sh_ok[w];
+        if (!__builtin_amdgcn_readfirstlane(all)) return;  // the same in every wave
+      }
+      const E tv = sh_tau, vl = vs[lane];
+      const bool act = __builtin_amdgcn_readfirstlane(re(tv) != 0.0 || im(tv) != 0.0) != 0;
+      E vk[NQ], wr;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) vk[q] = read_lane(vl, wave + NW * q);
+      if (act) {
+        const E cvl = conj_(vl);
+        E p[NQ], ry = zero<E>(), ru = zero<E>();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) p[q] = mul(cvl, xr[q]);
+        wr = wave_sum8(p);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          p[q] = lane > wave + NW * q ? mul(cvl, xd[q]) : zero<E>();
+        const E cs = wave_sum8(p);
+        // (v^H D)_k = conj((D v)_k)
+        if ((lane & 7) == 0) ys[wave + NW * (lane >> 3)] = conj_(cs);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          ry = add(ry, mul(xd[q], vk[q]));
+          ru = add(ru, mul(xc[q], vk[q]));
+        }
+        py[wave][lane] = ry;
+        pu[wave][lane] = ru;
+      }
+      __syncthreads();
+      if (act) {
+        // every wave forms y and u of its rows (the same bits in each)
+        E yl = lane < 8 * NW ? ys[lane] : zero<E>(), us = zero<E>();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          yl = add(yl, py[w][lane]);
+          us = add(us, pu[w][lane]);
+        }
+        const E ul = mul(tv, us);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) xc[q] = sub(xc[q], mul(ul, conj_(vk[q])));
+        const E ct = conj_(tv);
+        const double mu = wave_sum_dpp(re(mul(conj_(vl), yl)));
+        const double h2 = 0.5 * abs2(tv) * mu;
+        const E wl = sub(mul(tv, yl), mul(from_re<E>(h2), vl));
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const int k = wave + NW * q;
+          const E wk = read_lane(wl, k), rk = mul(ct, read_lane(wr, 8 * q));
+          // column 0 is the reduced one (j = 0: the only one)
+          if (k >= 1) xr[q] = sub(xr[q], mul(vl, rk));
+          xd[q] = sub(xd[q], add(mul(wl, conj_(vk[q])), mul(vl, conj_(wk))));
+          if (lane == k) xd[q] = real_part(xd[q]);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int k = wave + NW * q;
+        if (lane < L && k >= 1 && k < nR) store_dev(at(r, r - nb + k), xr[q]);
+        if (lane < L && k < L && lane >= k) store_dev(at(r, r + k), xd[q]);
+        xr[q] = xc[q];
+      }
+      if (wave == 0 && nC > 0) reflect(xc[0], r + L, nC, r, j + 1);
+      // every wave's stores are acknowledged, then the last one counts the step
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (lane == 0) {
+        const int a = __hip_atomic_fetch_add(&sh_arrived, 1, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (a == (int)(j + 1) * NW - 1)
+          __hip_atomic_store(st.prog + s * kProgStride, (int)(j + 1), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+}
+
+// The upper triangle of the result (the one-launch chase updates only the
 // lower one): A[k-1, k] = e[k-1], zeros above it up to 2 nb rows.
-__global__ __launch_bounds__(256) void k_upper_out(double* __restrict__ A, int64_t lda,
-                                                   int64_t n, int64_t nb,
-                                                   const double* __restrict__ e) {
+template <typename E>
+__global__ __launch_bounds__(256) void k_upper_out(E* __restrict__ A, int64_t lda, int64_t n,
+                                                   int64_t nb, const double* __restrict__ e) {
   const int64_t k = (int64_t)blockIdx.x + 1;   // columns 1 .. n-1
   const int64_t span = 2 * nb;
   for (int64_t q = threadIdx.x; q < span; q += blockDim.x) {
     const int64_t i = k - 1 - q;
     if (i < 0) break;
-    A[i + k * lda] = q == 0 ? e[k - 1] : 0.0;
+    A[i + k * lda] = from_re<E>(q == 0 ? e[k - 1] : 0.0);
   }
 }
 
 template <typename E>
 __global__ __launch_bounds__(256) void k_diag_out(const E* __restrict__ A, int64_t lda,
                                                   int64_t n, double* __restrict__ d,
-                                                  double* __restrict__ e) {
+                                                  double* __restrict__ e,
+                                                  const int* __restrict__ failed) {
+  const bool bad = failed && *failed != 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    d[i] = re(A[i + i * lda]);
+    d[i] = bad ? __builtin_nan("") : re(A[i + i * lda]);
     if (i + 1 < n) e[i] = re(A[i + 1 + i * lda]);
   }
 }
@@ -397,39 +593,59 @@ __global__ __launch_bounds__(256) void k_diag_out(const E* __restrict__ A, int64
 // J(s) = ceil((n-1-s)/nb)
 inline int64_t steps_of(int64_t n, int64_t nb, int64_t s) { return (n - 1 - s + nb - 1) / nb; }
 
+// nb <= 64: the one-launch chase
+template <typename E>
+int run_sweeps(int64_t n, int64_t nb, E* A, int64_t lda, double* d, double* e, E* hh, E* tau,
+               hipStream_t st) {
+  const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
+  int* words = nullptr;
+  const size_t bytes = ((size_t)std::max<int64_t>(n - 1, 1) + 1) * kProgStride * sizeof(int);
+  const hipError_t err = ehh::ws_alloc((void**)&words, bytes, st);
+  if (err != hipSuccess)
+    return err == hipErrorOutOfMemory ? ELPA_ERR_NOMEM : ELPA_ERR_DEVICE;
+  const ChaseState cs{words + kProgStride, words, words + 1};
+  if (n > 1) {
+    hipLaunchKernelGGL(k_chase_clear, dim3((unsigned)((n + 254) / 256)), dim3(256), 0, st, cs, n);
+    // a sweep lags two steps behind the one before it, so at most about J / 2
+    // are under way; the tickets make any number of workgroups correct
+    const int64_t J = (n - 1 + nb - 1) / nb;
+    const unsigned wgs = (unsigned)std::min<int64_t>({n - 1, J / 2 + 2, 512});
+    if (nb > 32)
+      hipLaunchKernelGGL((k_chase_sweeps<E, 8>), dim3(wgs), dim3(512), 0, st, A, lda, n, nb, cs,
+                         hh, tau);
+    else
+      hipLaunchKernelGGL((k_chase_sweeps<E, 4>), dim3(wgs), dim3(256), 0, st, A, lda, n, nb, cs,
+                         hh, tau);
+  }
+  hipLaunchKernelGGL(k_diag_out<E>, dim3(g), dim3(256), 0, st, (const E*)A, lda, n, d, e,
+                     (const int*)(n > 1 ? cs.failed : nullptr));
+  if (n > 1)
+    hipLaunchKernelGGL(k_upper_out<E>, dim3((unsigned)n - 1), dim3(256), 0, st, A, lda, n, nb,
+                       (const double*)e);
+  const bool ok = hipGetLastError() == hipSuccess;
+  return ehh::ws_free(words, st) == hipSuccess && ok ? ELPA_OK : ELPA_ERR_DEVICE;
+}
+
 template <typename E>
 int run(int64_t n, int64_t nb, E* A, int64_t lda, double* d, double* e, E* hh, E* tau,
         hipStream_t st) {
+  if (nb <= 64) return run_sweeps<E>(n, nb, A, lda, d, e, hh, tau, st);
   // launches t = 0 .. T-1 with T = max_s (3 s + J(s)); the active sweeps of
   // launch t are s_lo(t) .. min(t / kLag, n - 2), s_lo the least s with
   // 3 s + J(s) > t (3 s + J(s) increases with s)
   int64_t T = 0;
   for (int64_t s = 0; s <= n - 2; ++s) T = std::max(T, kLag * s + steps_of(n, nb, s));
-  // real bands up to 64 wide take the register, lower-triangle steps
-  constexpr bool real = std::is_same<E, double>::value;
-  const bool lower = real && nb <= 64;
   int64_t s_lo = 0;
   for (int64_t t = 0; t < T; ++t) {
     while (s_lo <= n - 2 && kLag * s_lo + steps_of(n, nb, s_lo) <= t) ++s_lo;
     const int64_t s_hi = std::min<int64_t>(t / kLag, n - 2);
     if (s_hi < s_lo) continue;
-    if constexpr (real) {
-      if (lower) {
-        hipLaunchKernelGGL(k_chase_reg<8>, dim3((unsigned)(s_hi - s_lo + 1)), dim3(512), 0, st, A,
-                           lda, n, nb, t, s_lo, hh, tau);
-        continue;
-      }
-    }
     hipLaunchKernelGGL(k_chase<E>, dim3((unsigned)(s_hi - s_lo + 1)), dim3(512), 0, st, A, lda,
                        n, nb, t, s_lo, hh, tau);
   }
   const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_diag_out<E>, dim3(g), dim3(256), 0, st, (const E*)A, lda, n, d, e);
-  if constexpr (real) {
-    if (lower && n > 1)
-      hipLaunchKernelGGL(k_upper_out, dim3((unsigned)n - 1), dim3(256), 0, st, (double*)A, lda,
-                         n, nb, (const double*)e);
-  }
+  hipLaunchKernelGGL(k_diag_out<E>, dim3(g), dim3(256), 0, st, (const E*)A, lda, n, d, e,
+                     (const int*)nullptr);
   return hipGetLastError() == hipSuccess ? ELPA_OK : ELPA_ERR_DEVICE;
 }
 

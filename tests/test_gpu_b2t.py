@@ -154,3 +154,21 @@ def test_b2t_n2000(torch_dev):
     assert np.max(np.abs(lt - lam)) <= 50 * n * np.finfo(float).eps * np.linalg.norm(B, 2)
     assert np.max(np.abs(d - d0)) <= 1e-7 * scale and np.max(np.abs(e - e0)) <= 1e-7 * scale
     assert rel(hh.cpu().numpy(), hh0) <= 1e-6 and rel(tau.cpu().numpy(), tau0) <= 1e-6
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("n,b", [(66, 33), (200, 48), (193, 64), (192, 64), (65, 64), (257, 31),
+                                 (400, 2), (129, 16)])
+def test_b2t_one_launch_sizes(torch_dev, n, b, cplx):
+    """The one-launch chase at the edges of its blocks: bands that do not fill
+    the four or eight waves, last steps of length 1 and of full length, more
+    sweeps than workgroups, and one sweep only."""
+    torch, dev = torch_dev
+    B = band_matrix(n, b, cplx, 440 + n)
+    d0, e0, hh0, tau0 = stage2.band_to_tridiag(B, b)
+    print(f"b2t n={n} b={b} cplx={cplx}", flush=True)
+    d, e, hh, tau = (x.cpu().numpy() for x in gpu_b2t(torch, dev, B, b))
+    scale = float(np.max(np.abs(B)))
+    assert np.max(np.abs(d - d0)) <= 1e-12 * scale * n ** 0.5
+    assert np.max(np.abs(e - e0)) <= 1e-12 * scale * n ** 0.5
+    assert rel(hh, hh0) <= 1e-10 and rel(tau, tau0) <= 1e-10
