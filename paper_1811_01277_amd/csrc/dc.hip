@@ -9,7 +9,7 @@
 // A merge of node [lo, hi) (split at mid, s rows) with the children's sorted
 // eigenvalues in L[lo, mid) and L[mid, hi) and eigenvectors in the diagonal
 // blocks of Q:
-//   prep:     z = [last row of Q1; sign(e) first row of Q2] / sqrt(2),
+//   prep:     (one workgroup per merge) z = [last row of Q1; sign(e) first row of Q2] / sqrt(2),
 //             rho' = 2 rho; the two sorted lists merged by rank; deflation
 //             scan in sorted order (tol = 8 eps max(|D|, |z|)): rho'|z_p| <=
 //             tol deflates p; else if the previous candidate pj is close,
@@ -50,7 +50,9 @@ struct Node {
   int64_t lo, mid, hi, woff;
 };
 
-constexpr int kSmall = 256;  // merges up to this size use the in-kernel product
+// merges up to this size use the in-kernel product, larger ones rocBLAS (which
+// needs the survivor counts on the host: one wait per level)
+constexpr int kSmall = 1024;
 constexpr double kEps = 1.1102230246251565e-16;  // 2^-53
 
 struct Ws {
@@ -95,10 +97,42 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return r;
 }
 
+constexpr int kWaves = 4;  // of a k_prep workgroup
+
+// Number of earlier threads of the workgroup with `on`, cnt[kWaves] = all of
+// them (every thread calls it; cnt holds until the next call).
+__device__ __forceinline__ int block_rank(bool on, int* cnt) {
+  const unsigned long long b = __ballot(on);
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  __syncthreads();
+  if (l == 0) cnt[w] = __popcll(b);
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int k = 0; k < kWaves; ++k) {
+    if (k < w) before += cnt[k];
+    all += cnt[k];
+  }
+  if (threadIdx.x == 0) cnt[kWaves] = all;
+  __syncthreads();
+  return before + __popcll(b & ((1ull << l) - 1));
+}
+
+// Deflation test of the sorted neighbours pj, p: rotating them so that
+// z_pj = 0 leaves an off-diagonal entry of at most tol.
+__device__ __forceinline__ bool rotates(double dp, double zp, double dpj, double zpj, double tol,
+                                        double* c, double* sn) {
+  const double r = hypot(zp, zpj);
+  *c = zp / r;
+  *sn = -zpj / r;
+  const double t = dp - dpj;
+  return fabs(t * *c * *sn) <= tol;
+}
+
 // One workgroup (256 threads) per merge.
 __global__ __launch_bounds__(256) void k_prep(const Node* __restrict__ nodes, int64_t n,
                                               const double* __restrict__ e, Ws w) {
   __shared__ double red[4];
+  __shared__ int cnt[kWaves + 1];
   const Node nd = nodes[blockIdx.x];
   const int64_t lo = nd.lo, mid = nd.mid, s = nd.hi - nd.lo, s1 = nd.mid - nd.lo;
   const double beta = e[mid - 1];
@@ -133,81 +167,126 @@ __global__ __launch_bounds__(256) void k_prep(const Node* __restrict__ nodes, in
     w.Ds[lo + rank] = val;
     w.zs[lo + rank] = zv;
     w.rflag[lo + t] = 0;
+    w.dfl[lo + t] = 0;
     dmax = fmax(dmax, fabs(val));
     zmax = fmax(zmax, fabs(zv));
   }
   dmax = block_max(dmax, red);
   zmax = block_max(zmax, red);
   __syncthreads();
-  if (threadIdx.x != 0) return;
   const double tol = 8.0 * kEps * fmax(dmax, zmax);
   double* Ds = w.Ds + lo;
   double* zs = w.zs + lo;
-  int32_t K = 0, ndf = 0, nrot = 0;
-  int64_t pj = -1;
-  double dpj = 0.0, zpj = 0.0;  // the candidate's current values
-  for (int64_t p = 0; p < s; ++p) {
-    double dp = Ds[p], zp = zs[p];
-    if (rho2 * fabs(zp) <= tol) {
-      w.dfl[lo + ndf++] = (int32_t)p;
-      continue;
+  int32_t* nlist = w.ndl + lo;    // kept positions, later the survivors
+  int32_t* flag = w.gidx + lo;    // per position: 0 kept, 1 negligible, 2 rotated away
+  int32_t* cand = w.org + lo;     // entries of nlist whose pair passes the rotation test
+  // Kept (not negligible) positions in order.
+  int64_t nk = 0;
+  for (int64_t p0 = 0; p0 < s; p0 += blockDim.x) {
+    const int64_t p = p0 + threadIdx.x;
+    const bool in = p < s, keep = in && !(rho2 * fabs(zs[p]) <= tol);
+    const int at = block_rank(keep, cnt);
+    if (in) flag[p] = keep ? 0 : 1;
+    if (keep) nlist[nk + at] = (int32_t)p;
+    nk += cnt[kWaves];
+  }
+  __syncthreads();
+  // The rotation test of every neighbouring pair of kept positions, with the
+  // values they start with.  A rotation changes its later position, so only
+  // the pair after it has to be tested again: one thread follows these chains,
+  // and the long serial part of the scan is left to the pairs that rotate
+  // (the whole scan in one thread: 0.19 ms per merge level at n = 1000, 0.61 ms
+  // at n = 4000).
+  int64_t nc = 0;
+  for (int64_t q0 = 1; q0 < nk; q0 += blockDim.x) {
+    const int64_t q = q0 + threadIdx.x;
+    bool rot = false;
+    if (q < nk) {
+      const int64_t p = nlist[q], pj = nlist[q - 1];
+      double c, sn;
+      rot = rotates(Ds[p], zs[p], Ds[pj], zs[pj], tol, &c, &sn);
     }
-    if (pj < 0) {
-      pj = p, dpj = dp, zpj = zp;
-      continue;
+    const int at = block_rank(rot, cnt);
+    if (rot) cand[nc + at] = (int32_t)q;
+    nc += cnt[kWaves];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t nrot = 0;
+    int64_t done = 0;  // pairs (q - 1, q) with q <= done are decided
+    for (int64_t x = 0; x < nc; ++x) {
+      int64_t q = cand[x];
+      if (q <= done) continue;
+      for (; q < nk; ++q) {
+        const int64_t p = nlist[q], pj = nlist[q - 1];
+        const double dp = Ds[p], zp = zs[p], dpj = Ds[pj], zpj = zs[pj];
+        double c, sn;
+        if (!rotates(dp, zp, dpj, zpj, tol, &c, &sn)) break;
+        Ds[pj] = dpj * c * c + dp * sn * sn;
+        zs[pj] = 0.0;
+        Ds[p] = dpj * sn * sn + dp * c * c;
+        zs[p] = hypot(zp, zpj);
+        w.ra[lo + nrot] = (int32_t)pj;
+        w.rb[lo + nrot] = (int32_t)p;
+        w.rc[lo + nrot] = c;
+        w.rs[lo + nrot] = sn;
+        ++nrot;
+        w.rflag[lo + pj] = 1;
+        w.rflag[lo + p] = 1;
+        flag[pj] = 2;
+        // the pair deflates when its later position is reached
+        w.dfl[lo + p] = (int32_t)pj + 1;
+      }
+      done = q;
     }
-    const double r = hypot(zp, zpj);
-    const double c = zp / r, sn = -zpj / r;
-    const double t = dp - dpj;
-    if (fabs(t * c * sn) <= tol) {
-      const double t2 = dpj * c * c + dp * sn * sn;
-      dp = dpj * sn * sn + dp * c * c;
-      zp = r;
-      Ds[pj] = t2;
-      zs[pj] = 0.0;
-      Ds[p] = dp;
-      zs[p] = zp;
-      w.ra[lo + nrot] = (int32_t)pj;
-      w.rb[lo + nrot] = (int32_t)p;
-      w.rc[lo + nrot] = c;
-      w.rs[lo + nrot] = sn;
-      ++nrot;
-      w.rflag[lo + pj] = 1;
-      w.rflag[lo + p] = 1;
-      w.dfl[lo + ndf++] = (int32_t)pj;
-    } else {
-      w.ndl[lo + K] = (int32_t)pj;
-      w.delta[lo + K] = dpj;
-      w.wv[lo + K] = zpj;
-      ++K;
+    w.nrot[blockIdx.x] = nrot;
+  }
+  __syncthreads();
+  // Survivors in order, with their group: the rows their column can be nonzero
+  // in are child 1's only, both (rotated), child 2's only.  Deflated positions
+  // in the order the scan meets them (a rotated one at its partner).
+  int64_t K = 0, ndf = 0;
+  int64_t gn[3] = {0, 0, 0};
+  for (int64_t p0 = 0; p0 < s; p0 += blockDim.x) {
+    const int64_t p = p0 + threadIdx.x;
+    const bool in = p < s, keep = in && flag[p] == 0;
+    const int g = !keep ? -1 : (w.rflag[lo + p] ? 1 : (w.perm[lo + p] < s1 ? 0 : 2));
+    const int32_t pair = in && flag[p] != 1 ? w.dfl[lo + p] : 0;
+    const int32_t gone = in && flag[p] == 1 ? (int32_t)p + 1 : pair;
+    const double dv = keep ? Ds[p] : 0.0, zv = keep ? zs[p] : 0.0;
+    const int at = block_rank(keep, cnt);
+    const int nkeep = cnt[kWaves];
+    const int df = block_rank(gone != 0, cnt);  // its barriers separate reads and writes
+    const int ndel = cnt[kWaves];
+    if (keep) {
+      nlist[K + at] = (int32_t)p;
+      w.delta[lo + K + at] = dv;
+      w.wv[lo + K + at] = zv;
     }
-    pj = p, dpj = dp, zpj = zp;
+    if (gone != 0) w.dfl[lo + ndf + df] = gone - 1;
+    for (int h = 0; h < 3; ++h) {
+      const int gi = block_rank(g == h, cnt);
+      if (g == h) cand[K + at] = (int32_t)(gn[h] + gi);
+      gn[h] += cnt[kWaves];
+    }
+    K += nkeep;
+    ndf += ndel;
   }
-  if (pj >= 0) {
-    w.ndl[lo + K] = (int32_t)pj;
-    w.delta[lo + K] = dpj;
-    w.wv[lo + K] = zpj;
-    ++K;
+  __syncthreads();
+  // gidx = the column of Qc (and row of U) of each survivor
+  for (int64_t j = threadIdx.x; j < K; j += blockDim.x) {
+    const int32_t pos = nlist[j];
+    const int g = w.rflag[lo + pos] ? 1 : (w.perm[lo + pos] < s1 ? 0 : 2);
+    w.gidx[lo + j] = cand[j] + (int32_t)(g == 0 ? 0 : (g == 1 ? gn[0] : gn[0] + gn[1]));
   }
-  // survivors grouped by the rows their column can be nonzero in: child 1
-  // only, both (rotated), child 2 only; gidx = the column of Qc (and row of U)
-  int32_t g[3] = {0, 0, 0};
-  for (int32_t j = 0; j < K; ++j) {
-    const int32_t pos = w.ndl[lo + j];
-    ++g[w.rflag[lo + pos] ? 1 : (w.perm[lo + pos] < s1 ? 0 : 2)];
+  if (threadIdx.x == 0) {
+    w.grp[3 * blockIdx.x] = (int32_t)gn[0];
+    w.grp[3 * blockIdx.x + 1] = (int32_t)gn[1];
+    w.grp[3 * blockIdx.x + 2] = (int32_t)gn[2];
+    w.K[blockIdx.x] = (int32_t)K;
+    w.ndf[blockIdx.x] = (int32_t)ndf;
+    w.rho[blockIdx.x] = rho2;
   }
-  int32_t c[3] = {0, g[0], g[0] + g[1]};
-  for (int32_t j = 0; j < K; ++j) {
-    const int32_t pos = w.ndl[lo + j];
-    w.gidx[lo + j] = c[w.rflag[lo + pos] ? 1 : (w.perm[lo + pos] < s1 ? 0 : 2)]++;
-  }
-  w.grp[3 * blockIdx.x] = g[0];
-  w.grp[3 * blockIdx.x + 1] = g[1];
-  w.grp[3 * blockIdx.x + 2] = g[2];
-  w.K[blockIdx.x] = K;
-  w.ndf[blockIdx.x] = ndf;
-  w.nrot[blockIdx.x] = nrot;
-  w.rho[blockIdx.x] = rho2;
 }
 
 // Flattened grid: block b -> merge b / per, item (b % per) * 256 + tid.
@@ -373,21 +452,75 @@ __global__ __launch_bounds__(256) void k_zero(double* __restrict__ C, int64_t ld
     C[(x / rows) * ldc + x % rows] = 0.0;
 }
 
-// Out = Qc U for merges of at most 256 rows: one workgroup per merge, a
-// thread per row.
-__global__ __launch_bounds__(256) void k_gemm_small(const Node* __restrict__ nodes, Ws w) {
-  const Node nd = nodes[blockIdx.x];
-  const int64_t s = nd.hi - nd.lo, r = threadIdx.x;
-  const int64_t K = w.K[blockIdx.x];
-  if (r >= s) return;
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// Out = Qc U for merges of at most kSmall rows, the survivor counts read on
+// the device: one workgroup per 64 x 64 tile of a merge's Out, each of its
+// four waves a 32 x 32 quarter as 2 x 2 fp64 MFMA tiles, 16 columns of Qc at a
+// time through LDS.  Rows of one child only meet the survivors that can be
+// nonzero there (groups 0-1 above the split, 1-2 below).  A thread per row of
+// a merge (one workgroup each) took 1.22 ms per level from 256 rows on, nine
+// tenths of it a serial chain of loads; with the tiles the
+// whole solve went from 13.1 to 1.7 ms at n = 1000 and from 23.6 to 6.6 ms at
+// n = 4000 (with the parallel deflation scan of k_prep).
+__global__ __launch_bounds__(256) void k_gemm_tile(const Node* __restrict__ nodes, int64_t tiles,
+                                                   Ws w) {
+  __shared__ double As[16][65], Bs[64][17];  // Qc chunk by column, U chunk by column
+  const int64_t m = (int64_t)blockIdx.x / (tiles * tiles);
+  const int64_t tl = (int64_t)blockIdx.x % (tiles * tiles);
+  const Node nd = nodes[m];
+  const int64_t s = nd.hi - nd.lo, s1 = nd.mid - nd.lo, K = w.K[m];
+  const int64_t r0 = tl % tiles * 64, i0 = tl / tiles * 64;
+  if (r0 >= s || i0 >= K) return;
+  const int64_t g0 = w.grp[3 * m], g1 = w.grp[3 * m + 1];
+  const int64_t jlo = r0 >= s1 ? g0 : 0, jhi = r0 + 64 <= s1 ? g0 + g1 : K;
   const double* __restrict__ Qc = w.Qc + nd.woff;
   const double* __restrict__ U = w.U + nd.woff;
   double* __restrict__ Out = w.Out + nd.woff;
-  for (int64_t i = 0; i < K; ++i) {
-    double acc = 0.0;
-    for (int64_t j = 0; j < K; ++j) acc = fma(Qc[j * s + r], U[i * s + j], acc);
-    Out[i * s + r] = acc;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = (wave & 1) * 32, wc = (wave >> 1) * 32, lr = lane & 15, lq = lane >> 4;
+  d4 acc[2][2] = {};
+  for (int64_t j0 = jlo; j0 < jhi; j0 += 16) {
+    double a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t ja = j0 + (tid >> 6) + 4 * u, ra = r0 + (tid & 63);
+      a[u] = (ja < jhi && ra < s) ? Qc[ja * s + ra] : 0.0;
+      const int64_t jb = j0 + (tid & 15), ib = i0 + (tid >> 4) + 16 * u;
+      b[u] = (jb < jhi && ib < K) ? U[ib * s + jb] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      As[(tid >> 6) + 4 * u][tid & 63] = a[u];
+      Bs[(tid >> 4) + 16 * u][tid & 15] = b[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      double x[2], y[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        x[t] = As[4 * kk + lq][wr + 16 * t + lr];
+        y[t] = Bs[wc + 16 * t + lr][4 * kk + lq];
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+          acc[t][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[t], y[v], acc[t][v], 0, 0, 0);
+    }
   }
+  // result register q of lane l: row l / 16 + 4 q, column l % 16
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t r = r0 + wr + 16 * t + lq + 4 * q, i = i0 + wc + 16 * v + lr;
+        if (r < s && i < K) Out[i * s + r] = acc[t][v][q];
+      }
 }
 
 // vals[lo + x]: x < K the roots, then the deflated values.
@@ -555,7 +688,9 @@ int run(int64_t n, int64_t nev, const double* d, const double* e, double* lam, E
     hipLaunchKernelGGL(k_vec, dim3((unsigned)(M * smax)), b256, 0, st, nl, smax, w);
     hipLaunchKernelGGL(k_compress, dim3((unsigned)(M * smax)), b256, 0, st, nl, smax, w);
     if (smax <= kSmall) {
-      hipLaunchKernelGGL(k_gemm_small, dim3((unsigned)M), b256, 0, st, nl, w);
+      const int64_t tiles = (smax + 63) / 64;
+      hipLaunchKernelGGL(k_gemm_tile, dim3((unsigned)(M * tiles * tiles)), b256, 0, st, nl, tiles,
+                         w);
     } else {
       if (hipMemcpyAsync(Kh.data(), w.K, (size_t)M * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
           hipMemcpyAsync(Gh.data(), w.grp, (size_t)M * 12, hipMemcpyDeviceToHost, st) !=

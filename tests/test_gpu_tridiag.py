@@ -250,3 +250,16 @@ def test_eigenvectors_api(torch_dev, n, nbw, nev, cplx):
     assert np.max(np.abs(lam - ref)) <= 8 * n * EPS * max(np.linalg.norm(A, 2), 1e-300)
     assert checks.norm1(A @ Z - Z * lam[None, :nev]) <= 50 * n * EPS * checks.norm1(A)
     assert checks.orth_ratio(Z) < 50
+
+
+@pytest.mark.parametrize("kind", ["gauss", "wilkinson", "repeated", "split"])
+@pytest.mark.parametrize("n", [64, 65, 129, 1024, 1025])
+def test_dc_merge_tiles_and_deflation(torch_dev, kind, n):
+    """Merges at the edges of the product's 64 x 64 tiles and at the size from
+    which rocBLAS takes over, with few and with many deflations (chains of
+    rotations among equal eigenvalues, negligible z entries)."""
+    torch, dev = torch_dev
+    d, e = make(kind, n, 900 + n)
+    print(f"tridiag_eigh kind={kind} n={n}", flush=True)
+    lam, Z = gpu_solve(torch, dev, d, e)
+    check_solution(d, e, lam, Z, (kind, n))
