@@ -1,8 +1,9 @@
 // Full -> band reduction (C ABI in include/elpa_f2b.h; Kus et al., Sec. 2).
 //
 // Panel p: the m = n-p-nbw rows below the band of columns [p, p+nbw) get a
-// Householder QR, one column at a time, spread over G workgroups of 256 rows
-// each, two launches per column and no waiting between workgroups:
+// Householder QR, one column at a time.  Bands up to 64 wide do a panel in one
+// launch (k_panel below).  Wider ones spread each column over G workgroups of
+// 256 rows, two launches per column and no waiting between workgroups:
 //   reflect(i): every workgroup sums the G partial norms of column p+i in a
 //     fixed order and derives the same larfg result (tau, beta, scale); it
 //     scales its rows of the column into V (zeros above the unit lead) and
@@ -230,6 +231,487 @@ __global__ __launch_bounds__(kRows) void k_update(E* __restrict__ A, int64_t lda
   }
 }
 
+// ---------------------------------------------------------------------------
+// nb <= 64: a panel in one launch
+//
+// A workgroup of four waves keeps 64 RT rows of the panel in registers from
+// its first column to its last: lane l holds rows l + 64 t (t < RT), wave w
+// the columns 4 c + w (c < CW).  Per column i:
+//   1. the wave that holds column i hands it to the others through LDS;
+//   2. every wave forms the products S_j = sum over rows > i of conj(x) a_j
+//      with the column as it is, not yet scaled to a reflector.  With the row i
+//      itself (the head) they give the norm for larfg (S_i) and, since
+//      v = (1, sc x), the update's coefficients v^H a_j = a_ij + conj(sc) S_j:
+//      one exchange between workgroups per column, and no norm is downdated;
+//   3. the workgroups' sums are exchanged and added in one fixed order, so all
+//      derive the same bits;
+//   4. larfg, update in registers; a column that has been reduced drops out by
+//      writing the wave's updated columns one place further left.
+//
+// The exchange.  A sum goes out as two (real) or four (complex) 8-byte words,
+// each half of a double and a tag that counts the columns of the call; a
+// reader takes a word when its tag is the column's, so no flag or fence is
+// needed.  Two sets of slots alternate: a workgroup writes a slot again two
+// columns later, after it has read every other workgroup's sums of the column
+// in between, which those send after they have read this slot.
+//
+// Waiting ends because all workgroups of the launch are resident together:
+// each first registers, and only when all have done so does any of them start
+// (state kGo).  Should they not come together within the time limit (the
+// device full of others that wait in the same way), the launch leaves the
+// panel as it was (state kAlone) and k_panel_alone, next on the stream, does
+// it with one workgroup and the same arithmetic.
+//
+// Bound: latency, about two microseconds a column for any number of rows up to
+// kMaxGroups workgroups, half of it the exchange.  Two launches per column (a
+// norm, then the coefficients; 12.5 and 9 us) took 21.5 us: the
+// reduction went from 22.6 to 4.7 ms at n = 1000 and from 100 to 28 ms at
+// n = 4000 (nbw = 64, fp64).
+// ---------------------------------------------------------------------------
+constexpr int kOpen = 0, kGo = 1, kAlone = 2;
+constexpr int kMaxGroups = 256;                       // one per compute unit
+constexpr int64_t kGatherTicks = 10000000;            // 0.1 s of the 100 MHz clock
+constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // never reached once all are resident
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kRor8 = 0x128;
+
+// lanes of even groups of 32 (16) lanes: a summed over the pair of groups, of
+// odd groups: b
+__device__ __forceinline__ double pair32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a),
+                                                  (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a),
+                                                  (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double pair16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a),
+                                                  (unsigned)__double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a),
+                                                  (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+// the same for groups of 8 and of 4 lanes within a row of 16
+template <int CTRL, int BIT>
+__device__ __forceinline__ double pair_dpp(double a, double b) {
+  const bool up = (threadIdx.x & BIT) != 0;
+  return (up ? b : a) + dpp_mov<CTRL>(up ? a : b);
+}
+// x[0..CW) per lane -> lane l: the wave's sum of x[l / (64 / CW)]
+template <int CW>
+__device__ __forceinline__ double wave_sums(const double (&x)[CW]) {
+  static_assert(CW == 8 || CW == 16, "8 or 16 columns per wave");
+  double y[CW / 2], z[CW / 4];
+#pragma unroll
+  for (int i = 0; i < CW / 2; ++i) y[i] = pair32(x[i], x[i + CW / 2]);
+#pragma unroll
+  for (int i = 0; i < CW / 4; ++i) z[i] = pair16(y[i], y[i + CW / 4]);
+  double t;
+  if constexpr (CW == 16) {
+    const double u0 = pair_dpp<kRor8, 8>(z[0], z[2]), u1 = pair_dpp<kRor8, 8>(z[1], z[3]);
+    t = pair_dpp<kHalfMirror, 4>(u0, u1);
+  } else {
+    t = pair_dpp<kRor8, 8>(z[0], z[1]);
+    t += dpp_mov<kHalfMirror>(t);
+  }
+  t += dpp_mov<kXor2>(t);
+  return t + dpp_mov<kXor1>(t);
+}
+template <int CW>
+__device__ __forceinline__ zc wave_sums(const zc (&x)[CW]) {
+  double a[CW], b[CW];
+#pragma unroll
+  for (int i = 0; i < CW; ++i) {
+    a[i] = x[i].re;
+    b[i] = x[i].im;
+  }
+  return zc{wave_sums<CW>(a), wave_sums<CW>(b)};
+}
+// sum over the 64 / CW lanes that share a column, each with its own part
+template <int CW>
+__device__ __forceinline__ double lane_sum(double t) {
+  if constexpr (CW == 8) t += dpp_mov<kHalfMirror>(t);
+  t += dpp_mov<kXor2>(t);
+  return t + dpp_mov<kXor1>(t);
+}
+template <int CW>
+__device__ __forceinline__ zc lane_sum(zc t) {
+  return zc{lane_sum<CW>(t.re), lane_sum<CW>(t.im)};
+}
+__device__ __forceinline__ double read_lane(double x, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                          __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+__device__ __forceinline__ zc read_lane(zc x, int l) {
+  return zc{read_lane(x.re, l), read_lane(x.im, l)};
+}
+
+typedef unsigned long long u64;
+// a value as tagged words (2 per double)
+__device__ __forceinline__ void send(u64* p, double x, unsigned tag) {
+  const u64 t = (u64)tag << 32;
+  __hip_atomic_store(p, t | (unsigned)__double2loint(x), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 1, t | (unsigned)__double2hiint(x), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void send(u64* p, zc x, unsigned tag) {
+  send(p, x.re, tag);
+  send(p + 2, x.im, tag);
+}
+template <int NWORD>
+struct Words {
+  u64 w[NWORD];
+  __device__ __forceinline__ void load(const u64* p) {
+#pragma unroll
+    for (int i = 0; i < NWORD; ++i)
+      w[i] = __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ bool has(unsigned tag) const {
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < NWORD; ++i) ok = ok && (unsigned)(w[i] >> 32) == tag;
+    return ok;
+  }
+  __device__ __forceinline__ void wait(const u64* p, unsigned tag) {
+    if (has(tag)) return;
+    const int64_t t0 = (int64_t)wall_clock64();
+    do {
+#pragma unroll 1
+      for (int k = 0; k < 1024; ++k) {
+        load(p);
+        if (has(tag)) return;
+      }
+    } while ((int64_t)wall_clock64() - t0 < kWaitTicks);
+  }
+  __device__ __forceinline__ void get(double& x) const {
+    x = __hiloint2double((int)(unsigned)w[1], (int)(unsigned)w[0]);
+  }
+  __device__ __forceinline__ void get(zc& x) const {
+    x.re = __hiloint2double((int)(unsigned)w[1], (int)(unsigned)w[0]);
+    x.im = __hiloint2double((int)(unsigned)w[NWORD - 1], (int)(unsigned)w[NWORD - 2]);
+  }
+};
+
+// larfg of (alpha, tail) from alpha and the tail's squared norm
+template <typename E>
+__device__ __forceinline__ void larfg(E alpha, double ss, E* tau, double* beta, E* sc) {
+  const double ar = re(alpha), ai = im(alpha);
+  *tau = from_re<E>(0.0);
+  *beta = ar;
+  *sc = from_re<E>(1.0);
+  if (ss == 0.0 && ai == 0.0) return;
+  const double h = sqrt(ar * ar + ai * ai + ss);
+  const double bt = ar >= 0.0 ? -h : h;
+  if constexpr (std::is_same<E, double>::value) {
+    *tau = (bt - ar) / bt;
+    *sc = 1.0 / (ar - bt);
+  } else {
+    *tau = zc{(bt - ar) / bt, -ai / bt};
+    const double dr = ar - bt, dd = dr * dr + ai * ai;
+    *sc = zc{dr / dd, -ai / dd};
+  }
+  *beta = bt;
+}
+
+// Geometry of one panel and the exchange's memory.
+template <typename E>
+struct Panel {
+  E* A;
+  int64_t lda, r0, p, m;
+  int b, k;  // columns, reflectors
+  E* V;
+  int64_t ldv;
+  E* tau;
+  u64* slots;   // [2][groups + 1][4 CW][words]: the groups' sums, then the head row
+  int* state;   // arrived, state
+  int groups;
+  unsigned tag0;
+  int64_t gather_ticks;
+};
+
+template <typename E>
+struct PanelTraits {
+  static constexpr int RT = std::is_same<E, double>::value ? 4 : 2;  // rows per lane
+  static constexpr int NWORD = std::is_same<E, double>::value ? 2 : 4;
+  static constexpr int ROWS = 64 * RT;
+};
+
+template <typename E, int CW>
+__device__ __forceinline__ u64* slot_of(const Panel<E>& P, unsigned tag, int g, int at) {
+  constexpr int NWORD = PanelTraits<E>::NWORD;
+  return P.slots + (((int64_t)(tag & 1) * (P.groups + 1) + g) * (4 * CW) + at) * NWORD;
+}
+
+__global__ __launch_bounds__(256) void k_panel_clear(u64* __restrict__ slots, int64_t words,
+                                                     int* __restrict__ state, int64_t states,
+                                                     int open) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
+       i += (int64_t)gridDim.x * blockDim.x)
+    slots[i] = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < states;
+       i += (int64_t)gridDim.x * blockDim.x)
+    state[i] = (i & 1) ? open : 0;
+}
+
+// One wave's share of a workgroup's sums for one column: x its rows of the
+// column (zero in the rows up to i).
+template <typename E, int RT, int CW>
+__device__ __forceinline__ E panel_sums(const E (&a)[RT][CW], const E (&x)[RT]) {
+  E p[CW];
+#pragma unroll
+  for (int c = 0; c < CW; ++c) {
+    p[c] = Num<E>::mul(conj_(x[0]), a[0][c]);
+#pragma unroll
+    for (int t = 1; t < RT; ++t) p[c] = Num<E>::add(p[c], Num<E>::mul(conj_(x[t]), a[t][c]));
+  }
+  return wave_sums<CW>(p);
+}
+
+template <typename E, int CW>
+__global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
+  constexpr int RT = PanelTraits<E>::RT, ROWS = PanelTraits<E>::ROWS;
+  constexpr int NWORD = PanelTraits<E>::NWORD;
+  constexpr int SUB = 64 / CW;  // lanes per column
+  __shared__ E xs[ROWS];
+  __shared__ E sh[2];
+  __shared__ int sh_state;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = P.groups, grp = (int)blockIdx.x;
+  const int64_t row0 = (int64_t)grp * ROWS;
+  const int cl = lane / SUB, part = lane % SUB;
+
+  if (G > 1) {
+    if (tid == 0) {
+      int st = __hip_atomic_load(P.state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (st == kOpen) {
+        const int old = __hip_atomic_fetch_add(P.state, 1, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+        int expect = kOpen;
+        if (old == G - 1)
+          __hip_atomic_compare_exchange_strong(P.state + 1, &expect, kGo, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t t0 = (int64_t)wall_clock64();
+        while ((st = __hip_atomic_load(P.state + 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT)) == kOpen) {
+          if ((int64_t)wall_clock64() - t0 > P.gather_ticks) {
+            expect = kOpen;
+            __hip_atomic_compare_exchange_strong(P.state + 1, &expect, kAlone, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+      }
+      sh_state = st;
+    }
+    __syncthreads();
+    if (sh_state != kGo) return;
+  }
+
+  E a[RT][CW];
+#pragma unroll
+  for (int c = 0; c < CW; ++c)
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int64_t row = row0 + lane + 64 * t;
+      const int j = 4 * c + wave;
+      a[t][c] = (row < P.m && j < P.b) ? P.A[P.r0 + row + (P.p + j) * P.lda] : from_re<E>(0.0);
+    }
+
+  int gone = 0;  // of this wave's columns
+  for (int i = 0; i < P.k; ++i) {
+    const bool own = (i & 3) == wave;
+    const unsigned tag = P.tag0 + (unsigned)i;
+    if (own) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t) xs[lane + 64 * t] = a[t][0];
+    }
+    __syncthreads();
+    E x[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      x[t] = xs[lane + 64 * t];
+      if (row0 + lane + 64 * t <= i) x[t] = from_re<E>(0.0);
+    }
+    // sums of column 4 (cl + gone) + wave, the same in the SUB lanes of cl
+    E S = panel_sums<E, RT, CW>(a, x), head = from_re<E>(0.0);
+    if (grp == 0) {
+      // row i is lane i's first row (i < 64)
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const E hc = read_lane(a[0][c], i);
+        if (cl == c) head = hc;
+      }
+    }
+    if (G > 1) {
+      const int at = wave * CW + cl;
+      if (part == 0) send(slot_of<E, CW>(P, tag, grp, at), S, tag);
+      if (grp == 0 && part == 1) send(slot_of<E, CW>(P, tag, G, at), head, tag);
+      // lane (cl, part) adds the groups part, part + SUB, ...; a batch of loads
+      // in flight at once
+      constexpr int U = 4;
+      Words<NWORD> hw;
+      if (grp != 0) hw.load(slot_of<E, CW>(P, tag, G, at));
+      E acc = from_re<E>(0.0);
+      for (int g0 = part; g0 < G; g0 += U * SUB) {
+        Words<NWORD> w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (g0 + u * SUB < G) w[u].load(slot_of<E, CW>(P, tag, g0 + u * SUB, at));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (g0 + u * SUB < G) {
+            w[u].wait(slot_of<E, CW>(P, tag, g0 + u * SUB, at), tag);
+            E y;
+            w[u].get(y);
+            acc = Num<E>::add(acc, y);
+          }
+      }
+      S = lane_sum<CW>(acc);
+      if (grp != 0) {
+        hw.wait(slot_of<E, CW>(P, tag, G, at), tag);
+        hw.get(head);
+      }
+    }
+    if (own) {  // lane 0 holds column i's sum and head
+      E tv, sc;
+      double beta;
+      larfg(read_lane(head, 0), re(read_lane(S, 0)), &tv, &beta, &sc);
+      if (lane == 0) {
+        sh[0] = tv;
+        sh[1] = sc;
+        if (grp == 0) {
+          P.tau[P.p + i] = tv;
+          P.A[P.r0 + i + (P.p + i) * P.lda] = from_re<E>(beta);
+        }
+      }
+    }
+    __syncthreads();
+    const E tv = sh[0], sc = sh[1];
+    // coefficient of this lane's column: conj(tau) v^H a_j
+    const E cw = Num<E>::mul(conj_(tv), Num<E>::add(head, Num<E>::mul(conj_(sc), S)));
+    E v[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int64_t row = row0 + lane + 64 * t;
+      v[t] = row == i ? from_re<E>(1.0) : Num<E>::mul(x[t], sc);
+      if (own && row < P.m) P.V[P.r0 + row + (P.p + i) * P.ldv] = v[t];
+    }
+    // row i of the result (v = 1 there), columns right of i
+    if (grp == 0 && part == 0 && !(own && cl == 0)) {
+      const int j = 4 * (cl + gone) + wave;
+      if (j < P.b) P.A[P.r0 + i + (P.p + j) * P.lda] = sub(head, cw);
+    }
+    if (own) {
+#pragma unroll
+      for (int c = 1; c < CW; ++c) {
+        const E w = read_lane(cw, c * SUB);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) a[t][c - 1] = sub(a[t][c], Num<E>::mul(v[t], w));
+      }
+#pragma unroll
+      for (int t = 0; t < RT; ++t) a[t][CW - 1] = from_re<E>(0.0);
+      ++gone;
+    } else {
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const E w = read_lane(cw, c * SUB);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) a[t][c] = sub(a[t][c], Num<E>::mul(v[t], w));
+      }
+    }
+  }
+  // zeros below the diagonal of the reduced columns; a panel with fewer rows
+  // than columns has all its rows written above
+  int first = lane;
+  asm volatile("" : "+v"(first));  // addresses are formed anew, not kept from the loads above
+#pragma unroll 1
+  for (int j = wave; j < P.b; j += 4)
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int64_t row = row0 + first + 64 * t;
+      if (row < P.m && row > j) P.A[P.r0 + row + (P.p + j) * P.lda] = from_re<E>(0.0);
+    }
+}
+
+// The panel by one workgroup, where k_panel's workgroups did not come together
+// (no work otherwise): the same sums in the same order, the panel in A.
+template <typename E, int CW>
+__global__ __launch_bounds__(256, 1) void k_panel_alone(Panel<E> P) {
+  constexpr int RT = PanelTraits<E>::RT, ROWS = PanelTraits<E>::ROWS;
+  constexpr int SUB = 64 / CW;
+  __shared__ E sh[2];
+  if (__hip_atomic_load(P.state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kGo) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cl = lane / SUB, part = lane % SUB;
+  for (int i = 0; i < P.k; ++i) {
+    const bool own = (i & 3) == wave;
+    const int gone = i > wave ? (i - wave + 3) / 4 : 0;
+    E acc = from_re<E>(0.0);
+    for (int g = 0; g < P.groups; ++g) {
+      E a[RT][CW], x[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int64_t row = (int64_t)g * ROWS + lane + 64 * t;
+        x[t] = row < P.m && row > i ? P.A[P.r0 + row + (P.p + i) * P.lda] : from_re<E>(0.0);
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          const int j = 4 * (c + gone) + wave;
+          a[t][c] = (row < P.m && j < P.b) ? P.A[P.r0 + row + (P.p + j) * P.lda]
+                                           : from_re<E>(0.0);
+        }
+      }
+      const E S = panel_sums<E, RT, CW>(a, x);
+      if (g % SUB == part) acc = Num<E>::add(acc, S);
+    }
+    const E S = lane_sum<CW>(acc);
+    const int jl = 4 * (cl + gone) + wave;
+    const E head = jl < P.b ? P.A[P.r0 + i + (P.p + jl) * P.lda] : from_re<E>(0.0);
+    double beta = 0.0;
+    if (own) {
+      E tv, sc;
+      larfg(read_lane(head, 0), re(read_lane(S, 0)), &tv, &beta, &sc);
+      if (lane == 0) {
+        sh[0] = tv;
+        sh[1] = sc;
+        P.tau[P.p + i] = tv;
+      }
+    }
+    __syncthreads();
+    const E tv = sh[0], sc = sh[1];
+    const E cw = Num<E>::mul(conj_(tv), Num<E>::add(head, Num<E>::mul(conj_(sc), S)));
+    E w[CW];
+#pragma unroll
+    for (int c = 0; c < CW; ++c) w[c] = read_lane(cw, c * SUB);
+    for (int64_t row = lane; row < P.m; row += 64) {
+      const E x = P.A[P.r0 + row + (P.p + i) * P.lda];
+      const E v = row == i ? from_re<E>(1.0) : (row > i ? Num<E>::mul(x, sc) : from_re<E>(0.0));
+      if (own) P.V[P.r0 + row + (P.p + i) * P.ldv] = v;
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const int j = 4 * (c + gone) + wave;
+        if (j > i && j < P.b && row >= i) {
+          E& y = P.A[P.r0 + row + (P.p + j) * P.lda];
+          y = sub(y, Num<E>::mul(v, w[c]));
+        }
+      }
+    }
+    __syncthreads();
+    if (own)
+      for (int64_t row = lane; row < P.m; row += 64)
+        if (row >= i)
+          P.A[P.r0 + row + (P.p + i) * P.lda] = from_re<E>(row == i ? beta : 0.0);
+    __syncthreads();
+  }
+}
+
 // A[p+j, r0+row] = conj(A[r0+row, p+j]) for the panel
 template <typename E>
 __global__ __launch_bounds__(256) void k_mirror(E* __restrict__ A, int64_t lda, int64_t r0,
@@ -255,7 +737,8 @@ __global__ __launch_bounds__(256) void k_scale(E* __restrict__ W, int64_t ld, in
 }
 
 template <typename E>
-int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipStream_t st) {
+int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipStream_t st,
+        int64_t gather_ticks) {
   using S = typename std::conditional<std::is_same<E, float>::value, float, double>::type;
   const size_t es = sizeof(E);
   const int64_t mmax = n - b;
@@ -270,7 +753,12 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
                off_g = off_pd + al((size_t)Gmax * b * es), off_m = off_g + al((size_t)b * b * es),
                off_w1 = off_m + al((size_t)b * b * es),
                off_w2 = off_w1 + al((size_t)2 * b * mmax * es),
-               off_part = off_w2 + al((size_t)2 * mmax * b * es), total = off_part + al(part_e * es);
+               off_part = off_w2 + al((size_t)2 * mmax * b * es), off_slot = off_part + al(part_e * es);
+  // one-launch panels: their exchange slots and per-panel states
+  constexpr int ROWS = PanelTraits<E>::ROWS, NWORD = PanelTraits<E>::NWORD;
+  const int64_t groups = b <= 64 ? std::min<int64_t>((mmax + ROWS - 1) / ROWS, kMaxGroups) : 0;
+  const int64_t words = 2 * (groups + 1) * 64 * NWORD, panels = (n - 1) / b;
+  const size_t off_state = off_slot + al((size_t)words * 8), total = off_state + al((size_t)panels * 8);
   char* ws = nullptr;
   if (hipMallocAsync((void**)&ws, total, st) != hipSuccess) return ELPA_ERR_NOMEM;
   double* pn0 = (double*)(ws + off_pn);
@@ -281,6 +769,12 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
   E* W1 = (E*)(ws + off_w1);
   E* W2 = (E*)(ws + off_w2);
   E* part = (E*)(ws + off_part);
+  u64* slots = (u64*)(ws + off_slot);
+  int* states = (int*)(ws + off_state);
+  if (groups > 0)
+    hipLaunchKernelGGL(k_panel_clear, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 256)),
+                       dim3(256), 0, st, slots, words, states, 2 * panels,
+                       gather_ticks < 0 ? kAlone : kOpen);
   int rc = ELPA_OK;
   {
     std::lock_guard<std::mutex> lock(ebt::Handles::get().mu);
@@ -290,18 +784,36 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
     const auto C_ = Blas<E>::adj;
     for (int64_t p = 0; rc == ELPA_OK && p + b < n; p += b) {
       const int64_t r0 = p + b, m = n - r0, k = std::min(b, m);
-      const int G = (int)((m + kRows - 1) / kRows);
-      double* pa = pn0;
-      double* pb = pn1;
-      hipLaunchKernelGGL(k_pnorm<E>, dim3(G), dim3(kRows), 0, st, (const E*)A, lda, r0, p, m,
-                         (int64_t)0, pa);
-      for (int64_t i = 0; i < k; ++i) {
-        hipLaunchKernelGGL(k_reflect<E>, dim3(G), dim3(kRows), 0, st, (const E*)A, lda, r0, p, m,
-                           b, i, G, (const double*)pa, V, ldv, tau, pd);
-        hipLaunchKernelGGL(k_update<E>, dim3(G), dim3(kRows), 0, st, A, lda, r0, p, m, b, i, G,
-                           (const E*)V, ldv, (const E*)tau, (const double*)pa, (const E*)pd, pb,
-                           k);
-        std::swap(pa, pb);
+      const int64_t wide = (m + ROWS - 1) / ROWS;  // workgroups of a one-launch panel
+      if (b <= 64 && wide <= kMaxGroups) {
+        const Panel<E> P{A,     lda, r0,    p, m, (int)b, (int)k, V, ldv,
+                         tau,   slots, states + 2 * (p / b), (int)wide, (unsigned)(p + 1),
+                         gather_ticks};
+        const dim3 g((unsigned)wide), t(256);
+        if (b > 32)
+          hipLaunchKernelGGL((k_panel<E, 16>), g, t, 0, st, P);
+        else
+          hipLaunchKernelGGL((k_panel<E, 8>), g, t, 0, st, P);
+        if (wide > 1) {
+          if (b > 32)
+            hipLaunchKernelGGL((k_panel_alone<E, 16>), dim3(1), t, 0, st, P);
+          else
+            hipLaunchKernelGGL((k_panel_alone<E, 8>), dim3(1), t, 0, st, P);
+        }
+      } else {
+        const int G = (int)((m + kRows - 1) / kRows);
+        double* pa = pn0;
+        double* pb = pn1;
+        hipLaunchKernelGGL(k_pnorm<E>, dim3(G), dim3(kRows), 0, st, (const E*)A, lda, r0, p, m,
+                           (int64_t)0, pa);
+        for (int64_t i = 0; i < k; ++i) {
+          hipLaunchKernelGGL(k_reflect<E>, dim3(G), dim3(kRows), 0, st, (const E*)A, lda, r0, p,
+                             m, b, i, G, (const double*)pa, V, ldv, tau, pd);
+          hipLaunchKernelGGL(k_update<E>, dim3(G), dim3(kRows), 0, st, A, lda, r0, p, m, b, i, G,
+                             (const E*)V, ldv, (const E*)tau, (const double*)pa, (const E*)pd, pb,
+                             k);
+          std::swap(pa, pb);
+        }
       }
       hipLaunchKernelGGL(k_mirror<E>, dim3((unsigned)std::min<int64_t>((m + 255) / 256, 1024),
                                            (unsigned)b),
@@ -359,8 +871,12 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 }  // namespace ef2b
 
-extern "C" int elpa_full_to_band(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
-                                 int64_t ldv, void* tau, int32_t dtype, void* stream) {
+// elpa_full_to_band with the time a one-launch panel's workgroups have to come
+// together, in ticks of the 100 MHz clock (negative: every panel that needs
+// several workgroups is done by one; the tests reach that path this way).
+extern "C" int elpa_full_to_band_gather(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
+                                        int64_t ldv, void* tau, int32_t dtype, void* stream,
+                                        int64_t gather_ticks) {
   if (dtype != ELPA_R64 && dtype != ELPA_C64) return ELPA_ERR_DTYPE;
   if (n < 1 || nbw < 1 || nbw > ef2b::kMaxNb || lda < n || ldv < n) return ELPA_ERR_ARG;
   if (!A) return ELPA_ERR_ARG;
@@ -371,6 +887,14 @@ extern "C" int elpa_full_to_band(int64_t n, int64_t nbw, void* A, int64_t lda, v
     return ELPA_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (dtype == ELPA_R64)
-    return ef2b::run<double>(n, nbw, (double*)A, lda, (double*)V, ldv, (double*)tau, st);
-  return ef2b::run<ebt::zc>(n, nbw, (ebt::zc*)A, lda, (ebt::zc*)V, ldv, (ebt::zc*)tau, st);
+    return ef2b::run<double>(n, nbw, (double*)A, lda, (double*)V, ldv, (double*)tau, st,
+                             gather_ticks);
+  return ef2b::run<ebt::zc>(n, nbw, (ebt::zc*)A, lda, (ebt::zc*)V, ldv, (ebt::zc*)tau, st,
+                            gather_ticks);
+}
+
+extern "C" int elpa_full_to_band(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
+                                 int64_t ldv, void* tau, int32_t dtype, void* stream) {
+  return elpa_full_to_band_gather(n, nbw, A, lda, V, ldv, tau, dtype, stream,
+                                  ef2b::kGatherTicks);
 }

@@ -88,3 +88,47 @@ def test_eigenvectors_all_stages_but_the_tridiagonal_solve_on_gpu(torch_dev, cpl
     assert checks.orth_ratio(Z) < 50
     assert np.max(np.abs(lam - np.linalg.eigvalsh(A))) <= 50 * n * np.finfo(float).eps * \
         np.linalg.norm(A, 2)
+
+
+def f2b_with_gather(torch, a, nbw, ticks):
+    """elpa_full_to_band with the time the one-launch panel's workgroups have
+    to come together (negative: one workgroup does every panel)."""
+    import ctypes as C
+
+    import paper_1811_01277_amd as P
+    n = a.shape[0]
+    N = n - nbw
+    v = torch.zeros((N, n), dtype=a.dtype, device=a.device).t()
+    tau = torch.zeros(N, dtype=a.dtype, device=a.device)
+    fn = P.library().elpa_full_to_band_gather
+    fn.argtypes = [C.c_int64, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p,
+                   C.c_int32, C.c_void_p, C.c_int64]
+    fn.restype = C.c_int
+    rc = fn(n, nbw, a.data_ptr(), n, v.data_ptr(), n, tau.data_ptr(),
+            P.C64 if a.is_complex() else P.R64, None, ticks)
+    assert rc == 0, rc
+    torch.cuda.synchronize()
+    return v, tau
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("alone", [False, True])
+@pytest.mark.parametrize("n,b", [(256 + 64, 64), (256 + 65, 64), (33 + 129, 33), (700, 63),
+                                 (545, 32), (300, 3), (200, 65)])
+def test_f2b_panel_workgroups(torch_dev, n, b, alone, cplx):
+    """Panels of one row more and less than whole workgroups, bands that do
+    not fill the waves, and the first band too wide for the one-launch panel;
+    done together and by one workgroup, against the oracle's panels."""
+    torch, dev = torch_dev
+    A = W.herm_gaussian(n, 530 + n) if cplx else W.sym_gaussian(n, 530 + n)
+    B0, panels = stage1.full_to_band(A, b)
+    V0, t0 = panels_to_abi(panels, n, b, np.complex128 if cplx else np.float64)
+    print(f"f2b n={n} b={b} cplx={cplx} alone={alone}", flush=True)
+    a = to_dev(torch, dev, A)
+    v, tau = f2b_with_gather(torch, a, b, -1 if alone else 10 ** 7)
+    B = a.cpu().numpy()
+    scale = float(np.max(np.abs(A)))
+    assert np.max(np.abs(B - B0)) <= 1e-11 * scale * n ** 0.5
+    read = ~np.isnan(V0)  # the entries below the unit leads
+    assert np.max(np.abs(v.cpu().numpy()[:, :n - b] - V0)[read], initial=0.0) <= 1e-10
+    assert np.max(np.abs(tau.cpu().numpy() - t0)) <= 1e-10
