@@ -86,13 +86,15 @@ enum {
     ELPA_PATH_REF = 1,    /* one reflector at a time, any nbw */
     ELPA_PATH_STRIPE = 2, /* register-window stripe kernel, k sweeps fused, one lane
                              per column (all element types) */
-    ELPA_PATH_SPLIT = 3,  /* register-window stripe kernel, k sweeps fused, two lanes
-                             per column and reflectors pre-packed in consumption order,
-                             real ones applied in pairs (real fp64, fp32 and complex
-                             fp64, nbw 32 or 64; the default) */
-    ELPA_PATH_WY = 4      /* compact-WY aggregation of 16 reflectors at a time,
-                             applied by MFMA tiles to an LDS-resident window (real fp64
-                             and fp32, nbw 32 or 64) */
+    ELPA_PATH_SPLIT = 3,  /* register-window stripe kernel, k sweeps fused (nbw 32 or
+                             64; the default).  fp32 and complex fp64: two lanes per
+                             column and reflectors pre-packed in consumption order,
+                             fp32 ones applied in pairs.  fp64: 16 reflectors at a time
+                             in compact-WY form on MFMA tiles, the reflectors read from
+                             hh, only the triangular factors packed */
+    ELPA_PATH_WY = 4      /* compact-WY aggregation of 16 reflectors at a time on MFMA
+                             tiles, both operands packed by a pre-pass (real fp64 and
+                             fp32, complex fp64, nbw 32 or 64) */
 };
 
 /* order of the tiles of one launch over the workgroup ids (elpa_hh_plan.order).
@@ -117,9 +119,15 @@ enum {
  * column groups) are split into this many groups whose launch sequences run
  * on concurrent library-owned streams, forked from and joined back into the
  * caller's stream (1 = everything on the caller's stream; at most 8;
- * 0 = library choice, 2); batch: schedule of the two-lane kernel in batched
+ * 0 = library choice, 2); batch: schedule of ELPA_PATH_SPLIT in batched
  * calls, ELPA_BATCH_* (single-problem calls ignore it).
- * Results do not depend on order, streams or batch.
+ * Results do not depend on steps, order, streams or batch.
+ * A single fp64 problem of ELPA_PATH_SPLIT whose plan sets neither steps nor
+ * several streams runs in one launch: the sweep blocks of a stripe side by
+ * side, each a step or two behind the next, on the waves of one workgroup or
+ * on one-wave workgroups of the whole device, by a model of both.  The second
+ * form takes 32 bytes per stripe of 16 columns and sweep block beside the
+ * workspace that elpa_hh_workspace_bytes reports, from the same cache.
  * A plan that leaves the kernel open (path AUTO, k, steps and batch 0, or
  * NULL) runs the tuner's plan for the problem's size class when there is one
  * (elpa_hh_tune, elpa_hh_tuner_*), with the caller's order and streams where
@@ -192,20 +200,21 @@ typedef struct {
  * `stream`.  Problems may differ in n, nev and ldq.  Problems that share
  * (dtype, nbw) and run the two-lane stripe kernel (ELPA_PATH_SPLIT, the
  * default where one is compiled) run as one group, in one of two schedules:
- *   - ONE kernel launch: every workgroup carries one 32-column stripe of one
- *     problem through all of that problem's reflectors (sweep blocks
- *     descending, chase steps ascending), the problems ordered by decreasing
- *     work so that the longest stripes start first; no workgroup waits for
- *     another.  For batches of many problems, whose stripes fill the device.
+ *   - ONE kernel launch: every workgroup carries one stripe (32 columns, fp64:
+ *     16) of one problem through all of that problem's reflectors (sweep
+ *     blocks descending, chase steps ascending; fp64 with few stripes: blocks
+ *     side by side on several waves of the workgroup), the problems ordered by
+ *     decreasing work so that the longest stripes start first; no workgroup
+ *     waits for another.  For batches of many problems, whose stripes fill the device.
  *   - the diagonal launch sequence of every problem side by side (launch t
  *     runs launch t's tiles of every problem): for a few large problems,
  *     whose stripes alone would leave the device idle.
  * plan->batch picks one (ELPA_BATCH_*); by default the library models both
  * (resident wave slots, per-unit and per-launch work) and runs the faster,
  * the single launch unless it is modelled more than 10 % slower; an explicit
- * plan->steps selects the diagonal sequence.  A reflector-packing launch and
- * a layout-conversion launch run before and one conversion launch after,
- * each over all problems of the group.  Problems whose plan picks the
+ * plan->steps selects the diagonal sequence.  A reflector-packing launch runs
+ * before and, for fp32 and complex, a layout-conversion launch before and one
+ * after, each over all problems of the group.  Problems whose plan picks the
  * one-lane or compact-WY family run as that family's diagonal launch
  * sequence (all problems of the group side by side, one launch per diagonal);
  * problems without a compiled stripe kernel run through the reference kernel

@@ -22,7 +22,7 @@
  *
  * The call allocates its workspace (about 5 n^2 doubles) in stream order and
  * synchronises `stream` after uploading the merge tree (n > 1) and once per
- * level of the tree whose merges exceed 256 rows (the host sizes the
+ * level of the tree whose merges exceed 1024 rows (the host sizes the
  * products from the deflation counts).
  * Returns ELPA_OK or ELPA_ERR_ARG / _DTYPE / _ALIGN / _NOMEM / _DEVICE
  * (elpa_hh.h); arguments are checked before anything is enqueued.  n = 0 is

@@ -26,7 +26,7 @@
 //             delta_j)/(delta_i - delta_j) prod_{j<=i<K-1} (lambda_i -
 //             delta_j)/(delta_i+1 - delta_j), sign of w_j;
 //   vec:      U[:, i] = w^ / (delta - lambda_i), normalised;
-//   product:  Out = W[:, survivors] U; above 256 rows as two products on the
+//   product:  Out = W[:, survivors] U; above 1024 rows as two products on the
 //             halves, the survivors grouped by the rows they can be nonzero
 //             in (child 1 only, both after a rotation, child 2 only);
 //   final:    every value's rank among the merge's s values; L and Q's block

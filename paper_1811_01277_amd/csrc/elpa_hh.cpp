@@ -40,10 +40,8 @@ const ehh::StripeEntry* find_entry(int path, int32_t dtype, int64_t nb, int k) {
 // compiled entry in order of preference (0 if none).
 int default_k(int path, int32_t dtype, int64_t nb, bool batched) {
   static const int split_pref[] = {80, 64, 48, 32, 96, 24, 16};
-  // batched calls at nbw = 32: the widest k that holds its window without
-  // spilling (k = 96 takes the 256-problem batched workload from 42.2 to
-  // 39.4 ms of kernel time against k = 64; a single small problem has too
-  // few sweep blocks for it: n = 512 takes 0.50 instead of 0.43 ms)
+  // batched calls at nbw = 32: the widest k (each loaded row meets more
+  // reflectors); a single small problem has too few sweep blocks for it
   static const int split_pref32[] = {96, 64, 48, 32};
   static const int wy_pref[] = {160, 128, 96, 64, 48, 32};
   static const int wy_pref32[] = {96, 64, 32, 128};
@@ -82,7 +80,7 @@ int default_k(int path, int32_t dtype, int64_t nb, bool batched) {
 // k = 160): a larger k reuses every loaded row more but leaves fewer sweep
 // blocks to run side by side (fp32 at n = 20000: 82.2 TFLOP/s at k = 160,
 // 77.3 at 96; at n = 4000: 36.9 against 39.2);
-// 0 = the two-lane VALU kernel (fp64 below n = 3000, complex at nbw = 32,
+// 0 = path SPLIT (fp64 below n = 3000, complex at nbw = 32,
 // other nbw, batched calls).  fp64 with fewer than 1024 columns
 // also takes the two-lane kernel:
 // the compact-WY kernel's T-build, which does not shrink with nev, is then a
@@ -207,6 +205,7 @@ ehh::TileOpts tile_opts(const elpa_hh_plan* plan) {
   o.xcd = (plan && plan->order == ELPA_ORDER_XCD) ? 8 : 1;
   // two stripe groups by default: one group's launch tails overlap the other's
   o.streams = (plan && plan->streams > 0) ? plan->streams : 2;
+  o.grouped = plan && plan->streams > 1;
   o.batch = plan ? plan->batch : ELPA_BATCH_AUTO;
   o.order = plan ? plan->order : ELPA_ORDER_AUTO;
   return o;
@@ -273,7 +272,11 @@ class SinglePrepared : public ehh::PreparedGroup {
   hipError_t init() {
     bytes_ = se_->workspace(p_.n, p_.nev);
     if (bytes_ == 0) return hipSuccess;
+    const size_t counts = (bytes_ + 255) / 256 * 256;
+    opt_.sync_bytes = ehh::pipe_sync_bytes(p_.n, p_.nev, se_->k);
+    bytes_ = counts + opt_.sync_bytes;
     const hipError_t err = hipMalloc(&ws_, bytes_);
+    if (err == hipSuccess) opt_.sync = (int*)((char*)ws_ + counts);
     if (err != hipSuccess) {
       ws_ = nullptr;
       (void)hipGetLastError();
@@ -574,8 +577,16 @@ int elpa_hh_trafo_noalloc(int64_t n, int64_t nev, int64_t nbw, const void* hh, c
       prof.on = prof_on;
       return ELPA_ERR_ADMIT;
     }
-    if (err == hipSuccess)
-      err = se->with_ws(hh, tau, Q, ldq, n, nev, tile_opts(&split), st, device_cus(), ws);
+    if (err == hipSuccess) {
+      // counts of the pipelined schedule behind the workspace, where they fit
+      ehh::TileOpts opt = tile_opts(&split);
+      const size_t at = (se->workspace(n, nev) + 255) / 256 * 256;
+      if (at < cap) {
+        opt.sync = (int*)((char*)ws + at);
+        opt.sync_bytes = cap - at;
+      }
+      err = se->with_ws(hh, tau, Q, ldq, n, nev, opt, st, device_cus(), ws);
+    }
   }
   prof.on = prof_on;
   return status_of(err);

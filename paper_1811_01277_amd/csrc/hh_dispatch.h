@@ -19,10 +19,20 @@ struct TileOpts {
   int64_t steps;
   int xcd;
   int streams;
+  bool grouped;  // the plan asks for several stripe groups (streams > 1)
   int batch;  // ELPA_BATCH_* (batched calls of the two-lane kernel)
+  // device memory for the pipelined schedule's counts that goes with a
+  // caller-provided workspace (null: none, that schedule is not taken there)
+  int* sync;
+  size_t sync_bytes;
   int order;  // ELPA_ORDER_* as given (the one-launch batched schedule groups
               // each problem's stripes on one die unless ELPA_ORDER_LINEAR)
 };
+
+// Bytes of counts that a pipelined call of this size may use, k sweeps per block.
+inline size_t pipe_sync_bytes(int64_t n, int64_t nev, int k) {
+  return (size_t)(((nev + 15) / 16) * ((n - 1 + k - 1) / k) + 1) * 32;
+}
 
 using StripeLaunch = hipError_t (*)(const void* hh, const void* tau, void* Q, int64_t ldq,
                                     int64_t n, int64_t nev, TileOpts opt, hipStream_t st,

@@ -1,6 +1,8 @@
-// Split-window stripe kernel (real and complex fp64) of the tridiagonal->band eigenvector
-// back-transformation  Q <- H(0,0) H(0,1) ... H(n-2, J-1) Q  (Kus et al.,
-// Sec. 2 and Sec. 3.1).
+// Split-window stripe kernel (fp32 and complex fp64) of the
+// tridiagonal->band eigenvector back-transformation
+//   Q <- H(0,0) H(0,1) ... H(n-2, J-1) Q  (Kus et al., Sec. 2 and Sec. 3.1),
+// and the launchers of its path, which for real fp64 run the compact-WY
+// kernels of hh_wyd_impl.h.
 //
 // Same block/step structure and diagonal launch schedule as the one-lane
 // stripe kernel (blocks of K sweeps slide a window of W = NB+K-1 rows down a
@@ -41,6 +43,7 @@
 #include "hh_dpp.h"
 #include "hh_layout.h"
 #include "hh_sched.h"
+#include "hh_wyd_impl.h"
 
 namespace ehh {
 
@@ -416,6 +419,107 @@ __global__ __launch_bounds__(64, OCC) void k_split_seq(const ProblemDesc* __rest
 }
 
 // ---------------------------------------------------------------------------
+// Kernels of the family per element type: fp32 and complex run the two-lane
+// kernels above, fp64 the compact-WY ones of hh_wyd_impl.h, with the same
+// packed area, stripes and schedules.
+// ---------------------------------------------------------------------------
+template <typename E_, int NB_, int K_, int OCC, int PD>
+struct TwoLane {
+  using E = E_;
+  static constexpr int NB = NB_, K = K_;
+  static constexpr bool kPipe = false;    // has the one-launch pipelined schedule
+  static constexpr bool kStripes = true;  // works on a stripe copy of Q
+  static int64_t slots(int cu) { return wave_slots(k_split<E, NB, K, OCC, PD>, cu); }
+  static int64_t slots_b(int cu) { return wave_slots(k_split_b<E, NB, K, OCC, PD>, cu); }
+  static void pack(int64_t groups, const void* hh, const void* tau, int64_t n, int64_t Jmax,
+                   E* P, int64_t* Bt, hipStream_t st) {
+    hipLaunchKernelGGL((k_pack_split<E, NB, K>), dim3((unsigned)groups), dim3(256), 0, st,
+                       (const E*)hh, (const E*)tau, n, Jmax, P, Bt);
+  }
+  static void pack_b(int64_t groups, const ProblemDesc* d, int count, hipStream_t st) {
+    hipLaunchKernelGGL((k_pack_split_b<E, NB, K>), dim3((unsigned)groups), dim3(256), 0, st, d,
+                       count);
+  }
+  static void tiles(int64_t tiles, const E* P, const int64_t* Bt, const void*, E* Qs,
+                    int64_t rows_pad, E*, int64_t, int64_t n, int64_t, int c0, int G, int M,
+                    int t, int m0, int S, int xcd, hipStream_t st) {
+    hipLaunchKernelGGL((k_split<E, NB, K, OCC, PD>), dim3((unsigned)tiles), dim3(64), 0, st, P,
+                       Bt, Qs, rows_pad, n, c0, G, M, t, m0, S, xcd);
+  }
+  static void tiles_b(int64_t tiles, const ProblemDesc* d, const DiagEntry* e, int ne, int t,
+                      int xcd, hipStream_t st) {
+    hipLaunchKernelGGL((k_split_b<E, NB, K, OCC, PD>), dim3((unsigned)tiles), dim3(64), 0, st, d,
+                       e, ne, t, xcd);
+  }
+  static void units_b(int64_t units, int64_t, int, const ProblemDesc* d, int count,
+                      const int* umap, hipStream_t st) {
+    hipLaunchKernelGGL((k_split_seq<E, NB, K, OCC, PD>), dim3((unsigned)units), dim3(64), 0, st,
+                       d, count, umap);
+  }
+};
+
+template <int NB_, int K_>
+struct WyDirect {
+  using E = double;
+  static constexpr int NB = NB_, K = K_;
+  static constexpr bool kPipe = true;
+  static constexpr bool kStripes = false;
+  // Waves of a batched local workgroup: one where the units alone fill the
+  // device several times over (no hand-overs), more for fewer units.
+  static int waves_b(int64_t units, int cus) {
+    const int64_t slots = 8 * (int64_t)cus;
+    return units >= 3 * slots ? 1 : units >= slots ? 2 : units >= slots / 2 ? 4 : 8;
+  }
+  // LDS of a local workgroup's wave
+  static constexpr unsigned lds() { return WydGeom<NB, K>::LDS * sizeof(double); }
+  // wave slots in stored stripes (two 16-column waves each)
+  static int64_t slots(int cu) { return wave_slots(k_wyd<NB, K>, cu) / 2; }
+  static int64_t slots_b(int cu) { return wave_slots(k_wyd_b<NB, K>, cu) / 2; }
+  static void pack(int64_t groups, const void* hh, const void* tau, int64_t n, int64_t Jmax,
+                   E* P, int64_t* Bt, hipStream_t st) {
+    hipLaunchKernelGGL((k_wyd_prep<NB, K>), dim3((unsigned)(groups * (K / 16))), dim3(256), 0, st,
+                       (const E*)hh, (const E*)tau, n, Jmax, P, Bt);
+  }
+  static void pack_b(int64_t groups, const ProblemDesc* d, int count, hipStream_t st) {
+    hipLaunchKernelGGL((k_wyd_prep_b<NB, K>), dim3((unsigned)(groups * (K / 16))), dim3(256), 0,
+                       st, d, count);
+  }
+  static void tiles(int64_t tiles, const E* P, const int64_t* Bt, const void* hh, E*, int64_t,
+                    E* Q, int64_t ldq, int64_t n, int64_t nev, int c0, int G, int M, int t,
+                    int m0, int S, int xcd, hipStream_t st) {
+    hipLaunchKernelGGL((k_wyd<NB, K>), dim3((unsigned)(2 * tiles)), dim3(64), 0, st, P, Bt,
+                       (const E*)hh, Q, ldq, n, nev, c0, G, M, t, m0, S, xcd);
+  }
+  static void tiles_b(int64_t tiles, const ProblemDesc* d, const DiagEntry* e, int ne, int t,
+                      int xcd, hipStream_t st) {
+    hipLaunchKernelGGL((k_wyd_b<NB, K>), dim3((unsigned)(2 * tiles)), dim3(64), 0, st, d, e, ne,
+                       t, xcd);
+  }
+  static void units_b(int64_t ids, int64_t stripes, int cus, const ProblemDesc* d, int count,
+                      const int* umap, hipStream_t st) {
+    const int w = waves_b(2 * stripes, cus);
+    if (w == 1)
+      hipLaunchKernelGGL((k_wyd_local_b<NB, K, true>), dim3((unsigned)(2 * ids)), dim3(64), lds(),
+                         st, d, count, umap);
+    else
+      hipLaunchKernelGGL((k_wyd_local_b<NB, K, false>), dim3((unsigned)(2 * ids)), dim3(64 * w),
+                         w * lds(), st, d, count, umap);
+  }
+  static void local(int64_t H, int waves, const E* P, const int64_t* Bt, const void* hh, E* Q,
+                    int64_t ldq, int64_t n, int64_t nev, int64_t M, hipStream_t st) {
+    hipLaunchKernelGGL((k_wyd_local<NB, K>), dim3((unsigned)H), dim3(64 * waves),
+                       (unsigned)waves * lds(), st, P, Bt,
+                       (const E*)hh, Q, ldq, n, nev, M);
+  }
+  static void device(int64_t wgs, const E* P, const int64_t* Bt, const void* hh, E* Q,
+                     int64_t ldq, int64_t n, int64_t nev, int64_t H, int64_t M, int* words,
+                     hipStream_t st) {
+    hipLaunchKernelGGL((k_wyd_dev<NB, K>), dim3((unsigned)wgs), dim3(64), 0, st, P, Bt,
+                       (const E*)hh, Q, ldq, n, nev, H, M, words);
+  }
+};
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 // Packed-reflector area of one problem: the step records of every block's
@@ -444,11 +548,13 @@ size_t split_workspace(int64_t n, int64_t nev) {
 // Single problem.  ws: a device workspace of at least split_workspace(n, nev)
 // bytes that no other work uses while this call's work runs, or null: then
 // the workspace is allocated and freed in stream order on st.
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int64_t n,
                      int64_t nev, TileOpts opt, hipStream_t st, int num_cu, void* ws_in) {
+  using E = typename F::E;
+  constexpr int NB = F::NB, K = F::K;
   using Gm = SplitGeom<NB, K>;
-  static const int64_t slots = wave_slots(k_split<E, NB, K, OCC, PD>, num_cu);
+  static const int64_t slots = F::slots(num_cu);
   const int64_t S = opt.steps > 0 ? opt.steps : choose_steps(n, nev, NB, K, slots, Gm::SW);
   const DiagPlan pl(n, nev, NB, K, S, Gm::SW);
   const int64_t Jmax = (n - 1 + NB - 1) / NB;
@@ -471,12 +577,54 @@ hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int6
   int64_t* Bt = (int64_t*)(ws + rbytes);
   E* Qs = (E*)(ws + pbytes);
   const unsigned gt = (unsigned)((nev + 63) / 64);
-  hipLaunchKernelGGL((k_pack_split<E, NB, K>), dim3((unsigned)(pl.M * Jmax)), dim3(256), 0, st,
-                     (const E*)hh, (const E*)tau, n, Jmax, Pk, Bt);
-  hipLaunchKernelGGL((k_to_rows_sw<E, Gm::SW>), dim3((unsigned)(pl.rows_pad / 64), gt), dim3(256), 0,
-                     st, (const E*)Q, ldq, n, nev, Qs, pl.rows_pad, pl.G);
-  const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(opt.streams, pl.G));
+  F::pack(pl.M * Jmax, hh, tau, n, Jmax, Pk, Bt, st);
+  if constexpr (F::kStripes)
+    hipLaunchKernelGGL((k_to_rows_sw<E, Gm::SW>), dim3((unsigned)(pl.rows_pad / 64), gt),
+                       dim3(256), 0, st, (const E*)Q, ldq, n, nev, Qs, pl.rows_pad, pl.G);
   hipError_t err = hipSuccess;
+  if constexpr (F::kPipe) {
+    if (opt.steps <= 0 && !opt.grouped) {
+      // one launch: the schedule is left open
+      const int64_t H = (nev + 15) / 16;
+      const double step_us = (K / 16) * (8.0 * (NB / 16 + 1) + 4.0) * 64.0 / 2400.0;
+      const int64_t nw = (int64_t)pipe_words(H * pl.M);
+      const bool room = ws_in == nullptr || opt.sync_bytes >= (size_t)nw * sizeof(int);
+      const PipeChoice pc =
+          choose_pipe(H, pl.M, Jmax, (double)block_base(n, NB, K, pl.M), num_cu, step_us,
+                      room && H * pl.M < INT32_MAX / kPipeStride,
+                      diag_steps(pl, 2.0 * (double)slots, step_us));
+      if (pc.form != PipeChoice::kDiagonal) {
+        int* words = nullptr;
+        const bool device = pc.form == PipeChoice::kDevice;
+        if (device) {
+          words = opt.sync;
+          if (!ws_in) err = ws_alloc((void**)&words, (size_t)nw * sizeof(int), st);
+          if (err != hipSuccess) return release(err);
+          hipLaunchKernelGGL(k_pipe_clear, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st,
+                             words, nw);
+          hipLaunchKernelGGL((k_to_rows_sw<E, Gm::SW>), dim3((unsigned)(pl.rows_pad / 64), gt),
+                             dim3(256), 0, st, (const E*)Q, ldq, n, nev, Qs, pl.rows_pad, pl.G);
+        }
+        {
+          ProfScope prof(st, K, 0);
+          prof.before(st);
+          if (device)
+            F::device(std::min<int64_t>(H * pl.M, 8 * (int64_t)num_cu), Pk, Bt, hh, Qs, pl.rows_pad,
+                      n, nev, H, pl.M, words, st);
+          else
+            F::local(H, pc.waves, Pk, Bt, hh, (E*)Q, ldq, n, nev, pl.M, st);
+          prof.after(st);
+        }
+        if (device) {
+          hipLaunchKernelGGL((k_from_rows_sw<E, Gm::SW>), dim3((unsigned)((n + 63) / 64), gt),
+                             dim3(256), 0, st, (const E*)Qs, pl.rows_pad, (E*)Q, ldq, n, nev, pl.G);
+          if (!ws_in) err = ws_free(words, st);
+        }
+        return release(err != hipSuccess ? err : hipGetLastError());
+      }
+    }
+  }
+  const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(opt.streams, pl.G));
   ProfScope prof(st, K, S, ns);
   {
     // stripe groups: one launch sequence each, on concurrent streams when
@@ -491,9 +639,8 @@ hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int6
       for (int i = 0; i < ns; ++i) {
         const int64_t c_lo = pl.G * i / ns, gs = pl.G * (i + 1) / ns - c_lo;
         prof.before(fork.stream(i));
-        hipLaunchKernelGGL((k_split<E, NB, K, OCC, PD>), dim3((unsigned)(cnt * gs)), dim3(64), 0,
-                           fork.stream(i), (const E*)Pk, (const int64_t*)Bt, Qs, pl.rows_pad, n,
-                           (int)c_lo, (int)gs, (int)pl.M, (int)t, (int)m0, (int)S, opt.xcd);
+        F::tiles(cnt * gs, Pk, Bt, hh, Qs, pl.rows_pad, (E*)Q, ldq, n, nev, (int)c_lo, (int)gs,
+                 (int)pl.M, (int)t, (int)m0, (int)S, opt.xcd, fork.stream(i));
         prof.after(fork.stream(i));
       }
     }
@@ -501,21 +648,22 @@ hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int6
   }
   prof.end();
   if (err != hipSuccess) return release(err);
-  hipLaunchKernelGGL((k_from_rows_sw<E, Gm::SW>), dim3((unsigned)((n + 63) / 64), gt), dim3(256), 0,
-                     st, (const E*)Qs, pl.rows_pad, (E*)Q, ldq, n, nev, pl.G);
+  if constexpr (F::kStripes)
+    hipLaunchKernelGGL((k_from_rows_sw<E, Gm::SW>), dim3((unsigned)((n + 63) / 64), gt),
+                       dim3(256), 0, st, (const E*)Qs, pl.rows_pad, (E*)Q, ldq, n, nev, pl.G);
   return release(hipGetLastError());
 }
 
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 hipError_t launch_split(const void* hh, const void* tau, void* Q, int64_t ldq, int64_t n,
                         int64_t nev, TileOpts opt, hipStream_t st, int num_cu) {
-  return run_split<E, NB, K, OCC, PD>(hh, tau, Q, ldq, n, nev, opt, st, num_cu, nullptr);
+  return run_split<F>(hh, tau, Q, ldq, n, nev, opt, st, num_cu, nullptr);
 }
 
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 hipError_t launch_split_ws(const void* hh, const void* tau, void* Q, int64_t ldq, int64_t n,
                            int64_t nev, TileOpts opt, hipStream_t st, int num_cu, void* ws) {
-  return run_split<E, NB, K, OCC, PD>(hh, tau, Q, ldq, n, nev, opt, st, num_cu, ws);
+  return run_split<F>(hh, tau, Q, ldq, n, nev, opt, st, num_cu, ws);
 }
 
 // Modelled times of the two batched schedules, in chase steps of one stripe
@@ -571,7 +719,7 @@ struct SplitBatchPlan {
   size_t dbytes = 0, ebytes = 0, ubytes = 0, total = 0, tiles = 0, otiles = 0, ptiles = 0,
          units = 0;
   int64_t T = 0;
-  int K = 0;
+  int K = 0, cus = 0;
   bool one_launch = false;
 };
 
@@ -586,14 +734,17 @@ struct SplitBatchPlan {
 //    the sweep-block parallelism of the diagonal schedule.
 // opt.batch forces one of them; an explicit tile height (opt.steps > 0)
 // selects the diagonal schedule.  Returns false if there is nothing to do.
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 hipError_t plan_split_batch(const elpa_hh_problem* probs, const int64_t* idx, int64_t cnt,
                             TileOpts opt, int num_cu, SplitBatchPlan* out) {
+  using E = typename F::E;
+  constexpr int NB = F::NB, K = F::K;
   using Gm = SplitGeom<NB, K>;
-  static const int64_t slots = wave_slots(k_split_b<E, NB, K, OCC, PD>, num_cu);
+  static const int64_t slots = F::slots_b(num_cu);
   SplitBatchPlan& B = *out;
   B = SplitBatchPlan{};
   B.K = K;
+  B.cus = num_cu;
   std::vector<int64_t> live;
   int64_t total_cols = 0;
   for (int64_t i = 0; i < cnt; ++i) {
@@ -719,47 +870,48 @@ inline void bind_split_batch(SplitBatchPlan& B, char* ws) {
 
 // The launches of a bound plan whose descriptor and entry tables are in the
 // workspace: packing, layout conversion, the schedule, conversion back.
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 void launch_split_batch(const SplitBatchPlan& B, const char* ws, int xcd, hipStream_t st) {
+  using E = typename F::E;
+  constexpr int NB = F::NB, K = F::K;
   using Gm = SplitGeom<NB, K>;
   const ProblemDesc* dd = (const ProblemDesc*)ws;
   const DiagEntry* de = (const DiagEntry*)(ws + B.dbytes);
   const int count = (int)B.d.size();
-  hipLaunchKernelGGL((k_pack_split_b<E, NB, K>), dim3((unsigned)B.ptiles), dim3(256), 0, st, dd,
-                     count);
-  hipLaunchKernelGGL((k_to_rows_sw_b<E, Gm::SW>), dim3((unsigned)B.tiles), dim3(256), 0, st, dd,
-                     count);
+  F::pack_b((int64_t)B.ptiles, dd, count, st);
+  if constexpr (F::kStripes)
+    hipLaunchKernelGGL((k_to_rows_sw_b<E, Gm::SW>), dim3((unsigned)B.tiles), dim3(256), 0, st,
+                       dd, count);
   {
     ProfScope prof(st, K, 0);
     if (B.one_launch) {
       prof.before(st);
       const int* um = B.umap.empty() ? nullptr : (const int*)(ws + B.dbytes + B.ebytes);
       const size_t grid = B.umap.empty() ? B.units : B.umap.size();
-      hipLaunchKernelGGL((k_split_seq<E, NB, K, OCC, PD>), dim3((unsigned)grid), dim3(64), 0, st,
-                         dd, count, um);
+      F::units_b((int64_t)grid, (int64_t)B.units, B.cus, dd, count, um, st);
       prof.after(st);
     } else {
       for (int64_t t = 0; t < B.T; ++t) {
         const int64_t ne = B.eoff[(size_t)t + 1] - B.eoff[(size_t)t];
         if (ne == 0) continue;
         prof.before(st);
-        hipLaunchKernelGGL((k_split_b<E, NB, K, OCC, PD>), dim3((unsigned)B.etiles[(size_t)t]),
-                           dim3(64), 0, st, dd, de + B.eoff[(size_t)t], (int)ne, (int)t, xcd);
+        F::tiles_b(B.etiles[(size_t)t], dd, de + B.eoff[(size_t)t], (int)ne, (int)t, xcd, st);
         prof.after(st);
       }
     }
   }
-  hipLaunchKernelGGL((k_from_rows_sw_b<E, Gm::SW>), dim3((unsigned)B.otiles), dim3(256), 0, st,
-                     dd, count);
+  if constexpr (F::kStripes)
+    hipLaunchKernelGGL((k_from_rows_sw_b<E, Gm::SW>), dim3((unsigned)B.otiles), dim3(256), 0, st,
+                       dd, count);
 }
 
 // Batched call: plan, stream-ordered workspace, tables staged through pinned
 // host memory, launches, workspace freed in stream order.
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 hipError_t launch_split_batched(const elpa_hh_problem* probs, const int64_t* idx, int64_t cnt,
                                 TileOpts opt, hipStream_t st, int num_cu) {
   SplitBatchPlan B;
-  hipError_t err = plan_split_batch<E, NB, K, OCC, PD>(probs, idx, cnt, opt, num_cu, &B);
+  hipError_t err = plan_split_batch<F>(probs, idx, cnt, opt, num_cu, &B);
   if (err != hipSuccess || B.d.empty()) return err;
   char* ws = nullptr;
   err = ws_alloc((void**)&ws, B.total, st);
@@ -777,7 +929,7 @@ hipError_t launch_split_batched(const elpa_hh_problem* probs, const int64_t* idx
     (void)ws_free(ws, st);
     return err;
   }
-  launch_split_batch<E, NB, K, OCC, PD>(B, ws, opt.xcd, st);
+  launch_split_batch<F>(B, ws, opt.xcd, st);
   err = hipGetLastError();
   const hipError_t e2 = ws_free(ws, st);
   return err != hipSuccess ? err : e2;
@@ -787,7 +939,7 @@ hipError_t launch_split_batched(const elpa_hh_problem* probs, const int64_t* idx
 // device for the handle's lifetime; run() only launches.  A single problem
 // runs the single-call path (stripe groups on library streams) on the owned
 // workspace; several run the batched schedule.
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 class SplitPrepared : public PreparedGroup {
  public:
   ~SplitPrepared() override {
@@ -806,10 +958,15 @@ class SplitPrepared : public PreparedGroup {
     if (live == 0) return hipSuccess;
     if (live == 1) {
       one_ = true;
-      bytes_ = split_workspace<E, NB, K>(single_.n, single_.nev);
-      return alloc(bytes_);
+      const size_t at =
+          align256(split_workspace<typename F::E, F::NB, F::K>(single_.n, single_.nev));
+      opt_.sync_bytes = F::kPipe ? pipe_sync_bytes(single_.n, single_.nev, F::K) : 0;
+      bytes_ = at + opt_.sync_bytes;
+      const hipError_t err = alloc(bytes_);
+      if (err == hipSuccess) opt_.sync = (int*)((char*)ws_ + at);
+      return err;
     }
-    hipError_t err = plan_split_batch<E, NB, K, OCC, PD>(probs, idx, cnt, opt, num_cu, &B_);
+    hipError_t err = plan_split_batch<F>(probs, idx, cnt, opt, num_cu, &B_);
     if (err != hipSuccess) return err;
     bytes_ = B_.total;
     err = alloc(bytes_);
@@ -827,9 +984,9 @@ class SplitPrepared : public PreparedGroup {
   hipError_t run(hipStream_t st) override {
     if (!ws_) return hipSuccess;
     if (one_)
-      return run_split<E, NB, K, OCC, PD>(single_.hh, single_.tau, single_.Q, single_.ldq,
+      return run_split<F>(single_.hh, single_.tau, single_.Q, single_.ldq,
                                           single_.n, single_.nev, opt_, st, num_cu_, ws_);
-    launch_split_batch<E, NB, K, OCC, PD>(B_, (const char*)ws_, opt_.xcd, st);
+    launch_split_batch<F>(B_, (const char*)ws_, opt_.xcd, st);
     return hipGetLastError();
   }
   size_t bytes() const override { return bytes_; }
@@ -857,10 +1014,10 @@ class SplitPrepared : public PreparedGroup {
   size_t bytes_ = 0;
 };
 
-template <typename E, int NB, int K, int OCC, int PD>
+template <typename F>
 hipError_t prepare_split(const elpa_hh_problem* probs, const int64_t* idx, int64_t cnt,
                          TileOpts opt, int num_cu, PreparedGroup** out) {
-  auto* g = new SplitPrepared<E, NB, K, OCC, PD>();
+  auto* g = new SplitPrepared<F>();
   const hipError_t err = g->init(probs, idx, cnt, opt, num_cu);
   if (err != hipSuccess) {
     delete g;

@@ -1,0 +1,96 @@
+"""The one-launch pipelined schedules of fp64 calls (path SPLIT): the local
+form (a workgroup per stripe), the device form (one-wave workgroups over the
+whole device) and the batched form with one, two, four and eight waves per
+workgroup, against the diagonal launch schedule (bitwise: the same per-column
+arithmetic) and the oracle."""
+import numpy as np
+import pytest
+
+import workload as W
+from oracle import bt, checks
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1811_01277_amd as P
+    P.library()
+    return torch, torch.device("cuda:0")
+
+
+def drawn(torch, dev, n, nbw, nev, seed):
+    g = torch.Generator(device=dev)
+    g.manual_seed(seed)
+    hh, tau = W.device_reflectors(torch, n, nbw, dev, g)
+    return W.device_block(torch, n, nev, dev, g), hh, tau
+
+
+# few stripes and long chains take the device form, the others the local one;
+# n around multiples of the block (k = 80 / 64) and of the band, ragged columns
+@pytest.mark.parametrize("n,nbw,nev", [
+    (2, 64, 1), (65, 64, 3), (81, 64, 16), (82, 64, 17), (145, 64, 33), (641, 64, 700),
+    (1000, 64, 97), (33, 32, 5), (64, 32, 64), (65, 32, 31), (66, 32, 1), (449, 32, 449),
+    (3000, 64, 40), (2500, 32, 17), (2999, 64, 1)])
+def test_pipelined_call_equals_launch_schedule(torch_dev, n, nbw, nev):
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    q, hh, tau = drawn(torch, dev, n, nbw, nev, 7000 + n)
+    ref = q.clone()
+    print(f"pipelined n={n} nbw={nbw} nev={nev}", flush=True)
+    P.hh_trafo(ref, hh, tau, nbw, path=P.PATH_SPLIT, steps=3)
+    P.profile_enable(True)
+    try:
+        P.hh_trafo(q, hh, tau, nbw, path=P.PATH_SPLIT)
+        pr = P.profile_last()
+    finally:
+        P.profile_enable(False)
+    torch.cuda.synchronize()
+    assert pr["launches"] == 1, pr
+    assert torch.equal(q, ref)
+    if n <= 700:
+        z0 = drawn(torch, dev, n, nbw, nev, 7000 + n)[0].cpu().numpy()
+        want = bt.bt_tridiag_to_band(hh.cpu().numpy(), tau.cpu().numpy(), np.asfortranarray(z0),
+                                     n, nbw)
+        assert checks.max_rel_err(q.cpu().numpy(), want) <= TOL
+
+
+def test_padded_ldq_and_prepared_device_form(torch_dev):
+    """A padded leading dimension (padding untouched), and the device form on a
+    prepared call's own counts, run twice."""
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    n, nbw, nev, ldq = 2600, 64, 35, 2613
+    z, hh, tau = drawn(torch, dev, n, nbw, nev, 7100)
+    buf = torch.full((nev, ldq), 7.0, dtype=torch.float64, device=dev)
+    buf[:, :n] = z.t()
+    q = buf.t()[:n]
+    ref = z.clone()
+    for _ in range(2):
+        P.hh_trafo(ref, hh, tau, nbw, path=P.PATH_SPLIT, steps=2)
+    b = P.Batch([(q, hh, tau, nbw)])
+    b.run()
+    b.run()
+    torch.cuda.synchronize()
+    assert torch.equal(q, ref) and bool((buf[:, n:] == 7.0).all())
+    b.close()
+
+
+@pytest.mark.parametrize("count,n", [(3, 700), (20, 1000), (40, 900), (130, 780)])
+def test_batched_waves_per_workgroup(torch_dev, count, n):
+    """Batches whose stripes call for eight, four, two and one waves per
+    workgroup."""
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    one = drawn(torch, dev, n, 32, n, 7200)
+    probs = [(one[0].clone(), one[1], one[2], 32) for _ in range(count)]
+    print(f"batched {count} x n={n}", flush=True)
+    P.hh_trafo(one[0], one[1], one[2], 32, path=P.PATH_SPLIT, k=96, steps=4)
+    P.hh_trafo_batched(probs, batch=P.BATCH_ONE_LAUNCH)
+    torch.cuda.synchronize()
+    for p in probs:
+        assert torch.equal(p[0], one[0])
