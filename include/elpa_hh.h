@@ -122,11 +122,12 @@ enum {
  * 0 = library choice, 2); batch: schedule of ELPA_PATH_SPLIT in batched
  * calls, ELPA_BATCH_* (single-problem calls ignore it).
  * Results do not depend on steps, order, streams or batch.
- * A single fp64 problem of ELPA_PATH_SPLIT whose plan sets neither steps nor
- * several streams runs in one launch: the sweep blocks of a stripe side by
- * side, each a step or two behind the next, on the waves of one workgroup or
- * on one-wave workgroups of the whole device, by a model of both.  The second
- * form takes 32 bytes per stripe of 16 columns and sweep block beside the
+ * A single problem of ELPA_PATH_WY or, in fp64, of ELPA_PATH_SPLIT whose plan
+ * sets neither steps nor several streams runs in one launch: the sweep blocks
+ * of a stripe side by side, each a step or two behind the next, on workgroups
+ * of the whole device or (ELPA_PATH_SPLIT, by a model of both) on the waves of
+ * one workgroup.  The first form takes 32 bytes per stripe of 16 (ELPA_PATH_WY:
+ * 64) columns and sweep block beside the
  * workspace that elpa_hh_workspace_bytes reports, from the same cache.
  * A plan that leaves the kernel open (path AUTO, k, steps and batch 0, or
  * NULL) runs the tuner's plan for the problem's size class when there is one

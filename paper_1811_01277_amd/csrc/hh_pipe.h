@@ -86,10 +86,13 @@ struct DevSync {
   __device__ __forceinline__ void wait(int64_t j) const {
     while (!ready(j)) __builtin_amdgcn_s_sleep(1);
   }
+  __device__ __forceinline__ void raise(int64_t j) const {
+    __hip_atomic_store(mine, (int)j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   __device__ __forceinline__ void done(int64_t j) const {
     // the rows' stores are acknowledged before the count is raised
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __hip_atomic_store(mine, (int)j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    raise(j);
   }
 };
 

@@ -43,6 +43,7 @@
 #include "hh_common.h"
 #include "hh_dispatch.h"
 #include "hh_layout.h"
+#include "hh_pipe.h"
 #include "hh_sched.h"
 
 namespace ehh {
@@ -348,18 +349,57 @@ __device__ __forceinline__ z64 wy_join<z64>(const double (&o)[2]) {
   return z64{o[0], o[1]};
 }
 
+// Device-scope accesses of stripe elements (they pass the caches that other
+// compute units do not see), at a byte offset from a wave-uniform base.
+typedef unsigned wy_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned wy_u4 __attribute__((ext_vector_type(4)));
+struct WyBuffer {
+  static constexpr int kScope = 16;  // sc1
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit WyBuffer(const void* p)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7fffffff, 0x00020000)) {}
+  __device__ __forceinline__ void get(float& x, int lane_off, int wave_off) const {
+    x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, lane_off, wave_off, kScope));
+  }
+  __device__ __forceinline__ void get(double& x, int lane_off, int wave_off) const {
+    const wy_u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, wave_off, kScope);
+    x = __hiloint2double((int)w[1], (int)w[0]);
+  }
+  __device__ __forceinline__ void get(z64& x, int lane_off, int wave_off) const {
+    const wy_u4 w = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, wave_off, kScope);
+    x = z64{__hiloint2double((int)w[1], (int)w[0]), __hiloint2double((int)w[3], (int)w[2])};
+  }
+  __device__ __forceinline__ void put(float x, int lane_off, int wave_off) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, lane_off, wave_off, kScope);
+  }
+  __device__ __forceinline__ void put(double x, int lane_off, int wave_off) const {
+    const wy_u2 w{(unsigned)__double2loint(x), (unsigned)__double2hiint(x)};
+    __builtin_amdgcn_raw_buffer_store_b64(w, r, lane_off, wave_off, kScope);
+  }
+  __device__ __forceinline__ void put(z64 x, int lane_off, int wave_off) const {
+    const wy_u4 w{(unsigned)__double2loint(x.re), (unsigned)__double2hiint(x.re),
+                  (unsigned)__double2loint(x.im), (unsigned)__double2hiint(x.im)};
+    __builtin_amdgcn_raw_buffer_store_b128(w, r, lane_off, wave_off, kScope);
+  }
+};
+
 // window tile tr <-> stripe rows row0 + 16 tr + row(q, r), columns 16 t + l%16
-template <typename E, int NB, int K, int T, int SW>
+template <typename E, int NB, int K, int T, int SW, bool DEV = false>
 __device__ __forceinline__ void wy_load_tile(WyWin<E, NB, K, T>& w, int tr,
                                              const E* __restrict__ rp) {
   using R = typename WyElem<E>::R;
   constexpr int PL = WyElem<E>::PL;
-  const int l = threadIdx.x, q = l >> 4, cl = l & 15;
+  const int l = threadIdx.x & 63, q = l >> 4, cl = l & 15;
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const E v = rp[(16 * tr + wy_row<WyElem<E>::kInterleaved>(q, r)) * SW + 16 * t + cl];
+      E v;
+      if constexpr (DEV)
+        WyBuffer(rp).get(v, (wy_row<WyElem<E>::kInterleaved>(q, r) * SW + cl) * (int)sizeof(E),
+                         (16 * tr * SW + 16 * t) * (int)sizeof(E));
+      else
+        v = rp[(16 * tr + wy_row<WyElem<E>::kInterleaved>(q, r)) * SW + 16 * t + cl];
       R o[PL];
       wy_split<E>(v, o);
 #pragma unroll
@@ -368,12 +408,12 @@ __device__ __forceinline__ void wy_load_tile(WyWin<E, NB, K, T>& w, int tr,
 }
 
 // skip_last: leave the tile's last row (row 15: quad 3, register 3) unwritten
-template <typename E, int NB, int K, int T, int SW>
+template <typename E, int NB, int K, int T, int SW, bool DEV = false>
 __device__ __forceinline__ void wy_store_tile(const WyWin<E, NB, K, T>& w, int tr,
                                               E* __restrict__ rp, bool skip_last) {
   using R = typename WyElem<E>::R;
   constexpr int PL = WyElem<E>::PL;
-  const int l = threadIdx.x, q = l >> 4, cl = l & 15;
+  const int l = threadIdx.x & 63, q = l >> 4, cl = l & 15;
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -382,34 +422,23 @@ __device__ __forceinline__ void wy_store_tile(const WyWin<E, NB, K, T>& w, int t
       R o[PL];
 #pragma unroll
       for (int p = 0; p < PL; ++p) o[p] = w.x[p][tr][t][r];
-      rp[(16 * tr + wy_row<WyElem<E>::kInterleaved>(q, r)) * SW + 16 * t + cl] = wy_join<E>(o);
+      if constexpr (DEV)
+        WyBuffer(rp).put(wy_join<E>(o),
+                         (wy_row<WyElem<E>::kInterleaved>(q, r) * SW + cl) * (int)sizeof(E),
+                         (16 * tr * SW + 16 * t) * (int)sizeof(E));
+      else
+        rp[(16 * tr + wy_row<WyElem<E>::kInterleaved>(q, r)) * SW + 16 * t + cl] = wy_join<E>(o);
     }
 }
 
-// Sub-group u applied to the window: W' = (-U)^H X over tiles u .. u+RT-1,
-// then X += V W' on the same tiles.  A: this sub-group's (-U)^H fragments;
-// its V fragments are loaded here; `next` (if not null) is the record whose
-// (-U)^H fragments go into An during the update.
-// With VP, Vin holds this sub-group's V fragments (loaded a sub-group ahead)
-// and Vn receives the next sub-group's during the first product; without VP
-// they are loaded here.
-template <typename E, int NB, int K, int T, int u, bool VP>
-__device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, NB, K>& A,
-                                            const typename WyElem<E>::R* __restrict__ rec,
-                                            const typename WyElem<E>::R* __restrict__ next,
-                                            WyA<E, NB, K>& An, const WyV<E, NB, K>& Vin,
-                                            WyV<E, NB, K>& Vn) {
-  using Gm = WyGeom<NB, K>;
+// W' = (-U)^H X over the window tiles u .. u+RT-1; a(plane, f) is (-U)^H
+// fragment f.
+template <typename E, int NB, int K, int T, int u, typename Frag>
+__device__ __forceinline__ void wy_first(const WyWin<E, NB, K, T>& w, Frag a,
+                                         typename WyElem<E>::V4 (&wr)[T],
+                                         typename WyElem<E>::V4 (&wi)[T]) {
   using V4 = typename WyElem<E>::V4;
-  constexpr int PL = WyElem<E>::PL, RT = Gm::RT;
-  WyV<E, NB, K> Vown;
-  if constexpr (VP) {
-    if (next) Vn.load(next);
-  } else {
-    Vown.load(rec);
-  }
-  const WyV<E, NB, K>& Vop = VP ? Vin : Vown;
-  V4 wr[T], wi[T];
+  constexpr int PL = WyElem<E>::PL, RT = WyGeom<NB, K>::RT;
   if constexpr (PL == 1) {
     V4 a0[T], a1[T];
 #pragma unroll
@@ -421,9 +450,9 @@ __device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, 
 #pragma unroll
         for (int t = 0; t < T; ++t) {
           if (kk & 1)
-            a1[t] = wy_mfma(A.a[0][4 * rt + kk], w.x[0][u + rt][t][kk], a1[t]);
+            a1[t] = wy_mfma(a(0, 4 * rt + kk), w.x[0][u + rt][t][kk], a1[t]);
           else
-            a0[t] = wy_mfma(A.a[0][4 * rt + kk], w.x[0][u + rt][t][kk], a0[t]);
+            a0[t] = wy_mfma(a(0, 4 * rt + kk), w.x[0][u + rt][t][kk], a0[t]);
         }
 #pragma unroll
     for (int t = 0; t < T; ++t) wr[t] = a0[t] + a1[t];
@@ -439,10 +468,10 @@ __device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, 
 #pragma unroll
         for (int t = 0; t < T; ++t) {
           const int f = 4 * rt + kk;
-          rr[t] = wy_mfma(A.a[0][f], w.x[0][u + rt][t][kk], rr[t]);
-          ii[t] = wy_mfma(A.a[1][f], w.x[1][u + rt][t][kk], ii[t]);
-          ri[t] = wy_mfma(A.a[0][f], w.x[1][u + rt][t][kk], ri[t]);
-          ir[t] = wy_mfma(A.a[1][f], w.x[0][u + rt][t][kk], ir[t]);
+          rr[t] = wy_mfma(a(0, f), w.x[0][u + rt][t][kk], rr[t]);
+          ii[t] = wy_mfma(a(1, f), w.x[1][u + rt][t][kk], ii[t]);
+          ri[t] = wy_mfma(a(0, f), w.x[1][u + rt][t][kk], ri[t]);
+          ir[t] = wy_mfma(a(1, f), w.x[0][u + rt][t][kk], ir[t]);
         }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -450,7 +479,15 @@ __device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, 
       wi[t] = ri[t] + ir[t];
     }
   }
-  if (next) An.load(next);
+}
+
+// X += V W' on the same tiles; v(plane, f) is V fragment f.
+template <typename E, int NB, int K, int T, int u, typename Frag>
+__device__ __forceinline__ void wy_second(WyWin<E, NB, K, T>& w, Frag v,
+                                          const typename WyElem<E>::V4 (&wr)[T],
+                                          const typename WyElem<E>::V4 (&wi)[T]) {
+  using V4 = typename WyElem<E>::V4;
+  constexpr int PL = WyElem<E>::PL, RT = WyGeom<NB, K>::RT;
   if constexpr (PL == 1) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -458,7 +495,7 @@ __device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, 
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int t = 0; t < T; ++t)
-          w.x[0][u + rt][t] = wy_mfma(Vop.v[0][4 * rt + kk], wr[t][kk], w.x[0][u + rt][t]);
+          w.x[0][u + rt][t] = wy_mfma(v(0, 4 * rt + kk), wr[t][kk], w.x[0][u + rt][t]);
   } else {
     // X += V W':  re += Vr W're - Vi W'im,  im += Vr W'im + Vi W're
     V4 nwi[T];
@@ -471,12 +508,39 @@ __device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, 
 #pragma unroll
         for (int t = 0; t < T; ++t) {
           const int f = 4 * rt + kk;
-          w.x[0][u + rt][t] = wy_mfma(Vop.v[0][f], wr[t][kk], w.x[0][u + rt][t]);
-          w.x[1][u + rt][t] = wy_mfma(Vop.v[0][f], wi[t][kk], w.x[1][u + rt][t]);
-          w.x[0][u + rt][t] = wy_mfma(Vop.v[1][f], nwi[t][kk], w.x[0][u + rt][t]);
-          w.x[1][u + rt][t] = wy_mfma(Vop.v[1][f], wr[t][kk], w.x[1][u + rt][t]);
+          w.x[0][u + rt][t] = wy_mfma(v(0, f), wr[t][kk], w.x[0][u + rt][t]);
+          w.x[1][u + rt][t] = wy_mfma(v(0, f), wi[t][kk], w.x[1][u + rt][t]);
+          w.x[0][u + rt][t] = wy_mfma(v(1, f), nwi[t][kk], w.x[0][u + rt][t]);
+          w.x[1][u + rt][t] = wy_mfma(v(1, f), wr[t][kk], w.x[1][u + rt][t]);
         }
   }
+}
+
+// Sub-group u applied to the window: W' = (-U)^H X over tiles u .. u+RT-1,
+// then X += V W' on the same tiles.  A: this sub-group's (-U)^H fragments;
+// its V fragments are loaded here; `next` (if not null) is the record whose
+// (-U)^H fragments go into An during the update.
+// With VP, Vin holds this sub-group's V fragments (loaded a sub-group ahead)
+// and Vn receives the next sub-group's during the first product; without VP
+// they are loaded here.
+template <typename E, int NB, int K, int T, int u, bool VP>
+__device__ __forceinline__ void wy_subgroup(WyWin<E, NB, K, T>& w, const WyA<E, NB, K>& A,
+                                            const typename WyElem<E>::R* __restrict__ rec,
+                                            const typename WyElem<E>::R* __restrict__ next,
+                                            WyA<E, NB, K>& An, const WyV<E, NB, K>& Vin,
+                                            WyV<E, NB, K>& Vn) {
+  using V4 = typename WyElem<E>::V4;
+  WyV<E, NB, K> Vown;
+  if constexpr (VP) {
+    if (next) Vn.load(next);
+  } else {
+    Vown.load(rec);
+  }
+  const WyV<E, NB, K>& Vop = VP ? Vin : Vown;
+  V4 wr[T], wi[T];
+  wy_first<E, NB, K, T, u>(w, [&](int p, int f) { return A.a[p][f]; }, wr, wi);
+  if (next) An.load(next);
+  wy_second<E, NB, K, T, u>(w, [&](int p, int f) { return Vop.v[p][f]; }, wr, wi);
 }
 
 // Chase steps [j0, j1) of block m on stripe c (j1 <= J0(m)); the stripe's
@@ -602,6 +666,186 @@ __global__ __launch_bounds__(64, OCC) void k_wy_b(const ProblemDesc* __restrict_
 }
 
 // ---------------------------------------------------------------------------
+// pipelined form: one launch
+// ---------------------------------------------------------------------------
+// A unit is one sweep block of 64 columns, all its chase steps in order, on a
+// workgroup of four waves with 16 columns each (hh_pipe.h, device form).  The
+// waves share the operand fragments: a sub-group's record passes through LDS
+// once for the four of them, fetched two sub-groups ahead, so that a wave
+// keeps registers only for its window and a compute unit holds two workgroups,
+// whose waits for rows overlap the other's products.  (One wave to a unit with
+// its fragments in registers: fp64 n = 4500 5.24 ms instead of 5.00, fp32 n =
+// 2501 with 1251 columns 0.70 instead of 0.57: a sub-group of fp32 products is
+// shorter than the latency of its fragments' loads.)
+//
+// Bound: large calls by the matrix cores (fp64, n = 4500: 80 % of the cycles,
+// at the 1.9 GHz that this load runs at); small ones by the chain of M + J
+// steps, each a wave's products (3.2 us for fp32, K = 96; 14 us complex, K =
+// 48), six or three barriers and about 3 us for the rows to pass from block to
+// block through memory.  Rows loaded ahead where the block above is far enough
+// were no faster (the lag they need costs the chain what the loads save).
+template <typename E, int NB, int K>
+struct WyUnit {
+  using R = typename WyElem<E>::R;
+  static constexpr int WAVES = 4;
+  static constexpr int REC = WyRec<E, NB, K>::REC;
+  static constexpr int CH = REC * (int)sizeof(R) / 16;              // 16-byte pieces of a record
+  static constexpr int PER = (CH + 64 * WAVES - 1) / (64 * WAVES);  // of one thread
+  static constexpr int LDS = 2 * REC;                               // two records
+  // workgroups of a compute unit (complex: registers, and 80 KB of LDS)
+  static constexpr int PER_CU = WyElem<E>::PL == 2 ? 1 : 2;
+  static constexpr bool kHas = K >= 32;  // two records are fetched ahead
+};
+
+// Steps 0 .. steps-1 of block m on 16 columns per wave (row r of a wave's
+// columns at bp + r SW; live: the wave has columns).
+template <typename E, int NB, int K, int SW>
+__device__ __forceinline__ void run_wy_unit(const typename WyElem<E>::R* __restrict__ P,
+                                            const int64_t* __restrict__ Bt,
+                                            E* __restrict__ bp, bool live, int64_t m,
+                                            int64_t steps, DevSync sync,
+                                            typename WyElem<E>::R* lds) {
+  using Gm = WyGeom<NB, K>;
+  using Un = WyUnit<E, NB, K>;
+  using R = typename WyElem<E>::R;
+  using V4 = typename WyElem<E>::V4;
+  constexpr int PL = WyElem<E>::PL, NF = Gm::NF, SG = Gm::SG, RTW = Gm::RTW;
+  constexpr int TN = NB / 16, TK = K / 16, REC = Un::REC, PER = Un::PER;
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int64_t s0 = m * K;
+  const R* __restrict__ Pm = P + Bt[m] * (SG * REC);
+  wy_u4 pre[2][PER];
+  auto fetch = [&](wy_u4 (&d)[PER], int64_t j, int u) {
+    const wy_u4* __restrict__ src = (const wy_u4*)(Pm + (j * SG + u) * REC) + tid;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if ((i + 1) * 64 * Un::WAVES <= Un::CH || i * 64 * Un::WAVES + tid < Un::CH)
+        d[i] = src[i * 64 * Un::WAVES];
+  };
+  auto stage = [&](const wy_u4 (&d)[PER], int buf) {
+    wy_u4* dst = (wy_u4*)(lds + buf * REC) + tid;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if ((i + 1) * 64 * Un::WAVES <= Un::CH || i * 64 * Un::WAVES + tid < Un::CH)
+        dst[i * 64 * Un::WAVES] = d[i];
+  };
+  WyWin<E, NB, K, 1> w;
+#pragma unroll
+  for (int p = 0; p < PL; ++p)
+#pragma unroll
+    for (int tr = 0; tr < RTW; ++tr) w.x[p][tr][0] = V4{0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < PER; ++i) pre[0][i] = pre[1][i] = wy_u4{0, 0, 0, 0};
+  fetch(pre[0], 0, SG - 1);
+  fetch(pre[1], 0, SG - 2);
+  stage(pre[0], 0);
+  int buf = 0;
+  sync.wait(0);
+  if (live) {
+    const E* __restrict__ rp = bp + (s0 + 1) * SW;
+#pragma unroll
+    for (int tr = 0; tr < RTW; ++tr) wy_load_tile<E, NB, K, 1, SW, true>(w, tr, rp);
+  }
+  for (int64_t j = 0; j < steps; ++j) {
+    E* __restrict__ rp = bp + (s0 + 1 + j * NB) * SW;
+    const bool more = j + 1 < steps;
+    RevFor<SG>::run([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      constexpr int cur = (SG - 1 - u) & 1;
+      // The record staged during the last sub-group is complete, and its
+      // predecessor's place free.  A step's first barrier follows the step
+      // before's stores' acknowledgement too.
+      if constexpr (u == SG - 1)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      else
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if constexpr (u == SG - 1) {
+        if (j > 0) {
+          if (tid == 0) sync.raise(j);
+          sync.wait(j);
+          if (live) {
+#pragma unroll
+            for (int tr = TK; tr < RTW; ++tr) wy_load_tile<E, NB, K, 1, SW, true>(w, tr, rp);
+          }
+        }
+      }
+      if constexpr (u > 1)
+        fetch(pre[cur], j, u - 2);
+      else if (more)
+        fetch(pre[cur], j + 1, SG + u - 2);
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay up here
+      const R* fr = lds + buf * REC + lane;
+      V4 wr[1], wi[1];
+      wy_first<E, NB, K, 1, u>(w, [&](int p, int f) { return fr[(p * NF + f) * 64]; }, wr, wi);
+      wy_second<E, NB, K, 1, u>(w, [&](int p, int f) { return fr[((PL + p) * NF + f) * 64]; }, wr,
+                                wi);
+      buf ^= 1;
+      if (u > 0 || more) stage(pre[cur ^ 1], buf);
+    });
+    if constexpr ((SG & 1) == 1)
+#pragma unroll
+      for (int i = 0; i < PER; ++i) pre[1][i] = pre[0][i];
+    // rows final for this block
+    if (live) {
+#pragma unroll
+      for (int tr = 0; tr < TN; ++tr) wy_store_tile<E, NB, K, 1, SW, true>(w, tr, rp, false);
+    }
+    if (more) {
+      // carried tiles TN .. RTW-1 move to 0 .. TK-1; the next NB rows follow
+#pragma unroll
+      for (int p = 0; p < PL; ++p)
+#pragma unroll
+        for (int tr = 0; tr < TK; ++tr) w.x[p][tr][0] = w.x[p][tr + TN][0];
+    }
+  }
+  // carried rows (or final after the block's last step); the window's last row
+  // may belong to another unit
+  if (live) {
+    E* __restrict__ rl = bp + (s0 + 1 + (steps - 1) * NB) * SW;
+#pragma unroll
+    for (int tr = TN; tr < RTW; ++tr)
+      wy_store_tile<E, NB, K, 1, SW, true>(w, tr, rl, tr == RTW - 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  if (tid == 0) sync.raise(steps);
+}
+
+// Units (order o, 64 columns h) by ticket; tiles: 16-column tiles of the
+// stripe copy, whose stripes are SW wide.
+template <typename E, int NB, int K, int SW>
+__global__ __launch_bounds__(256, (WyUnit<E, NB, K>::PER_CU)) void k_wy_units(
+    const typename WyElem<E>::R* __restrict__ P, const int64_t* __restrict__ Bt,
+    E* __restrict__ Qs, int64_t rows_pad, int64_t n, int64_t tiles, int64_t M,
+    int* __restrict__ words) {
+  using Un = WyUnit<E, NB, K>;
+  __shared__ typename WyElem<E>::R lds[Un::LDS];
+  __shared__ int ticket;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t H = (tiles + Un::WAVES - 1) / Un::WAVES;
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0)
+      ticket = __hip_atomic_fetch_add(words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int64_t u = __builtin_amdgcn_readfirstlane(ticket);
+    if (u >= M * H) return;
+    const int64_t o = u / H, h = u - o * H, m = M - 1 - o;
+    const int64_t c = Un::WAVES * h + wave;
+    DevSync sync;
+    sync.mine = words + (u + 1) * kPipeStride;
+    sync.before = o == 0 ? nullptr : words + (u - H + 1) * kPipeStride;
+    sync.before_steps = o == 0 ? 0 : (int)block_steps(n, NB, K, m + 1);
+    run_wy_unit<E, NB, K, SW>(
+        P, Bt, Qs + (c * 16 / SW) * rows_pad * SW + c * 16 % SW, c < tiles, m,
+        block_steps(n, NB, K, m), sync, lds);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 // Packed area of one problem: the records of every block's existing steps
@@ -662,6 +906,41 @@ hipError_t run_wy(const void* hh, const void* tau, void* Q, int64_t ldq, int64_t
                      st, (const E*)hh, (const E*)tau, n, Jmax, Pk, Bt);
   hipLaunchKernelGGL((k_to_rows_sw<E, SW>), dim3((unsigned)(pl.rows_pad / 64), gt), dim3(256), 0,
                      st, (const E*)Q, ldq, n, nev, Qs, pl.rows_pad, pl.G);
+  if constexpr (WyUnit<E, NB, K>::kHas) {
+    // One launch where the schedule is left open and the counts have room,
+    // unless the diagonal schedule is one launch too.  Against the diagonal
+    // launches: fp32, n = 300 / 1000 / 2501 with 1251 columns / 6000 / 12000:
+    // 96 / 219 / 577 / 5630 / 38800 us against 166 / 396 / 995 / 6900 / 45000;
+    // complex, n = 300 / 1500 / 4000: 249 / 1186 / 12600 against 294 / 1711 /
+    // 13080; fp64, n = 3000 / 6000 with 3000 columns / 20000: 1.79 / 5.66 / 321
+    // ms against 2.86 / 7.35 / 338; n = 2 (one launch): 57 us against 50.
+    const int64_t tiles = (nev + 15) / 16, H = (tiles + 3) / 4;
+    const int64_t groups = std::min<int64_t>(opt.streams, pl.G);
+    const int64_t nw = (int64_t)pipe_words(H * pl.M);
+    if (opt.steps <= 0 && !opt.grouped && pl.T * groups > 1 &&
+        H * pl.M < INT32_MAX / kPipeStride &&
+        (ws_in == nullptr || opt.sync_bytes >= (size_t)nw * sizeof(int))) {
+      int* words = opt.sync;
+      if (!ws_in) err = ws_alloc((void**)&words, (size_t)nw * sizeof(int), st);
+      if (err != hipSuccess) return release(err);
+      hipLaunchKernelGGL(k_pipe_clear, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, words,
+                         nw);
+      {
+        ProfScope prof(st, K, 0);
+        prof.before(st);
+        const int64_t wgs =
+            std::min<int64_t>(H * pl.M, WyUnit<E, NB, K>::PER_CU * (int64_t)num_cu);
+        hipLaunchKernelGGL((k_wy_units<E, NB, K, SW>), dim3((unsigned)wgs), dim3(256), 0, st,
+                           (const R*)Pk, (const int64_t*)Bt, Qs, pl.rows_pad, n, tiles, pl.M,
+                           words);
+        prof.after(st);
+      }
+      hipLaunchKernelGGL((k_from_rows_sw<E, SW>), dim3((unsigned)((n + 63) / 64), gt), dim3(256),
+                         0, st, (const E*)Qs, pl.rows_pad, (E*)Q, ldq, n, nev, pl.G);
+      if (!ws_in) err = ws_free(words, st);
+      return release(err != hipSuccess ? err : hipGetLastError());
+    }
+  }
   const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(opt.streams, pl.G));
   ProfScope prof(st, K, S, ns);
   {

@@ -1,5 +1,5 @@
-"""The one-launch pipelined schedules of fp64 calls (path SPLIT): the local
-form (a workgroup per stripe), the device form (one-wave workgroups over the
+"""The one-launch pipelined schedules: path WY's workgroups of four waves, and
+the fp64 calls of path SPLIT: the local form (a workgroup per stripe), the device form (one-wave workgroups over the
 whole device) and the batched form with one, two, four and eight waves per
 workgroup, against the diagonal launch schedule (bitwise: the same per-column
 arithmetic) and the oracle."""
@@ -94,3 +94,42 @@ def test_batched_waves_per_workgroup(torch_dev, count, n):
     torch.cuda.synchronize()
     for p in probs:
         assert torch.equal(p[0], one[0])
+
+
+# path WY: ragged columns (units of 64, tiles of 16), n around blocks and bands,
+# odd and even numbers of sub-groups
+@pytest.mark.parametrize("dt,n,nbw,k,nev", [
+    ("r32", 98, 64, 96, 1), ("r32", 700, 64, 96, 65), ("r32", 1601, 64, 160, 17),
+    ("r32", 513, 32, 96, 130), ("c64", 66, 64, 48, 3), ("c64", 338, 64, 48, 81),
+    ("c64", 400, 32, 32, 33), ("r64", 161, 64, 160, 64), ("r64", 1025, 64, 128, 63),
+    ("r64", 640, 64, 112, 129), ("r64", 450, 32, 96, 48), ("r64", 3201, 64, 128, 1030)])
+def test_wy_units_equal_launch_schedule(torch_dev, dt, n, nbw, k, nev):
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    q, hh, tau = drawn(torch, dev, n, nbw, nev, 7300 + n)
+    if dt == "r32":
+        q, hh, tau = q.t().float().t(), hh.float(), tau.float()
+    elif dt == "c64":   # unitary: H = I - tau v v^H with real tau and |v| fixed
+        ph = torch.polar(torch.ones_like(hh), torch.arange(hh.numel(), device=dev).reshape(
+            hh.shape).to(torch.float64))
+        hh, tau = hh * ph, tau.to(torch.complex128)
+        q = torch.complex(q.t(), q.t().flip(0)).t()
+    z = q.clone().cpu().numpy()
+    ref = q.t().clone().t()
+    print(f"wy units {dt} n={n} nbw={nbw} k={k} nev={nev}", flush=True)
+    P.hh_trafo(ref, hh, tau, nbw, path=P.PATH_WY, k=k, steps=2)
+    P.profile_enable(True)
+    try:
+        P.hh_trafo(q, hh, tau, nbw, path=P.PATH_WY, k=k)
+        pr = P.profile_last()
+    finally:
+        P.profile_enable(False)
+    torch.cuda.synchronize()
+    assert pr["launches"] == 1, pr
+    assert torch.equal(q, ref)
+    if n <= 700:
+        wide = np.complex128 if dt == "c64" else np.float64
+        want = bt.bt_tridiag_to_band(hh.cpu().numpy().astype(wide), tau.cpu().numpy().astype(wide),
+                                     np.asfortranarray(z.astype(wide)), n, nbw)
+        assert checks.max_rel_err(q.cpu().numpy().astype(wide), want) <= (
+            5e-5 if dt == "r32" else TOL)
