@@ -514,7 +514,7 @@ struct WyDirect {
   static void device(int64_t wgs, const E* P, const int64_t* Bt, const void* hh, E* Q,
                      int64_t ldq, int64_t n, int64_t nev, int64_t H, int64_t M, int* words,
                      hipStream_t st) {
-    hipLaunchKernelGGL((k_wyd_dev<NB, K>), dim3((unsigned)wgs), dim3(64), 0, st, P, Bt,
+    hipLaunchKernelGGL((k_wyd_units<NB, K>), dim3((unsigned)wgs), dim3(256), 0, st, P, Bt,
                        (const E*)hh, Q, ldq, n, nev, H, M, words);
   }
 };
@@ -587,12 +587,12 @@ hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int6
       // one launch: the schedule is left open
       const int64_t H = (nev + 15) / 16;
       const double step_us = (K / 16) * (8.0 * (NB / 16 + 1) + 4.0) * 64.0 / 2400.0;
-      const int64_t nw = (int64_t)pipe_words(H * pl.M);
+      const int64_t nw = (int64_t)pipe_words((H + 3) / 4 * pl.M);
       const bool room = ws_in == nullptr || opt.sync_bytes >= (size_t)nw * sizeof(int);
       const PipeChoice pc =
           choose_pipe(H, pl.M, Jmax, (double)block_base(n, NB, K, pl.M), num_cu, step_us,
                       room && H * pl.M < INT32_MAX / kPipeStride,
-                      diag_steps(pl, 2.0 * (double)slots, step_us));
+                      diag_us(pl, 2.0 * (double)slots, step_us));
       if (pc.form != PipeChoice::kDiagonal) {
         int* words = nullptr;
         const bool device = pc.form == PipeChoice::kDevice;
@@ -609,8 +609,8 @@ hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int6
           ProfScope prof(st, K, 0);
           prof.before(st);
           if (device)
-            F::device(std::min<int64_t>(H * pl.M, 8 * (int64_t)num_cu), Pk, Bt, hh, Qs, pl.rows_pad,
-                      n, nev, H, pl.M, words, st);
+            F::device(std::min<int64_t>((H + 3) / 4 * pl.M, 2 * (int64_t)num_cu), Pk, Bt, hh, Qs,
+                      pl.rows_pad, n, nev, (H + 3) / 4, pl.M, words, st);
           else
             F::local(H, pc.waves, Pk, Bt, hh, (E*)Q, ldq, n, nev, pl.M, st);
           prof.after(st);

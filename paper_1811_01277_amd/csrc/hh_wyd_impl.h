@@ -20,8 +20,8 @@
 // for it, so problems of a few thousand rows ran at a fifth of the peak; an
 // MFMA keeps the unit busy from one wave, and a wave covers 16 columns, so a
 // stripe's step is four times shorter.  With the one-launch schedules of
-// hh_pipe.h: n = 512, nbw = 32: 426 -> 152 us; n = 1000, nbw = 64: 637 -> 359
-// us; n = 8192 with 819 columns: 6.6 -> 4.4 ms; 256 problems of n = 200 ..
+// hh_pipe.h: n = 512, nbw = 32: 426 -> 152 us; n = 1000, nbw = 64: 637 -> 329
+// us; n = 8192 with 819 columns: 6.6 -> 4.1 ms; 256 problems of n = 200 ..
 // 2000, nbw = 32: 46.8 -> 41.4 ms.  A step of K = 80, NB = 64 takes about
 // 10 us on a wave that has its SIMD to itself, 6.8 of them MFMAs (74 cycles
 // each from one wave, 65 with two waves per SIMD).
@@ -166,61 +166,65 @@ struct WydBuffer {
   }
 };
 
-// Chase steps [j0, j1) of block m on the columns 16 h .. 16 h + 15 of the
-// caller's column-major Q: a lane's four rows of a tile are consecutive there
-// and a column's 16 rows one cache line, so no stripe copy is made (for n = 512
-// the two copies took 17 of 166 us, for the 256-problem batch 3 of 43 ms).
-// Rows past n and columns past nev are zero and not stored.  The device form
-// works on a stripe copy all the same (Q, ldq: the copy and its rows): its
-// stores go through to memory, where a stripe's whole lines cost less than a
-// column's 16-byte pieces (n = 8192, 819 columns: 4.5 ms against 5.3).
-// lv: WydGeom::LDS doubles of LDS of this wave's own, where it keeps the
-// current sub-group's reflectors: reflector i at i STR + 16, zeros
-// 16 places before and after it.  Both operands are read from there (row rho
-// of the sub-group meets reflector i's entry rho - i), so the parallelogram
-// needs no masks; reading them from the caller's array instead, 25 cache lines
-// per load on average, kept the address units 85 % busy and ran the
-// 256-problem batch at 57 ms.
-template <int NB, int K, typename Sync>
-__device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
-                                              const int64_t* __restrict__ Bt,
-                                              const double* __restrict__ hh, int64_t n,
-                                              int64_t nev, double* __restrict__ Q, int64_t ldq,
-                                              int64_t h, int64_t m, int64_t j0, int64_t j1,
-                                              const Sync& sync, double* __restrict__ lv) {
-  using Gm = WydGeom<NB, K>;
-  constexpr int SG = Gm::SG, RT = Gm::RT, RTW = Gm::RTW, SW = Gm::SW, STR = Gm::STR;
-  constexpr int TN = NB / 16, TK = K / 16;
-  constexpr int PER = 64 / NB;  // reflectors per load of the wave
-  constexpr int LG = NB == 64 ? 6 : 5;
-  const int lane = (int)(threadIdx.x & 63), q = lane >> 4, c = lane & 15;
-  const int pc = 4 * (c & 3) + (c >> 2);  // matrix row of label c within a tile
-  const int64_t s0 = m * K;
-  const double* __restrict__ Pm = P + Bt[m] * (K * Gm::RS) + lane;
-  const double* __restrict__ hb = hh + slot_offset(n, NB, s0) * NB;
-  // zeros around the reflectors
-  for (int e = lane; e < 16 * 32; e += 64) {
-    const int i = e >> 5, t = e & 31;
-    lv[i * STR + (t < 16 ? t : NB + t)] = 0.0;
-  }
-  double* const lw = lv + (lane / NB) * STR + 16 + lane % NB;  // staging
-  const double* const la = lv + c * (STR - 1) + 4 * q + 16;    // V^T operand
-  const double* const lb = lv + q * (STR - 1) + pc + 16;       // V operand
-  const int reach = lane % NB + lane / NB;
+// W = V^T X and X += V (-T W) of a sub-group, tiles u .. of the window x; la,
+// lb: the lane's operands in the staged reflectors, t: its -T fragments.
+template <int NB, int u>
+__device__ __forceinline__ wyd_d4 wyd_first(const wyd_d4* x, const double* la) {
+  wyd_d4 w0{0, 0, 0, 0}, w1{0, 0, 0, 0};
+#pragma unroll
+  for (int rt = 0; rt < NB / 16 + 1; ++rt)
+#pragma unroll
+    for (int kk = 0; kk < 4; kk += 2) {
+      w0 = wyd_mfma(la[16 * rt + kk], x[u + rt][kk], w0);
+      w1 = wyd_mfma(la[16 * rt + kk + 1], x[u + rt][kk + 1], w1);
+    }
+  return w0 + w1;
+}
+template <int NB, int u>
+__device__ __forceinline__ void wyd_second(wyd_d4* x, const double* lb, const double (&t)[4],
+                                           wyd_d4 w) {
+  // (two chains: each product waits for the one before it)
+  wyd_d4 z0{0, 0, 0, 0}, z1{0, 0, 0, 0};
+  z0 = wyd_mfma(t[0], w[0], z0);
+  z1 = wyd_mfma(t[1], w[1], z1);
+  z0 = wyd_mfma(t[2], w[2], z0);
+  z1 = wyd_mfma(t[3], w[3], z1);
+  const wyd_d4 z = z0 + z1;
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+    for (int rt = 0; rt < NB / 16 + 1; ++rt)
+      x[u + rt] = wyd_mfma(lb[4 * kk * (NB + 49) + 16 * rt], z[kk], x[u + rt]);
+}
 
-  wyd_d4 x[RTW];
-  double pre[16 / PER];
-  // the next step's rows, loaded during the step's last sub-group where that
-  // fits 256 registers without spilling
-  constexpr bool kAhead = NB == 32;
-  wyd_d4 nx[kAhead ? TN : 1];
-  const bool col_ok = 16 * h + c < nev;
-  double* __restrict__ qp = Q + (col_ok ? 16 * h + c : 0) * ldq + 4 * q;  // column major
-  double* __restrict__ sp = Q + (h >> 1) * ldq * SW + 16 * (h & 1);       // stripes
-  const int lane_off = (4 * q * SW + c) * 8;
-  // tiles [t0, t1) of the window at row w0 into y[0 ..)
-  auto load_rows = [&](wyd_d4* y, int t0, int t1, int64_t w0) {
-    if constexpr (Sync::kDev) {
+// The window rows of 16 columns: 16-row tiles [t0, t1) of the window at row w0.
+// Plain form: the caller's column-major Q, where a lane's four rows of a tile
+// are consecutive and a column's 16 rows one cache line, so no stripe copy is
+// made (for n = 512 the two copies took 17 of 166 us, for the 256-problem batch
+// 3 of 43 ms).  Rows past n and columns past nev are zero and not stored.
+// Device form (Q, ldq: a stripe copy and its rows): the stores go through to
+// memory, where a stripe's whole lines cost less than a column's 16-byte pieces
+// (n = 8192, 819 columns: 4.5 ms against 5.3).
+template <int NB, int K, bool DEV>
+struct WydRows {
+  using Gm = WydGeom<NB, K>;
+  static constexpr int SW = Gm::SW;
+  int64_t n;
+  int q;
+  bool col_ok;
+  double* qp;    // column major: the lane's column
+  double* sp;    // stripes
+  int lane_off;
+  __device__ __forceinline__ WydRows(double* Q, int64_t ldq, int64_t n_, int64_t nev, int64_t h,
+                                     int lane)
+      : n(n_),
+        q(lane >> 4),
+        col_ok(16 * h + (lane & 15) < nev),
+        qp(Q + (16 * h + (lane & 15) < nev ? 16 * h + (lane & 15) : 0) * ldq + 4 * (lane >> 4)),
+        sp(Q + (h >> 1) * ldq * SW + 16 * (h & 1)),
+        lane_off((4 * (lane >> 4) * SW + (lane & 15)) * 8) {}
+  __device__ __forceinline__ void load(wyd_d4* y, int t0, int t1, int64_t w0) const {
+    if constexpr (DEV) {
       const WydBuffer win(sp + w0 * SW);
 #pragma unroll
       for (int i = 0; i < t1 - t0; ++i)
@@ -245,9 +249,10 @@ __device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
         for (int r = 0; r < 4; ++r)
           y[i][r] = (col_ok && 16 * (t0 + i) + r < left) ? p[16 * (t0 + i) + r] : 0.0;
     }
-  };
-  auto store_rows = [&](int t0, int t1, int64_t w0, bool skip_last) {
-    if constexpr (Sync::kDev) {
+  }
+  __device__ __forceinline__ void store(const wyd_d4* x, int t0, int t1, int64_t w0,
+                                        bool skip_last) const {
+    if constexpr (DEV) {
       const WydBuffer win(sp + w0 * SW);
 #pragma unroll
       for (int tr = t0; tr < t1; ++tr)
@@ -269,11 +274,54 @@ __device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
       for (int tr = t0; tr < t1; ++tr)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (col_ok && 16 * tr + r < left &&
-              !(skip_last && tr == t1 - 1 && r == 3 && q == 3))
+          if (col_ok && 16 * tr + r < left && !(skip_last && tr == t1 - 1 && r == 3 && q == 3))
             p[16 * tr + r] = x[tr][r];
     }
-  };
+  }
+};
+
+// Chase steps [j0, j1) of block m on the columns 16 h .. 16 h + 15 of Q.
+// lv: WydGeom::LDS doubles of LDS of this wave's own, where it keeps the
+// current sub-group's reflectors: reflector i at i STR + 16, zeros
+// 16 places before and after it.  Both operands are read from there (row rho
+// of the sub-group meets reflector i's entry rho - i), so the parallelogram
+// needs no masks; reading them from the caller's array instead, 25 cache lines
+// per load on average, kept the address units 85 % busy and ran the
+// 256-problem batch at 57 ms.
+template <int NB, int K, typename Sync>
+__device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
+                                              const int64_t* __restrict__ Bt,
+                                              const double* __restrict__ hh, int64_t n,
+                                              int64_t nev, double* __restrict__ Q, int64_t ldq,
+                                              int64_t h, int64_t m, int64_t j0, int64_t j1,
+                                              const Sync& sync, double* __restrict__ lv) {
+  using Gm = WydGeom<NB, K>;
+  constexpr int SG = Gm::SG, RTW = Gm::RTW, STR = Gm::STR;
+  constexpr int TN = NB / 16, TK = K / 16;
+  constexpr int PER = 64 / NB;  // reflectors per load of the wave
+  constexpr int LG = NB == 64 ? 6 : 5;
+  const int lane = (int)(threadIdx.x & 63), q = lane >> 4, c = lane & 15;
+  const int pc = 4 * (c & 3) + (c >> 2);  // matrix row of label c within a tile
+  const int64_t s0 = m * K;
+  const double* __restrict__ Pm = P + Bt[m] * (K * Gm::RS) + lane;
+  const double* __restrict__ hb = hh + slot_offset(n, NB, s0) * NB;
+  // zeros around the reflectors
+  for (int e = lane; e < 16 * 32; e += 64) {
+    const int i = e >> 5, t = e & 31;
+    lv[i * STR + (t < 16 ? t : NB + t)] = 0.0;
+  }
+  double* const lw = lv + (lane / NB) * STR + 16 + lane % NB;  // staging
+  const double* const la = lv + c * (STR - 1) + 4 * q + 16;    // V^T operand
+  const double* const lb = lv + q * (STR - 1) + pc + 16;       // V operand
+  const int reach = lane % NB + lane / NB;
+
+  wyd_d4 x[RTW];
+  double pre[16 / PER];
+  // the next step's rows, loaded during the step's last sub-group where that
+  // fits 256 registers without spilling
+  constexpr bool kAhead = NB == 32;
+  wyd_d4 nx[kAhead ? TN : 1];
+  const WydRows<NB, K, false> rows(Q, ldq, n, nev, h, lane);
   // The sub-group's reflectors (s0 + 16 u + i, j) into registers.  Sweep s's
   // steps number (n - 1 - s + NB - 1) / NB, and that many slots lie between
   // its reflectors and the next sweep's; entry d exists for row r + d < n.
@@ -300,7 +348,7 @@ __device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
   };
 
   sync.wait(j0);
-  load_rows(x, 0, RTW, s0 + 1 + j0 * NB);
+  rows.load(x, 0, RTW, s0 + 1 + j0 * NB);
   fetch(j0, SG - 1);
   for (int64_t j = j0; j < j1; ++j) {
     const int64_t w0r = s0 + 1 + j * NB;
@@ -323,42 +371,19 @@ __device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
         fetch(j + 1, SG - 1);
       if constexpr (kAhead && u == 0) {
         ahead = j + 1 < j1 && sync.ready(j + 1);
-        if (ahead) load_rows(nx, TK, RTW, w0r + NB);
+        if (ahead) rows.load(nx, TK, RTW, w0r + NB);
       }
-      // W = V^T X
-      wyd_d4 w0{0, 0, 0, 0}, w1{0, 0, 0, 0};
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int kk = 0; kk < 4; kk += 2) {
-          w0 = wyd_mfma(la[16 * rt + kk], x[u + rt][kk], w0);
-          w1 = wyd_mfma(la[16 * rt + kk + 1], x[u + rt][kk + 1], w1);
-        }
+      const wyd_d4 w = wyd_first<NB, u>(x, la);
       // the last step's stores are older than the loads of this product: by
       // now their acknowledgement costs no wait
-      if constexpr (u == SG - 1 && !Sync::kDev)
+      if constexpr (u == SG - 1)
         if (j > j0) sync.done(j);
-      const wyd_d4 w = w0 + w1;
-      // W' = -T W (two chains: each product waits for the one before it)
-      wyd_d4 z0{0, 0, 0, 0}, z1{0, 0, 0, 0};
-      z0 = wyd_mfma(t[0], w[0], z0);
-      z1 = wyd_mfma(t[1], w[1], z1);
-      z0 = wyd_mfma(t[2], w[2], z0);
-      z1 = wyd_mfma(t[3], w[3], z1);
-      const wyd_d4 z = z0 + z1;
-      // X += V W'
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          x[u + rt] = wyd_mfma(lb[4 * kk * (STR - 1) + 16 * rt], z[kk], x[u + rt]);
+      wyd_second<NB, u>(x, lb, t, w);
       __builtin_amdgcn_wave_barrier();
     });
     __builtin_amdgcn_sched_barrier(0);
     // rows final for this block
-    store_rows(0, TN, w0r, false);
-    if constexpr (Sync::kDev)
-      if (j + 1 < j1) sync.done(j + 1);
+    rows.store(x, 0, TN, w0r, false);
     if (j + 1 < j1) {
 #pragma unroll
       for (int tr = 0; tr < TK; ++tr) x[tr] = x[tr + TN];
@@ -367,14 +392,131 @@ __device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
         for (int tr = 0; tr < TN; ++tr) x[TK + tr] = nx[tr];
       if (!ahead) {
         sync.wait(j + 1);
-        load_rows(x + TK, TK, RTW, w0r + NB);
+        rows.load(x + TK, TK, RTW, w0r + NB);
       }
     }
   }
   // carried rows; the window's last row (row NB+K-1, which no reflector of the
   // block touches) may belong to another tile and is not written
-  store_rows(TN, RTW, s0 + 1 + (j1 - 1) * NB, true);
+  rows.store(x, TN, RTW, s0 + 1 + (j1 - 1) * NB, true);
   sync.done(j1);
+}
+
+// A unit of the device form: all steps of block m on a workgroup of four waves,
+// this wave on the 16-column tile h16 (live: it has columns).  The waves share
+// the staged reflectors: each thread passes four (NB = 32: two) consecutive
+// entries of one reflector per sub-group, fetched two sub-groups ahead, and the
+// row waits of one workgroup overlap the products of the other on its compute
+// unit.  (One wave to a unit, each staging for itself: n = 8192 with 819
+// columns 4.45 ms instead of 4.06, n = 2900 1.9 instead of 1.6.  The same units
+// without hand-overs for a batch ran 256 problems in 53.8 ms, the one-wave
+// local form in 41.4: it loads the next rows ahead and has no barriers.)
+// lds: 2 WydGeom::LDS doubles.
+template <int NB, int K>
+__device__ __forceinline__ void run_wyd_unit(const double* __restrict__ P,
+                                             const int64_t* __restrict__ Bt,
+                                             const double* __restrict__ hh, int64_t n,
+                                             int64_t nev, double* __restrict__ Q, int64_t ldq,
+                                             int64_t h16, bool live, int64_t m,
+                                             const DevSync& sync, double* lds) {
+  using Gm = WydGeom<NB, K>;
+  constexpr int SG = Gm::SG, RTW = Gm::RTW, STR = Gm::STR, LDS = Gm::LDS;
+  constexpr int TN = NB / 16, TK = K / 16;
+  constexpr int PER = NB / 16;  // entries of a thread
+  const int tid = (int)threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+  const int pc = 4 * (c & 3) + (c >> 2);  // matrix row of label c within a tile
+  const int fi = tid >> 4, fd = (tid & 15) * PER;  // the thread's reflector and first entry
+  const int64_t s0 = m * K, steps = block_steps(n, NB, K, m);
+  const double* __restrict__ Pm = P + Bt[m] * (K * Gm::RS) + lane;
+  const int64_t slot0 = slot_offset(n, NB, s0);
+  const double* __restrict__ hb = hh + slot0 * NB;
+  int off[SG];  // of the thread's reflectors of step 0, in bytes
+#pragma unroll
+  for (int u = 0; u < SG; ++u) {
+    const int64_t s = s0 + 16 * u + fi;
+    off[u] = s <= n - 2 ? (int)((slot_offset(n, NB, s) - slot0) * (NB * 8)) + fd * 8 : 0;
+  }
+  double pre[2][PER];
+  auto fetch = [&](double (&d)[PER], int64_t j, int u) {
+    const WydBuffer src(hb + j * NB);
+    const int left = (int)(n - 1 - s0 - j * NB) - 16 * u - fi - fd;  // entries from fd on
+#pragma unroll
+    for (int e = 0; e < PER; ++e) d[e] = src.get(e < left, off[u] + 8 * e);
+  };
+  auto stage = [&](const double (&d)[PER], int buf) {
+    double* p = lds + buf * LDS + fi * STR + 16 + fd;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) p[e] = d[e];
+  };
+  const WydRows<NB, K, true> rows(Q, ldq, n, nev, h16, lane);
+  wyd_d4 x[RTW];
+#pragma unroll
+  for (int tr = 0; tr < RTW; ++tr) x[tr] = wyd_d4{0, 0, 0, 0};
+  // zeros around the reflectors
+  for (int e = tid; e < 2 * 16 * 32; e += 256) {
+    const int i = (e >> 5) & 15, t = e & 31;
+    lds[(e >> 9) * LDS + i * STR + (t < 16 ? t : NB + t)] = 0.0;
+  }
+  fetch(pre[0], 0, SG - 1);
+  fetch(pre[1], 0, SG - 2);
+  stage(pre[0], 0);
+  int buf = 0;
+  sync.wait(0);
+  if (live) rows.load(x, 0, RTW, s0 + 1);
+  for (int64_t j = 0; j < steps; ++j) {
+    const int64_t w0r = s0 + 1 + j * NB;
+    const bool more = j + 1 < steps;
+    const double* __restrict__ tp = Pm + j * (K * Gm::RS);
+    RevFor<SG>::run([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      constexpr int cur = (SG - 1 - u) & 1;
+      // the sub-group's reflectors are staged, its predecessor's place is
+      // free; a step's first barrier follows the step before's stores'
+      // acknowledgement too
+      if constexpr (u == SG - 1)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      else
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if constexpr (u == SG - 1) {
+        if (j > 0) {
+          if (tid == 0) sync.raise(j);
+          sync.wait(j);
+          if (live) rows.load(x + TK, TK, RTW, w0r);
+        }
+      }
+      double t[4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) t[kk] = tp[u * (16 * Gm::RS) + 64 * kk];
+      if constexpr (u > 1)
+        fetch(pre[cur], j, u - 2);
+      else if (more)
+        fetch(pre[cur], j + 1, SG + u - 2);
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay up here
+      const double* lv = lds + buf * LDS;
+      const wyd_d4 w = wyd_first<NB, u>(x, lv + c * (STR - 1) + 4 * q + 16);
+      wyd_second<NB, u>(x, lv + q * (STR - 1) + pc + 16, t, w);
+      buf ^= 1;
+      if (u > 0 || more) stage(pre[cur ^ 1], buf);
+    });
+    if constexpr ((SG & 1) == 1)
+#pragma unroll
+      for (int e = 0; e < PER; ++e) pre[1][e] = pre[0][e];
+    // rows final for this block
+    if (live) rows.store(x, 0, TN, w0r, false);
+    if (more) {
+#pragma unroll
+      for (int tr = 0; tr < TK; ++tr) x[tr] = x[tr + TN];
+    }
+  }
+  // carried rows; the window's last row (row NB+K-1, which no reflector of the
+  // block touches) may belong to another unit and is not written
+  if (live) rows.store(x, TN, RTW, s0 + 1 + (steps - 1) * NB, true);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  if (tid == 0) sync.raise(steps);
 }
 
 // Diagonal schedule: launch t's tiles (16-column halves of the stripes c0 ..
@@ -475,28 +617,31 @@ __global__ __launch_bounds__(ONE ? 64 : 512, 2) void k_wyd_local_b(
   }
 }
 
-// Device form: units (order o, 16-column half h) by ticket.
+// Device form: units (order o, 64 columns h) by ticket, on a stripe copy.
 template <int NB, int K>
-__global__ __launch_bounds__(64, 2) void k_wyd_dev(const double* __restrict__ P,
-                                                   const int64_t* __restrict__ Bt,
-                                                   const double* __restrict__ hh,
-                                                   double* __restrict__ Q, int64_t ldq,
-                                                   int64_t n, int64_t nev, int64_t H, int64_t M,
-                                                   int* __restrict__ words) {
-  __shared__ double lv[WydGeom<NB, K>::LDS];
+__global__ __launch_bounds__(256, 2) void k_wyd_units(const double* __restrict__ P,
+                                                      const int64_t* __restrict__ Bt,
+                                                      const double* __restrict__ hh,
+                                                      double* __restrict__ Qs, int64_t rows_pad,
+                                                      int64_t n, int64_t nev, int64_t H,
+                                                      int64_t M, int* __restrict__ words) {
+  __shared__ double lds[2 * WydGeom<NB, K>::LDS];
+  __shared__ int ticket;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   for (;;) {
-    int t = 0;
+    __syncthreads();
     if (threadIdx.x == 0)
-      t = __hip_atomic_fetch_add(words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int64_t u = __builtin_amdgcn_readfirstlane(t);
+      ticket = __hip_atomic_fetch_add(words, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int64_t u = __builtin_amdgcn_readfirstlane(ticket);
     if (u >= M * H) return;
-    const int64_t o = u / H, h = u - o * H, m = M - 1 - o;
+    const int64_t o = u / H, h = u - o * H, m = M - 1 - o, h16 = 4 * h + wave;
+    const bool live = 16 * h16 < nev;
     DevSync sync;
     sync.mine = words + (u + 1) * kPipeStride;
     sync.before = o == 0 ? nullptr : words + (u - H + 1) * kPipeStride;
     sync.before_steps = o == 0 ? 0 : (int)block_steps(n, NB, K, m + 1);
-    run_wyd_steps<NB, K>(P, Bt, hh, n, nev, Q, ldq, h, m, 0,
-                         block_steps(n, NB, K, m), sync, lv);
+    run_wyd_unit<NB, K>(P, Bt, hh, n, nev, Qs, rows_pad, live ? h16 : 0, live, m, sync, lds);
   }
 }
 
