@@ -37,10 +37,13 @@ extern "C" {
  * dtype: ELPA_R64 or ELPA_C64 (ELPA_R32 is not provided: single-precision
  *    solves keep the reduction in double precision); 1 <= nbw <= 512.
  * Asynchronous on `stream` (a hipStream_t; NULL = the null stream).  Bands
- * with nbw <= 64 run the chase in one launch, a workgroup per sweep in order
- * of a ticket, each step's blocks held in registers; only A's lower triangle
- * is read and updated (the two-sided update of the diagonal block as a rank-2
- * update), the upper triangle is written once at the end, and a small
+ * with nbw <= 64 run the chase in one launch, each step's blocks held in
+ * registers: a workgroup per chase position, which all run at once and pass
+ * rows and reflectors to their neighbours, or, where the device has no room for
+ * that (it is found out within a millisecond, before anything is written), a
+ * workgroup per sweep in order of a ticket.  Only A's lower triangle is read
+ * and updated (the two-sided update of the diagonal block as a rank-2 update),
+ * the upper triangle is written once at the end, and a small
  * workspace comes from the library's workspace cache.  Wider bands take about
  * 3 n kernel launches, each a bounded set of independent chase steps (steps
  * that touch disjoint entries), and update both triangles step by step.

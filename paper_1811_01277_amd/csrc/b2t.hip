@@ -2,7 +2,8 @@
 // include/elpa_b2t.h; Kus et al., Sec. 2), one column per chase step, with
 // the reflectors written in the slot layout of the tridiagonal -> band
 // back-transformation.  Bands up to 64 wide run the whole chase in one launch
-// (k_chase_sweeps below); wider ones run the launch schedule described here.
+// (k_chase_resident, or k_chase_sweeps, below); wider ones run the launch
+// schedule described here.
 //
 // Schedule.  Chase step (s, j) (row r = s+1+j*nbw, length L <= nbw) reads and
 // writes only entries of the square [r-nbw, r+L+nbw)^2 that lie in rows
@@ -282,7 +283,9 @@ __global__ __launch_bounds__(512) void k_chase(E* __restrict__ A, int64_t lda, i
 // Bound: the chain of two steps and one hand-over per sweep, all latency.
 // One launch per step (3 n launches, 12.1 us each at any size) took 34 ms at
 // n = 1000 and 148 ms at n = 4000 (nbw = 64, fp64); the one-launch chase takes
-// 8.7 and 36 ms, about 9 us per sweep.
+// 8.7 and 36 ms, about 9 us per sweep.  It runs where the resident form below
+// (4.5 and 21.4 ms) does not: more positions than the device holds, or a busy
+// device.
 //
 // Layout: lane i of each wave holds row i of the blocks, wave w of NW the
 // columns w, w + NW, ... (8 per wave): each block is one coalesced access per
@@ -292,6 +295,7 @@ __global__ __launch_bounds__(512) void k_chase(E* __restrict__ A, int64_t lda, i
 // take 15 exchanges and not 48, and lane 8 q ends with column q's.
 constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // 20 s of the 100 MHz clock
 constexpr int kProgStride = 16;                          // counts 64 bytes apart
+constexpr int64_t kGatherTicks = 100000;                 // 1 ms
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov(double x) {
@@ -372,19 +376,42 @@ __device__ __forceinline__ void store_dev(z64* p, z64 x) {
 __device__ __forceinline__ double real_part(double a) { return a; }
 __device__ __forceinline__ z64 real_part(z64 a) { return z64{a.re, 0.0}; }
 
-// progress counts, ticket and failure word of one call
+// keeps a product out of a fused multiply-add
+__device__ __forceinline__ double rounded(double x) {
+  asm("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ z64 rounded(z64 x) { return z64{rounded(x.re), rounded(x.im)}; }
+// a conj(b) + c conj(d), in one way in both chases
+__device__ __forceinline__ double rank2(double a, double b, double c, double d) {
+  return __builtin_fma(a, b, rounded(c * d));
+}
+__device__ __forceinline__ z64 rank2(z64 a, z64 b, z64 c, z64 d) {
+  return add(mul(a, conj_(b)), mul(c, conj_(d)));
+}
+
+// progress counts, ticket, failure word and messages of one call
+using u64 = unsigned long long;
 struct ChaseState {
   int* prog;  // [n - 1] counts, kProgStride apart
   int* ticket;
   int* failed;
+  int* arrived;  // resident form: workgroups that are there
+  int* state;    // kOpen, kGo, kAlone
+  u64* words;    // its messages
+  int64_t nwords;
 };
+constexpr int kOpen = 0, kGo = 1, kAlone = 2;
 
-__global__ __launch_bounds__(256) void k_chase_clear(ChaseState c, int64_t n) {
+__global__ __launch_bounds__(256) void k_chase_clear(ChaseState c, int64_t n, int open) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n - 1) c.prog[i * kProgStride] = 0;
+  for (int64_t w = i; w < c.nwords; w += (int64_t)gridDim.x * blockDim.x) c.words[w] = 0;
   if (i == 0) {
     *c.ticket = 0;
     *c.failed = 0;
+    *c.arrived = 0;
+    *c.state = open;
   }
 }
 
@@ -420,6 +447,9 @@ __global__ __launch_bounds__(64 * NW) void k_chase_sweeps(E* __restrict__ A, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // row i0 + lane of column k: a wave-uniform base and a 32-bit lane offset
   auto at = [&](int64_t i0, int64_t k) -> E* { return A + (i0 + k * lda) + (unsigned)lane; };
+
+  // the resident form did the whole chase
+  if (__hip_atomic_load(st.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kGo) return;
 
   for (;;) {
     __syncthreads();
@@ -538,7 +568,7 @@ __global__ __launch_bounds__(64 * NW) void k_chase_sweeps(E* __restrict__ A, int
           const E wk = read_lane(wl, k), rk = mul(ct, read_lane(wr, 8 * q));
           // column 0 is the reduced one (j = 0: the only one)
           if (k >= 1) xr[q] = sub(xr[q], mul(vl, rk));
-          xd[q] = sub(xd[q], add(mul(wl, conj_(vk[q])), mul(vl, conj_(wk))));
+          xd[q] = sub(xd[q], rank2(wl, vk[q], vl, wk));
           if (lane == k) xd[q] = real_part(xd[q]);
         }
       }
@@ -563,8 +593,366 @@ __global__ __launch_bounds__(64 * NW) void k_chase_sweeps(E* __restrict__ A, int
   }
 }
 
-// The upper triangle of the result (the one-launch chase updates only the
-// lower one): A[k-1, k] = e[k-1], zeros above it up to 2 nb rows.
+// ---------------------------------------------------------------------------
+// nb <= 64, all positions resident
+// ---------------------------------------------------------------------------
+// A workgroup stays at chase position j and holds its blocks R and D (as above)
+// through all sweeps: the next sweep's blocks are the same ones, one row and
+// one column further down.  Columns sit in the waves by their global index
+// modulo nb, so the column that comes takes the place of the one that leaves;
+// rows move up one lane.  Sums run in the order of the moving form's, which
+// gives the same bits where the waves divide nb.  Per sweep two messages pass between neighbours:
+//   forward   v and tau of position j, for the right update of R_{j+1};
+//   backward  the row that position j+1 gives up, R_{j+1}'s first: beta, the
+//             entries behind it, and D_{j+1}'s first entry: position j's new
+//             last row.  (New entries left of beta are zero.)
+// Position 0 gives its first row up to the result: e and d.
+//
+// A position's reflector needs the forward message, beta of the backward
+// message of the sweep before, and its own blocks, so the chain is, per sweep,
+// two hand-overs, two sums over the waves' columns and two reflectors; the
+// rest of a step runs beside it.  Every wave receives for itself and forms the
+// reflector for itself, which saves the barriers a broadcast would take.
+//
+// Words: an 8-byte word carries half a double and the sweep's tag, so a word
+// that is there is whole.  Messages alternate between two places.  A forward
+// place is written again two sweeps later, after the receiver's beta of the
+// sweep between came back, which followed a barrier behind its waves' receipt;
+// a backward place two sweeps later after the forward message of that sweep,
+// which the receiver sent after the barriers of the sweep between.
+//
+// All J positions must be running: the workgroups count themselves, and the
+// last one opens the chase (kGo).  If they do not come together in time the
+// chase is left to k_chase_sweeps behind (kAlone), nothing having been written.
+// A wait of more than kWaitTicks is given up as above, and then all are.
+//
+// Bound: the latency of that chain, and nearly as much the instructions of one
+// position's step.  n = 1000 / 4000, nbw = 64: 4.5 / 21.4 ms, where workgroups
+// that follow the sweeps take 8.7 / 36; complex, n = 700, nbw = 32: 4.1 ms
+// against 7.1.  Selects in place of uniform branches and column numbers kept
+// from sweep to sweep took 6.2 ms to 4.5 at n = 1000.
+template <typename E>
+struct ChaseWords {
+  static constexpr int W = std::is_same<E, double>::value ? 2 : 4;  // words per value
+  static constexpr int FWD = 64 * W, BACK = 65 * W, ALL = 2 * (FWD + BACK);
+};
+__device__ __forceinline__ void put_word(u64* p, unsigned half, unsigned tag) {
+  __hip_atomic_store(p, ((u64)half << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_value(u64* p, double x, unsigned tag) {
+  put_word(p, (unsigned)__double2hiint(x), tag);
+  put_word(p + 1, (unsigned)__double2loint(x), tag);
+}
+__device__ __forceinline__ void put_value(u64* p, z64 x, unsigned tag) {
+  put_value(p, x.re, tag);
+  put_value(p + 2, x.im, tag);
+}
+__device__ __forceinline__ u64 get_word(const u64* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool get_value(const u64* p, double& x, unsigned tag) {
+  const u64 h = get_word(p), l = get_word(p + 1);
+  x = __hiloint2double((int)(h >> 32), (int)(l >> 32));
+  return (unsigned)h == tag && (unsigned)l == tag;
+}
+__device__ __forceinline__ bool get_value(const u64* p, z64& x, unsigned tag) {
+  const bool a = get_value(p, x.re, tag), b = get_value(p + 2, x.im, tag);
+  return a && b;
+}
+// the lanes with `mine` (`mine2`) receive their values; zero in the others
+template <typename E>
+__device__ __forceinline__ void receive(const u64* p, bool mine, unsigned tag, E& x, const u64* p2,
+                                        bool mine2, unsigned tag2, E& x2, int* failed) {
+  int64_t t0 = 0;
+  x = x2 = zero<E>();
+  for (int k = 0;; ++k) {
+    E y = zero<E>(), y2 = zero<E>();
+    bool ok = true;
+    if (mine) ok = get_value(p, y, tag);
+    if (mine2 && !get_value(p2, y2, tag2)) ok = false;
+    if (__all(ok)) {
+      x = y;
+      x2 = y2;
+      return;
+    }
+    if ((k & 63) == 63) {
+      if (__hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+      const int64_t t = (int64_t)wall_clock64();
+      if (t0 == 0) t0 = t;
+      if (t - t0 > kWaitTicks) {
+        __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ double choose(bool c, double a, double b) { return c ? a : b; }
+__device__ __forceinline__ z64 choose(bool c, z64 a, z64 b) {
+  return z64{c ? a.re : b.re, c ? a.im : b.im};
+}
+// lane l takes lane l + 1's value, the last one zero
+__device__ __forceinline__ double next_lane(double x) { return dpp_mov<0x130>(x); }
+__device__ __forceinline__ z64 next_lane(z64 x) { return z64{next_lane(x.re), next_lane(x.im)}; }
+
+template <typename E, int NW>
+__global__ __launch_bounds__(64 * NW) void k_chase_resident(E* __restrict__ A, int64_t lda, int n,
+                                                            int nb, ChaseState st,
+                                                            int64_t gather_ticks,
+                                                            E* __restrict__ hh,
+                                                            E* __restrict__ tau) {
+  constexpr int NQ = 8, W = ChaseWords<E>::W;
+  __shared__ E cs[64], ys[64], py[NW][64], pu[NW][64], row[NW][NQ];
+  __shared__ int sh_j, sh_state;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid == 0) {
+    int now = __hip_atomic_load(st.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (now == kOpen) {
+      const int old =
+          __hip_atomic_fetch_add(st.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sh_j = old;
+      int expect = kOpen;
+      if (old == (int)gridDim.x - 1)
+        __hip_atomic_compare_exchange_strong(st.state, &expect, kGo, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int64_t t0 = (int64_t)wall_clock64();
+      while ((now = __hip_atomic_load(st.state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) ==
+             kOpen) {
+        if ((int64_t)wall_clock64() - t0 > gather_ticks) {
+          expect = kOpen;
+          __hip_atomic_compare_exchange_strong(st.state, &expect, kAlone, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
+    sh_state = now;
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(sh_state) != kGo) return;
+  const int j = __builtin_amdgcn_readfirstlane(sh_j);
+  u64* const out_fwd = st.words + (int64_t)j * ChaseWords<E>::ALL;   // to position j + 1
+  u64* const out_back = out_fwd + 2 * ChaseWords<E>::FWD;            // to position j - 1
+  const u64* const in_fwd = out_fwd - ChaseWords<E>::ALL;
+  const u64* const in_back = out_back + ChaseWords<E>::ALL;
+
+  const bool in_band = lane < nb;
+  unsigned base = nb == 1 ? 0 : 1;  // place of columns r - nb and r
+  int J = (n - 1 + nb - 1) / nb, last = n - 1 - (J - 1) * nb;  // of this sweep; its last length
+  int64_t slot0 = 0;
+  E xr[NQ], xd[NQ];
+  // col[q]: the block's column at the wave's place q; nb, a lane of zeros, for
+  // places past the band
+  int col[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int k = wave + NW * q;
+    col[q] = k >= nb ? nb : (k < (int)base ? k - (int)base + nb : k - (int)base);
+    const int r = 1 + j * nb, c = col[q];
+    const bool ok = in_band && k < nb && r + lane < n;
+    xr[q] = ok && (j > 0 || c == nb - 1) ? A[r + lane + (int64_t)(r - nb + c) * lda] : zero<E>();
+    xd[q] = ok && r + c < n && lane >= c ? A[r + lane + (int64_t)(r + c) * lda] : zero<E>();
+  }
+  for (int s = 0;; ++s) {
+    const int r = s + 1 + j * nb;
+    if (r >= n) return;
+    const unsigned tag = (unsigned)s + 1u;
+    const unsigned old = base == 0 ? nb - 1 : base - 1;  // place of the last column
+    const int turn = nb - (int)base;  // columns from here on sit at places from 0
+    // the sweep before: position j + 1 gave up row r + nb - 1
+    const bool gained = s > 0 && r + nb - 1 < n;
+    const u64* const bw = in_back + ((s - 1) & 1) * ChaseWords<E>::BACK;
+    // the forward message, and beta of the last row for the wave that holds it
+    // (together: they come at about the same time)
+    E vp, last_beta;
+    receive<E>(in_fwd + (s & 1) * ChaseWords<E>::FWD + lane * W, j > 0 && in_band, tag, vp,
+               bw + old * W, gained && old % NW == (unsigned)wave && lane == nb - 1, tag - 1u, last_beta,
+               st.failed);
+    const bool newest = gained && old % NW == (unsigned)wave;
+    if (newest) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        xr[q] = choose(col[q] == nb - 1 && lane == nb - 1, last_beta, xr[q]);
+    }
+    // right update of R with the reflector of position j - 1; sums in the
+    // order of the columns, not of their places
+    E tp = zero<E>(), ul = zero<E>();
+    E vk[NQ];
+    const unsigned red = j > 0 ? base : old;  // place of the column to reduce
+    if (j > 0) {
+      tp = read_lane(vp, 0);
+      if (lane == 0) vp = from_re<E>(1.0);
+      E ru = zero<E>();
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        vk[q] = read_lane(vp, col[q] & 63);
+        ru = add(ru, mul(xr[q], choose(col[q] < turn, vk[q], zero<E>())));
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        ru = add(ru, mul(xr[q], choose(col[q] >= turn, vk[q], zero<E>())));
+      pu[wave][lane] = ru;
+    }
+    if (red % NW == (unsigned)wave) {
+      const int want = j > 0 ? 0 : nb - 1;
+      E x = xr[0];
+#pragma unroll
+      for (int q = 1; q < NQ; ++q) x = choose(col[q] == want, xr[q], x);
+      cs[lane] = x;
+    }
+    __syncthreads();
+    E x = cs[lane];
+    const bool right =
+        j > 0 && __builtin_amdgcn_readfirstlane(re(tp) != 0.0 || im(tp) != 0.0) != 0;
+    if (right) {
+      E us = zero<E>();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) us = add(us, pu[(base + w) % NW][lane]);
+      // (rounded once, for the reduced column too, whose entry of v is 1)
+      ul = rounded(mul(tp, us));
+      x = sub(x, ul);
+    }
+    // the reflector, in every wave the same
+    const double ss = wave_sum_dpp(in_band && lane >= 1 ? abs2(x) : 0.0);
+    const E alpha = read_lane(x, 0);
+    const double ar = re(alpha), ai = im(alpha);
+    E tv = zero<E>(), sc = zero<E>();
+    double beta = ar;
+    const bool act = __builtin_amdgcn_readfirstlane(ss != 0.0 || ai != 0.0) != 0;
+    if (act) {
+      const double h = sqrt(ar * ar + ai * ai + ss);
+      beta = ar >= 0.0 ? -h : h;
+      if constexpr (std::is_same<E, double>::value) {
+        tv = (beta - ar) / beta;
+        sc = 1.0 / (ar - beta);
+      } else {
+        tv = z64{(beta - ar) / beta, -ai / beta};
+        const double dr = ar - beta, dd = dr * dr + ai * ai;
+        sc = z64{dr / dd, -ai / dd};
+      }
+    }
+    const E vl = lane == 0 ? from_re<E>(1.0) : (in_band ? mul(x, sc) : zero<E>());
+    if (wave == 0 && r + nb < n && in_band)
+      put_value(out_fwd + (s & 1) * ChaseWords<E>::FWD + lane * W, lane == 0 ? tv : vl, tag);
+    if (wave == 1 && lane == 0) {
+      if (j > 0)
+        put_value(out_back + (s & 1) * ChaseWords<E>::BACK + base * W, from_re<E>(beta), tag);
+      else
+        A[s + 1 + (int64_t)s * lda] = from_re<E>(beta);
+    }
+    if (wave == 2) {
+      if (in_band) hh[(slot0 + j) * nb + lane] = vl;
+      if (lane == 0) tau[slot0 + j] = tv;
+    }
+    if (right) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) xr[q] = sub(xr[q], mul(ul, conj_(vk[q])));
+    }
+    // the rest of the last row, in D: lane q receives this wave's column q
+    const int kq = wave + NW * (lane & 7);
+    if (gained) {
+      E m, none;
+      receive<E>(bw + (kq == (int)old ? 64 : kq) * W, lane < NQ && kq < nb, tag - 1u, m, nullptr, false,
+                 0, none, st.failed);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const E v = read_lane(m, q);
+        xd[q] = choose(lane == nb - 1, v, xd[q]);
+      }
+    }
+    // left update of R, two-sided update of D
+    E wr = zero<E>();
+    if (act) {
+      const E cvl = conj_(vl);
+      E p[NQ], ry = zero<E>();
+      if (j > 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) p[q] = mul(cvl, xr[q]);
+        wr = wave_sum8(p);
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        p[q] = choose(lane > col[q], mul(cvl, xd[q]), zero<E>());
+        vk[q] = read_lane(vl, col[q] & 63);
+        ry = add(ry, mul(xd[q], choose(col[q] < turn, vk[q], zero<E>())));
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        ry = add(ry, mul(xd[q], choose(col[q] >= turn, vk[q], zero<E>())));
+      const E cd = wave_sum8(p);
+      // (v^H D)_k = conj((D v)_k)
+      const int k8 = wave + NW * (lane >> 3), c8 = k8 - (int)base;
+      if ((lane & 7) == 0 && k8 < nb) ys[c8 < 0 ? c8 + nb : c8] = conj_(cd);
+      py[wave][lane] = ry;
+    }
+    __syncthreads();
+    if (act) {
+      E yl = in_band ? ys[lane] : zero<E>();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) yl = add(yl, py[(base + w) % NW][lane]);
+      const double mu = wave_sum_dpp(re(mul(conj_(vl), yl)));
+      const double h2 = 0.5 * abs2(tv) * mu;
+      const E wl = sub(mul(tv, yl), mul(from_re<E>(h2), vl));
+      if (j > 0) {
+        const E ct = conj_(tv);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          xr[q] = sub(xr[q], mul(vl, mul(ct, read_lane(wr, 8 * q))));
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const E wk = read_lane(wl, col[q] & 63);
+        xd[q] = sub(xd[q], rank2(wl, vk[q], vl, wk));
+        xd[q] = choose(lane < col[q], zero<E>(), xd[q]);
+        if constexpr (!std::is_same<E, double>::value)
+          xd[q] = choose(lane == col[q], real_part(xd[q]), xd[q]);
+      }
+    }
+    // column r passes from D to R: its first entry is the last of row r that
+    // leaves, the others follow in R
+    if (base % NW == (unsigned)wave) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        xr[q] = choose(col[q] == 0, xd[q], xr[q]);
+        xd[q] = choose(col[q] == 0, zero<E>(), xd[q]);
+      }
+    }
+    // row r leaves
+    {
+      if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) row[wave][q] = xr[q];
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (j > 0) {
+        if (lane < NQ && kq < nb)
+          put_value(out_back + (s & 1) * ChaseWords<E>::BACK + (kq == (int)base ? 64 : kq) * W,
+                    row[wave][lane], tag);
+      } else if (lane < NQ && kq == (int)base) {
+        A[r + (int64_t)r * lda] = row[wave][lane];
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    // the rows move up by one; row r + nb comes with the next sweep
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      xr[q] = next_lane(xr[q]);
+      xd[q] = next_lane(xd[q]);
+      const int c = col[q] == 0 ? nb - 1 : col[q] - 1;
+      col[q] = col[q] == nb ? nb : c;
+    }
+    slot0 += J;
+    if (--last == 0) {
+      --J;
+      last = nb;
+    }
+    base = base + 1 == (unsigned)nb ? 0 : base + 1;
+  }
+}
+
+// The rest of the result (the one-launch chases leave the upper triangle, the
+// resident one also the zeros of the lower): A[k-1, k] = e[k-1], zeros above it
+// up to 2 nb rows; zeros in column k-1 below row k up to nb rows.
 template <typename E>
 __global__ __launch_bounds__(256) void k_upper_out(E* __restrict__ A, int64_t lda, int64_t n,
                                                    int64_t nb, const double* __restrict__ e) {
@@ -575,6 +963,8 @@ __global__ __launch_bounds__(256) void k_upper_out(E* __restrict__ A, int64_t ld
     if (i < 0) break;
     A[i + k * lda] = from_re<E>(q == 0 ? e[k - 1] : 0.0);
   }
+  for (int64_t i = k + 1 + threadIdx.x; i < n && i < k + nb; i += blockDim.x)
+    A[i + (k - 1) * lda] = zero<E>();
 }
 
 template <typename E>
@@ -596,19 +986,38 @@ inline int64_t steps_of(int64_t n, int64_t nb, int64_t s) { return (n - 1 - s + 
 // nb <= 64: the one-launch chase
 template <typename E>
 int run_sweeps(int64_t n, int64_t nb, E* A, int64_t lda, double* d, double* e, E* hh, E* tau,
-               hipStream_t st) {
+               hipStream_t st, int64_t gather_ticks) {
+  const auto resident = nb > 32 ? k_chase_resident<E, 8> : k_chase_resident<E, 4>;
+  const int threads = nb > 32 ? 512 : 256;
+  const int64_t J = n > 1 ? steps_of(n, nb, 0) : 0;
+  // the resident form needs a place for every position on an idle device
+  int dev = 0, cus = 0, per_cu = 0;
+  const bool fits = gather_ticks >= 0 && n < (int64_t(1) << 30) &&
+                    hipGetDevice(&dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) ==
+                        hipSuccess &&
+                    hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                        &per_cu, reinterpret_cast<const void*>(resident), threads, 0) ==
+                        hipSuccess &&
+                    J <= (int64_t)cus * per_cu;
   const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
   int* words = nullptr;
-  const size_t bytes = ((size_t)std::max<int64_t>(n - 1, 1) + 1) * kProgStride * sizeof(int);
-  const hipError_t err = ehh::ws_alloc((void**)&words, bytes, st);
+  const size_t counts = ((size_t)std::max<int64_t>(n - 1, 1) + 1) * kProgStride * sizeof(int);
+  const int64_t nwords = fits ? J * ChaseWords<E>::ALL : 0;
+  const hipError_t err = ehh::ws_alloc((void**)&words, counts + (size_t)nwords * sizeof(u64), st);
   if (err != hipSuccess)
     return err == hipErrorOutOfMemory ? ELPA_ERR_NOMEM : ELPA_ERR_DEVICE;
-  const ChaseState cs{words + kProgStride, words, words + 1};
+  const ChaseState cs{words + kProgStride, words,     words + 1, words + 2,
+                      words + 3,           (u64*)((char*)words + counts), nwords};
   if (n > 1) {
-    hipLaunchKernelGGL(k_chase_clear, dim3((unsigned)((n + 254) / 256)), dim3(256), 0, st, cs, n);
-    // a sweep lags two steps behind the one before it, so at most about J / 2
-    // are under way; the tickets make any number of workgroups correct
-    const int64_t J = (n - 1 + nb - 1) / nb;
+    hipLaunchKernelGGL(k_chase_clear, dim3((unsigned)((n + 254) / 256)), dim3(256), 0, st, cs, n,
+                       fits ? kOpen : kAlone);
+    if (fits)
+      hipLaunchKernelGGL(resident, dim3((unsigned)J), dim3(threads), 0, st, A, lda, (int)n,
+                         (int)nb, cs, gather_ticks, hh, tau);
+    // (returns at once where the resident form ran) a sweep lags two steps
+    // behind the one before it, so at most about J / 2 are under way; the
+    // tickets make any number of workgroups correct
     const unsigned wgs = (unsigned)std::min<int64_t>({n - 1, J / 2 + 2, 512});
     if (nb > 32)
       hipLaunchKernelGGL((k_chase_sweeps<E, 8>), dim3(wgs), dim3(512), 0, st, A, lda, n, nb, cs,
@@ -628,8 +1037,8 @@ int run_sweeps(int64_t n, int64_t nb, E* A, int64_t lda, double* d, double* e, E
 
 template <typename E>
 int run(int64_t n, int64_t nb, E* A, int64_t lda, double* d, double* e, E* hh, E* tau,
-        hipStream_t st) {
-  if (nb <= 64) return run_sweeps<E>(n, nb, A, lda, d, e, hh, tau, st);
+        hipStream_t st, int64_t gather_ticks) {
+  if (nb <= 64) return run_sweeps<E>(n, nb, A, lda, d, e, hh, tau, st, gather_ticks);
   // launches t = 0 .. T-1 with T = max_s (3 s + J(s)); the active sweeps of
   // launch t are s_lo(t) .. min(t / kLag, n - 2), s_lo the least s with
   // 3 s + J(s) > t (3 s + J(s) increases with s)
@@ -653,9 +1062,11 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 }  // namespace eb2t
 
-extern "C" int elpa_band_to_tridiag(int64_t n, int64_t nbw, void* A, int64_t lda, double* d,
-                                    double* e, void* hh, void* tau, int32_t dtype,
-                                    void* stream) {
+// (for tests: gather_ticks, of the 100 MHz clock, is how long the resident
+// form's workgroups wait for each other; negative: that form is not tried)
+extern "C" int elpa_band_to_tridiag_gather(int64_t n, int64_t nbw, void* A, int64_t lda,
+                                           double* d, double* e, void* hh, void* tau,
+                                           int32_t dtype, void* stream, int64_t gather_ticks) {
   if (dtype != ELPA_R64 && dtype != ELPA_C64) return ELPA_ERR_DTYPE;
   if (n < 1 || nbw < 1 || nbw > eb2t::kMaxNb || lda < n) return ELPA_ERR_ARG;
   if (!A || !d || (n > 1 && (!e || !hh || !tau))) return ELPA_ERR_ARG;
@@ -665,7 +1076,15 @@ extern "C" int elpa_band_to_tridiag(int64_t n, int64_t nbw, void* A, int64_t lda
     return ELPA_ERR_ALIGN;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (dtype == ELPA_R64)
-    return eb2t::run<double>(n, nbw, (double*)A, lda, d, e, (double*)hh, (double*)tau, st);
+    return eb2t::run<double>(n, nbw, (double*)A, lda, d, e, (double*)hh, (double*)tau, st,
+                             gather_ticks);
   return eb2t::run<ehh::z64>(n, nbw, (ehh::z64*)A, lda, d, e, (ehh::z64*)hh, (ehh::z64*)tau,
-                             st);
+                             st, gather_ticks);
+}
+
+extern "C" int elpa_band_to_tridiag(int64_t n, int64_t nbw, void* A, int64_t lda, double* d,
+                                    double* e, void* hh, void* tau, int32_t dtype,
+                                    void* stream) {
+  return elpa_band_to_tridiag_gather(n, nbw, A, lda, d, e, hh, tau, dtype, stream,
+                                     eb2t::kGatherTicks);
 }

@@ -172,3 +172,59 @@ def test_b2t_one_launch_sizes(torch_dev, n, b, cplx):
     assert np.max(np.abs(d - d0)) <= 1e-12 * scale * n ** 0.5
     assert np.max(np.abs(e - e0)) <= 1e-12 * scale * n ** 0.5
     assert rel(hh, hh0) <= 1e-10 and rel(tau, tau0) <= 1e-10
+
+
+def b2t_with_gather(torch, dev, B, b, ticks):
+    """elpa_band_to_tridiag with the time the resident form's workgroups have
+    to come together (negative: the workgroups follow the sweeps)."""
+    import ctypes as C
+
+    import paper_1811_01277_amd as P
+    n = B.shape[0]
+    a = torch.from_numpy(np.ascontiguousarray(B.T)).to(dev).t()
+    R = P.num_reflectors(n, b)
+    d = torch.empty(n, dtype=torch.float64, device=dev)
+    e = torch.empty(n - 1, dtype=torch.float64, device=dev)
+    hh = torch.empty(R * b, dtype=a.dtype, device=dev)
+    tau = torch.empty(R, dtype=a.dtype, device=dev)
+    fn = P.library().elpa_band_to_tridiag_gather
+    fn.argtypes = [C.c_int64, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p,
+                   C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_int64]
+    fn.restype = C.c_int
+    rc = fn(n, b, a.data_ptr(), n, d.data_ptr(), e.data_ptr(), hh.data_ptr(), tau.data_ptr(),
+            P.C64 if a.is_complex() else P.R64, None, ticks)
+    assert rc == 0, rc
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in (a, d, e, hh, tau)]
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("n,b", [(2, 1), (3, 2), (30, 1), (66, 33), (65, 64), (66, 64), (129, 64),
+                                 (130, 64), (200, 48), (193, 32), (257, 31), (90, 7)])
+def test_b2t_resident_and_moving(torch_dev, n, b, cplx):
+    """Workgroups that stay at their chase positions and workgroups that follow
+    the sweeps: one position and many, last steps of length 1 and full, bands
+    that do not fill the waves.  Same reflectors, and the matrix left behind
+    holds the tridiagonal result and zeros."""
+    torch, dev = torch_dev
+    B = band_matrix(n, b, cplx, 480 + n)
+    # B = Q T Q^H with Q the reflectors' product, to 50 n eps |B|: the entries
+    # themselves can lose digits without bound (n = 65 with this seed: 5e-11)
+    tol = 50 * n * np.finfo(float).eps * np.linalg.norm(B, 2)
+    got = []
+    for ticks in (10 ** 7, -1):
+        print(f"b2t n={n} b={b} cplx={cplx} ticks={ticks}", flush=True)
+        a, d, e, hh, tau = b2t_with_gather(torch, dev, B, b, ticks)
+        got.append((d, e, hh, tau))
+        T = np.diag(d) + np.diag(e, -1) + np.diag(e, 1)
+        Q = bt.bt_tridiag_to_band(hh, tau, np.asfortranarray(np.eye(n, dtype=B.dtype)), n, b)
+        assert np.max(np.abs(B @ Q - Q @ T)) <= tol
+        assert np.max(np.abs(Q.conj().T @ Q - np.eye(n))) <= 50 * n * np.finfo(float).eps
+        if cplx:   # the input's diagonal is real to rounding only
+            assert np.max(np.abs(np.diag(a).imag)) <= tol
+            np.fill_diagonal(a, np.diag(a).real)
+        assert np.array_equal(a, T)
+    # the sums run in the same order where the waves divide the band (complex
+    # products may be contracted differently in the two kernels)
+    if not cplx and b % (8 if b > 32 else 4) == 0:
+        assert all(np.array_equal(x, y) for x, y in zip(*got))
