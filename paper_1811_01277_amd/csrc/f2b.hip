@@ -18,7 +18,8 @@
 // M = I + diag(tau) striu(V^H V), in the symmetric two-sided form:
 //   X = A22 V T,  Y = T^H (V^H X),  W = X - V Y / 2,
 //   Q^H A22 Q = A22 - V W^H - W V^H   (one product with inner dimension 2k),
-// as GEMMs and triangular solves on the matrix cores (rocBLAS).
+// as GEMMs and triangular solves on the matrix cores (rocBLAS); with up to 64
+// reflectors T and Y come from one small kernel instead (k_small_factors).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -269,6 +270,7 @@ __global__ __launch_bounds__(kRows) void k_update(E* __restrict__ A, int64_t lda
 // n = 4000 (nbw = 64, fp64).
 // ---------------------------------------------------------------------------
 constexpr int kOpen = 0, kGo = 1, kAlone = 2;
+constexpr int64_t kSmall = 64;  // reflectors of k_small_factors
 constexpr int kMaxGroups = 256;                       // one per compute unit
 constexpr int64_t kGatherTicks = 10000000;            // 0.1 s of the 100 MHz clock
 constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // never reached once all are resident
@@ -712,6 +714,244 @@ __global__ __launch_bounds__(256, 1) void k_panel_alone(Panel<E> P) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// trailing update, up to 64 reflectors
+// ---------------------------------------------------------------------------
+// B = [V | W | V | Z] (m rows, ld mp, k columns each; rows m .. mp of the last
+// two zero), Z = A22 V, GS = V^H [V | Z].  Then T from the first half of GS, Y =
+// T^H (V^H Z) T and W = [V | Z] [-Y / 2; T] = A22 V T - V Y / 2, and A22 takes
+// one product of the first half of B with its middle.  Four products, where
+// the general order (below) has five, two triangular solves (each an inversion
+// of diagonal blocks in launches of its own), two scalings and three copies: at
+// n = 4000, nbw = 64 an update took 245 us on average with those and takes 108
+// (all of f2b: 27.9 -> 19.4 ms; n = 1000: 4.6 -> 3.4; complex, n = 700, nbw = 32:
+// 6.6 -> 3.7).
+
+// The panel mirrored into the rows above, V into both its places, zeros.
+template <typename E>
+__global__ __launch_bounds__(256) void k_panel_out(E* __restrict__ A, int64_t lda, int64_t r0,
+                                                   int64_t p, int64_t m, int64_t k, int64_t mp,
+                                                   const E* __restrict__ V, int64_t ldv,
+                                                   E* __restrict__ B) {
+  const int64_t j = blockIdx.y;
+  for (int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; row < mp;
+       row += (int64_t)gridDim.x * blockDim.x) {
+    if (row < m) A[p + j + (r0 + row) * lda] = conj_(A[r0 + row + (p + j) * lda]);
+    if (j < k) {
+      const E v = row < m ? V[r0 + row + (p + j) * ldv] : from_re<E>(0.0);
+      B[row + j * mp] = v;
+      B[row + (2 * k + j) * mp] = v;
+      if (row >= m) B[row + (3 * k + j) * mp] = v;
+    }
+  }
+}
+
+// K chunks of Z = A22 V: its m / 64 output tiles fill a quarter of the device at
+// m = 4000 (144 us in one product, 40 in eight chunks); at most 8, of 128
+// columns or more, and about 512 tiles in all.
+inline int64_t zsplit(int64_t m) {
+  return std::max<int64_t>(1, std::min<int64_t>({8, m / 128, 512 / ((m + 63) / 64)}));
+}
+
+// Z = the sum of `chunks` partial products of kc columns of A22 each (m x k, in
+// a fixed order) and the columns of A22 past them (fewer than chunks)
+template <typename E>
+__global__ __launch_bounds__(256) void k_sum_z(const E* __restrict__ part, int64_t chunks,
+                                               int64_t kc, const E* __restrict__ A22, int64_t lda,
+                                               const E* __restrict__ V, int64_t m, int64_t k,
+                                               int64_t mp, E* __restrict__ Z) {
+  const int64_t c = blockIdx.y;
+  for (int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; row < m;
+       row += (int64_t)gridDim.x * blockDim.x) {
+    E acc = part[row + c * m];
+    for (int64_t s = 1; s < chunks; ++s) acc = Num<E>::add(acc, part[s * m * k + row + c * m]);
+    for (int64_t l = chunks * kc; l < m; ++l)
+      acc = Num<E>::add(acc, Num<E>::mul(A22[row + l * lda], V[l + c * mp]));
+    Z[row + c * mp] = acc;
+  }
+}
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+template <typename E>
+struct Planes {
+  static constexpr int PL = std::is_same<E, double>::value ? 1 : 2;
+};
+__device__ __forceinline__ void split(double x, double* re, double*) { *re = x; }
+__device__ __forceinline__ void split(zc x, double* re, double* im) {
+  *re = x.re;
+  *im = x.im;
+}
+__device__ __forceinline__ double join(const double (&x)[1]) { return x[0]; }
+__device__ __forceinline__ zc join(const double (&x)[2]) { return zc{x[0], x[1]}; }
+
+// C (2 k x k) = [-Y / 2; T] for k <= 64, one workgroup.  T by halves: the
+// diagonal blocks of 16 by the forward recurrence, T_ii = tau_i, T[0:i, i] =
+// -tau_i T[0:i, 0:i] G[0:i, i], a lane to a row; a block beside two of them as
+// -T1 (G12 T2), and the two products of Y, on the matrix cores.  An MFMA result
+// is the second operand of the next product as it lies in its registers (row q
+// + 4 r of lane quad q, register r).  Planes of complex values apart.
+// Bound: a chain of dependent products and LDS reads on one compute unit, 13 us
+// (real); with the products in plain loops 29.
+template <typename E>
+__global__ __launch_bounds__(256) void k_small_factors(const E* __restrict__ GS,
+                                                       const E* __restrict__ tau, int k,
+                                                       E* __restrict__ C) {
+  constexpr int PL = Planes<E>::PL, N = 64, LD = N + 1, I = PL - 1;
+  __shared__ double G[PL][N * LD], T[PL][N * LD];
+  const int tid = (int)threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  E g[16], s[16];  // entries lane of columns wave, wave + 4, ...
+#pragma unroll
+  for (int x = 0; x < 16; ++x) {
+    const int c = wave + 4 * x;
+    const bool ok = lane < k && c < k;
+    g[x] = ok ? GS[lane + (int64_t)c * k] : from_re<E>(0.0);
+    s[x] = ok ? GS[lane + (int64_t)(k + c) * k] : from_re<E>(0.0);
+  }
+  E tk = lane < k ? tau[lane] : from_re<E>(0.0);
+  auto put = [&](const E (&v)[16]) {
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      double y[2];
+      split(v[x], &y[0], &y[1]);
+#pragma unroll
+      for (int p = 0; p < PL; ++p) G[p][lane * LD + wave + 4 * x] = y[p];
+    }
+  };
+  put(g);
+#pragma unroll
+  for (int p = 0; p < PL; ++p)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) T[p][lane * LD + wave + 4 * x] = 0.0;
+  __syncthreads();
+  if (wave == 0) {  // row lane of its diagonal block
+    double t[PL][16], ty[2];
+    split(tk, &ty[0], &ty[1]);
+    const int o = lane & ~15;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      double a[2] = {0.0, 0.0};
+#pragma unroll
+      for (int l = 0; l < i; ++l) {
+        const double gr = G[0][(o + l) * LD + o + i];
+        if constexpr (PL == 1) {
+          a[0] += t[0][l] * gr;
+        } else {
+          const double gi = G[I][(o + l) * LD + o + i];
+          a[0] += t[0][l] * gr - t[I][l] * gi;
+          a[1] += t[0][l] * gi + t[I][l] * gr;
+        }
+      }
+      const double tr = __shfl(ty[0], o + i, 64);
+      if constexpr (PL == 1) {
+        t[0][i] = i == c16 ? tr : (i > c16 ? -(tr * a[0]) : 0.0);
+      } else {
+        const double ti = __shfl(ty[1], o + i, 64);
+        t[0][i] = i == c16 ? tr : (i > c16 ? -(tr * a[0] - ti * a[1]) : 0.0);
+        t[I][i] = i == c16 ? ti : (i > c16 ? -(tr * a[1] + ti * a[0]) : 0.0);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) T[p][lane * LD + o + i] = t[p][i];
+  }
+  __syncthreads();
+  // acc (tile, per plane) += (ar + i ai) (br + i bi)
+  auto mac = [&](double ar, double ai, double br, double bi, d4 (&acc)[PL]) {
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, acc[0], 0, 0, 0);
+    if constexpr (PL == 2) {
+      acc[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acc[I], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, acc[0], 0, 0, 0);
+      acc[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acc[I], 0, 0, 0);
+    }
+  };
+  // T12 = -T1 (G12 T2) of the S-wide blocks at o, o + S; this wave its columns
+  // 16 cs ..
+  auto beside = [&](auto tiles, int o, int cs) {
+    constexpr int NT = decltype(tiles)::value, S = 16 * NT;
+    d4 x[NT][PL], y[NT][PL];
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+      for (int p = 0; p < PL; ++p) x[rt][p] = y[rt][p] = d4{0, 0, 0, 0};
+    const int col = o + S + 16 * cs + c16;
+#pragma unroll
+    for (int kk = 0; kk < 4 * NT; ++kk) {
+      const int l = o + S + 4 * kk + q;
+      const double br = T[0][l * LD + col], bi = T[I][l * LD + col];
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) {
+        const int at = (o + 16 * rt + c16) * LD + l;
+        mac(G[0][at], G[I][at], br, bi, x[rt]);
+      }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4 * NT; ++kk) {
+      const int l = o + 4 * kk + q;
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) {
+        const int at = (o + 16 * rt + c16) * LD + l;
+        mac(T[0][at], T[I][at], x[kk / 4][0][kk % 4], x[kk / 4][I][kk % 4], y[rt]);
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+      for (int p = 0; p < PL; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T[p][(o + 16 * rt + q + 4 * r) * LD + col] = -y[rt][p][r];
+  };
+  if (wave < 2) beside(std::integral_constant<int, 1>{}, 32 * wave, 0);
+  __syncthreads();
+  if (wave < 2) beside(std::integral_constant<int, 2>{}, 0, wave);
+  __syncthreads();
+  put(s);
+  __syncthreads();
+  // this wave's 16 columns of U = S T, then of Y = T^H U
+  d4 u[4][PL], y[4][PL];
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int p = 0; p < PL; ++p) u[rt][p] = y[rt][p] = d4{0, 0, 0, 0};
+  const int col = 16 * wave + c16;
+#pragma unroll 4
+  for (int kk = 0; kk < 16; ++kk) {
+    const int l = 4 * kk + q;
+    const double br = T[0][l * LD + col], bi = T[I][l * LD + col];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) {
+      const int at = (16 * rt + c16) * LD + l;
+      mac(G[0][at], G[I][at], br, bi, u[rt]);
+    }
+  }
+#pragma unroll
+  for (int kk = 0; kk < 16; ++kk) {
+    const int l = 4 * kk + q;
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) {
+      if (kk / 4 > rt) continue;  // T is upper triangular
+      const int at = l * LD + 16 * rt + c16;
+      mac(T[0][at], -T[I][at], u[kk / 4][0][kk % 4], u[kk / 4][I][kk % 4], y[rt]);
+    }
+  }
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * rt + q + 4 * r;
+      if (i >= k || col >= k) continue;
+      double a[PL], t[PL];
+#pragma unroll
+      for (int p = 0; p < PL; ++p) {
+        a[p] = -0.5 * y[rt][p][r];
+        t[p] = T[p][i * LD + col];
+      }
+      C[i + (int64_t)col * 2 * k] = join(a);
+      C[k + i + (int64_t)col * 2 * k] = join(t);
+    }
+}
+
 // A[p+j, r0+row] = conj(A[r0+row, p+j]) for the panel
 template <typename E>
 __global__ __launch_bounds__(256) void k_mirror(E* __restrict__ A, int64_t lda, int64_t r0,
@@ -748,12 +988,17 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
   for (int64_t p = 0; p + b < n; p += b) {
     const int64_t m = n - p - b, k = std::min(b, m);
     part_e = std::max(part_e, (size_t)ebt::ksplit(m, k, k, es) * k * k);
+    if (b <= kSmall) part_e = std::max(part_e, (size_t)ebt::ksplit(m, k, 2 * k, es) * 2 * k * k);
+    if (b <= kSmall && zsplit(m) > 1) part_e = std::max(part_e, (size_t)zsplit(m) * m * k);
   }
+  // (the padded rows of a small update: fewer than its chunks, at most 768)
+  const int64_t wrows = b <= kSmall ? mmax + 768 : mmax;
   const size_t off_pn = 0, off_pd = off_pn + al(2 * Gmax * sizeof(double) + 512),
-               off_g = off_pd + al((size_t)Gmax * b * es), off_m = off_g + al((size_t)b * b * es),
-               off_w1 = off_m + al((size_t)b * b * es),
-               off_w2 = off_w1 + al((size_t)2 * b * mmax * es),
-               off_part = off_w2 + al((size_t)2 * mmax * b * es), off_slot = off_part + al(part_e * es);
+               off_g = off_pd + al((size_t)Gmax * b * es),
+               off_m = off_g + al((size_t)2 * b * b * es),
+               off_w1 = off_m + al((size_t)2 * b * b * es),
+               off_w2 = off_w1 + al((size_t)2 * b * wrows * es),
+               off_part = off_w2 + al((size_t)2 * b * wrows * es), off_slot = off_part + al(part_e * es);
   // one-launch panels: their exchange slots and per-panel states
   constexpr int ROWS = PanelTraits<E>::ROWS, NWORD = PanelTraits<E>::NWORD;
   const int64_t groups = b <= 64 ? std::min<int64_t>((mmax + ROWS - 1) / ROWS, kMaxGroups) : 0;
@@ -815,13 +1060,51 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
           std::swap(pa, pb);
         }
       }
-      hipLaunchKernelGGL(k_mirror<E>, dim3((unsigned)std::min<int64_t>((m + 255) / 256, 1024),
-                                           (unsigned)b),
-                         dim3(256), 0, st, A, lda, r0, p, m, b);
       // trailing update with the panel's k reflectors
       const E* Vp = V + r0 + p * ldv;
       E* A22 = A + r0 + r0 * lda;
       const E* tp = tau + p;
+      if (b <= kSmall) {
+        const int64_t chunks = ebt::ksplit(m, k, 2 * k, es), kc = (m + chunks - 1) / chunks;
+        const int64_t mp = kc * chunks;
+        E* VZ = W1 + 2 * k * mp;
+        hipLaunchKernelGGL(k_panel_out<E>,
+                           dim3((unsigned)std::min<int64_t>((mp + 255) / 256, 1024), (unsigned)b),
+                           dim3(256), 0, st, A, lda, r0, p, m, k, mp, V, ldv, W1);
+        E* Z = VZ + k * mp;
+        const int64_t zc_ = zsplit(m), zk = m / zc_;
+        bool ok;
+        if (zc_ == 1) {
+          ok = Blas<E>::gemm(h, N_, N_, m, k, m, S(1), A22, lda, VZ, mp, S(0), Z, mp) ==
+               rocblas_status_success;
+        } else {
+          ok = Blas<E>::gemm_sb(h, N_, N_, m, k, zk, S(1), A22, lda, zk * lda, VZ, mp, zk, S(0),
+                                part, m, m * k, zc_) == rocblas_status_success;
+          if (ok)
+            hipLaunchKernelGGL(k_sum_z<E>, dim3((unsigned)((m + 255) / 256), (unsigned)k),
+                               dim3(256), 0, st, (const E*)part, zc_, zk, (const E*)A22, lda,
+                               (const E*)VZ, m, k, mp, Z);
+        }
+        ok = ok && Blas<E>::gemm_sb(h, C_, N_, k, 2 * k, kc, S(1), VZ, mp, kc, VZ, mp, kc, S(0),
+                                    part, k, 2 * k * k, chunks) == rocblas_status_success;
+        if (ok) {
+          hipLaunchKernelGGL(ebt::k_sum_parts<E>, dim3((unsigned)((2 * k * k + 255) / 256)),
+                             dim3(256), 0, st, (const E*)part, chunks, 2 * k * k,
+                             (const E*)nullptr, k, Gm);
+          hipLaunchKernelGGL(k_small_factors<E>, dim3(1), dim3(256), 0, st, (const E*)Gm, tp,
+                             (int)k, M);
+        }
+        ok = ok && Blas<E>::gemm(h, N_, N_, m, k, 2 * k, S(1), VZ, mp, M, 2 * k, S(0), W1 + k * mp,
+                                 mp) == rocblas_status_success;
+        // A22 -= [V W] [W V]^H: one rank-2k product over both triangles
+        ok = ok && Blas<E>::gemm(h, N_, C_, m, m, 2 * k, S(-1), W1, mp, W1 + k * mp, mp, S(1),
+                                 A22, lda) == rocblas_status_success;
+        if (!ok || hipGetLastError() != hipSuccess) rc = ELPA_ERR_DEVICE;
+        continue;
+      }
+      hipLaunchKernelGGL(k_mirror<E>, dim3((unsigned)std::min<int64_t>((m + 255) / 256, 1024),
+                                           (unsigned)b),
+                         dim3(256), 0, st, A, lda, r0, p, m, b);
       bool ok = ebt::gemm_adj_splitk<E, S>(h, k, k, m, Vp, ldv, Vp, ldv,
                                            ebt::ksplit(m, k, k, es), part, nullptr, Gm, st);
       if (ok)
