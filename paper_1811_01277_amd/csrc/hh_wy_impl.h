@@ -204,32 +204,38 @@ __device__ __forceinline__ void wy_prep_group(const E* __restrict__ hh, const E*
     }
     Gr[a][b] = gr;
     Gi[a][b] = gi;
-    Tr[a][b] = 0.0;
-    Ti[a][b] = 0.0;
   }
   __syncthreads();
   // forward recurrence, column i: T[0:i, i] = -tau_i T[0:i, 0:i] G[0:i, i].
   // Entry (a, i) needs only row a of T (T[a][l] = 0 for l < a), so lane a
-  // computes its whole row in column order, with no barrier in between.
+  // computes its whole row in column order, in registers, with no barrier in
+  // between.
   if (tid < 16) {
-    Tr[tid][tid] = tr_[tid];
-    Ti[tid][tid] = ti_[tid];
-    for (int i = tid + 1; i < 16; ++i) {
+    double t[16], u[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
       double ar = 0.0, ai = 0.0;
-      for (int l = tid; l < i; ++l) {
+#pragma unroll
+      for (int l = 0; l < i; ++l) {
         if constexpr (CPLX) {
-          ar += Tr[tid][l] * Gr[l][i] - Ti[tid][l] * Gi[l][i];
-          ai += Tr[tid][l] * Gi[l][i] + Ti[tid][l] * Gr[l][i];
+          ar += t[l] * Gr[l][i] - u[l] * Gi[l][i];
+          ai += t[l] * Gi[l][i] + u[l] * Gr[l][i];
         } else {
-          ar += Tr[tid][l] * Gr[l][i];
+          ar += t[l] * Gr[l][i];
         }
       }
       if constexpr (CPLX) {
-        Tr[tid][i] = -(tr_[i] * ar - ti_[i] * ai);
-        Ti[tid][i] = -(tr_[i] * ai + ti_[i] * ar);
+        t[i] = i == tid ? tr_[i] : (i > tid ? -(tr_[i] * ar - ti_[i] * ai) : 0.0);
+        u[i] = i == tid ? ti_[i] : (i > tid ? -(tr_[i] * ai + ti_[i] * ar) : 0.0);
       } else {
-        Tr[tid][i] = -(tr_[i] * ar);
+        t[i] = i == tid ? tr_[i] : (i > tid ? -(tr_[i] * ar) : 0.0);
+        u[i] = 0.0;
       }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      Tr[tid][i] = t[i];
+      Ti[tid][i] = u[i];
     }
   }
   __syncthreads();
