@@ -37,7 +37,8 @@ def parse():
     ap.add_argument("--nev", type=int, default=20000)
     ap.add_argument("--dtype", default="r64", choices=["r64", "r32", "c64"])
     ap.add_argument("--path", type=int, default=0,
-                    help="0 auto, 1 reference, 2 one-lane stripe, 3 two-lane stripe, 4 compact WY")
+                    help="0 auto, 1 reference, 2 one-lane stripe, 3 split (fp64: compact WY with "
+                         "the reflectors in place, else two-lane stripe), 4 compact WY")
     ap.add_argument("--k", type=int, default=0, help="sweeps fused per pass (0 = auto)")
     ap.add_argument("--tile-steps", type=int, default=0,
                     help="chase steps per tile of the launch schedule (0 = auto)")
@@ -849,12 +850,15 @@ def main():
     in_flight = prof["sum_launch_ms"] / prof["kernel_ms"]
     achieved = (flops / launches) / (avg_launch_ms * 1e-3) * in_flight / 1e12
     peak = PEAK_TFLOPS[dt]
-    kname = {1: "k_ref", 2: "k_diag", 3: "k_split", 4: "k_wy"}.get(prof["path"], "?")
-    # the compact-WY kernel runs on the matrix cores and executes (nbw+16)/nbw
-    # times the counted flops (its sub-groups' parallelograms padded to whole
-    # 16-row tiles); the VALU kernels execute the counted flops
-    mfma = prof["path"] == 4
-    executed = achieved * ((nbw + 16) / nbw if mfma else 1.0)
+    direct = prof["path"] == 3 and dt == "r64"
+    kname = {1: "k_ref", 2: "k_diag", 3: "k_wyd" if direct else "k_split",
+             4: "k_wy"}.get(prof["path"], "?")
+    # the compact-WY kernels run on the matrix cores and execute (nbw+16)/nbw
+    # times the counted flops (their sub-groups' parallelograms padded to whole
+    # 16-row tiles; path 3 applies T by itself, 8 more rows' worth); the VALU
+    # kernels execute the counted flops
+    mfma = prof["path"] == 4 or direct
+    executed = achieved * ((nbw + (24 if direct else 16)) / nbw if mfma else 1.0)
     traffic = recorded_traffic({"n": n, "nbw": nbw, "nev": nev, "dtype": dt, "path": prof["path"],
                                 "k": prof["k"], "tile_steps": prof["steps"],
                                 "streams": prof["streams"]})

@@ -143,7 +143,7 @@ typedef struct {
     int32_t batch;
 } elpa_hh_plan;
 
-/* schedule of a batched call's two-lane group (elpa_hh_plan.batch) */
+/* schedule of a batched call's ELPA_PATH_SPLIT group (elpa_hh_plan.batch) */
 enum {
     ELPA_BATCH_AUTO = 0,       /* the one with the smaller modelled time (see
                                   elpa_hh_trafo_batched) */
@@ -199,7 +199,7 @@ typedef struct {
  * Batched back-transformation: the same operation for every problem in
  * probs[0..count) (host array, read before the call returns), asynchronous on
  * `stream`.  Problems may differ in n, nev and ldq.  Problems that share
- * (dtype, nbw) and run the two-lane stripe kernel (ELPA_PATH_SPLIT, the
+ * (dtype, nbw) and run the stripe kernel of ELPA_PATH_SPLIT (the
  * default where one is compiled) run as one group, in one of two schedules:
  *   - ONE kernel launch: every workgroup carries one stripe (32 columns, fp64:
  *     16) of one problem through all of that problem's reflectors (sweep
@@ -232,11 +232,11 @@ int elpa_hh_trafo_batched(const elpa_hh_problem *probs, int64_t count, void *str
  * Allocation-free variant of elpa_hh_trafo, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid allocation).  Same operation, arguments, layouts and validation
- * as elpa_hh_trafo.  The two-lane stripe kernel (the library default, nbw 32
+ * as elpa_hh_trafo.  ELPA_PATH_SPLIT's kernel (the library default, nbw 32
  * or 64) runs entirely on the caller's stream with its workspace (the
  * stripe-major copy of Q and the packed reflectors) in a fixed device array of
  * ELPA_HH_NOALLOC_SCRATCH_BYTES per device, which the library holds from load
- * until the process ends; nbw without a two-lane kernel runs the reference
+ * until the process ends; nbw without such a kernel runs the reference
  * kernel, which needs no workspace.  No device memory is allocated or freed
  * and no tuned plan is consulted (the library's default k for (dtype, nbw);
  * 1 stripe group).
@@ -263,7 +263,7 @@ int elpa_hh_trafo_noalloc(int64_t n, int64_t nev, int64_t nbw, const void *hh,
  *
  * elpa_hh_batch_create: validates the problems and plan exactly as
  *   elpa_hh_trafo_batched (same codes; a group whose kernel family has no
- *   prepared form, i.e. other than the two-lane kernel, gives ELPA_ERR_PLAN),
+ *   prepared form, i.e. other than ELPA_PATH_SPLIT's, gives ELPA_ERR_PLAN),
  *   builds the same schedules, allocates the device workspace and tables on
  *   the current device (hipMalloc; ELPA_ERR_NOMEM if it cannot) and copies the
  *   tables there before returning (synchronous).  A batch in which exactly
@@ -399,7 +399,7 @@ int elpa_hh_tune(int64_t n, int64_t nev, int64_t nbw, const void *hh, const void
 
 /*
  * Batch tuner: times uniform plans (one plan for every problem, among those
- * that every problem of the batch can run in a batched call; for the two-lane
+ * that every problem of the batch can run in a batched call; for the ELPA_PATH_SPLIT
  * family both batched schedules, ELPA_BATCH_ONE_LAUNCH and
  * ELPA_BATCH_DIAGONAL) on scratch
  * copies of the problems' Q (the Q buffers are not modified; the call

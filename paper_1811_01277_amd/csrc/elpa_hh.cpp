@@ -82,18 +82,19 @@ int default_k(int path, int32_t dtype, int64_t nb, bool batched) {
 // 77.3 at 96; at n = 4000: 36.9 against 39.2);
 // 0 = path SPLIT (fp64 below n = 3000, complex at nbw = 32,
 // other nbw, batched calls).  fp64 with fewer than 1024 columns
-// also takes the two-lane kernel:
+// also takes path SPLIT:
 // the compact-WY kernel's T-build, which does not shrink with nev, is then a
-// large part of the call (n = 8192, nev = 819: 6.7 ms two-lane, 7.9 ms WY;
+// large part of the call (n = 8192, nev = 819: 4.2 ms, 4.8 ms WY;
 // nev = 2000 at n = 20000 is faster on WY).  nev = 0: not known, taken as
 // large.
 int auto_wy_k(int32_t dtype, int64_t nb, int64_t n, int64_t nev) {
   // nbw = 32, real: the compact-WY kernel from n = 2000 despite its 1.5x
-  // executed flops there (fp64, n = 2000 / 4000 / 6000 / 12000: 8.0 / 21.7 /
-  // 29.2 / 34.3 TFLOP/s against 6.1 / 17.1 / 25.1 / 31.7 for the two-lane
-  // kernel; fp32 at n = 2000 / 6000 / 12000: 10.6 / 44.3 / 54.4 against 7.3 /
-  // 36.8 / 52.6); complex keeps the two-lane kernel (n = 6000: 37.5 against
-  // 31.4 for WY k = 32)
+  // executed flops there (in diagonal launches, fp64, n = 2000 / 4000 / 6000 /
+  // 12000: 8.0 / 21.7 / 29.2 / 34.3 TFLOP/s against 6.1 / 17.1 / 25.1 / 31.7 for
+  // the two-lane kernel; fp32 at n = 2000 / 6000 / 12000: 10.6 / 44.3 / 54.4
+  // against 7.3 / 36.8 / 52.6; in one launch, fp64 at n = 2000: 835 us against
+  // 843 of path SPLIT); complex keeps the two-lane kernel (n = 6000: 37.5
+  // against 31.4 for WY k = 32)
   if (nb == 32)
     return ((dtype == ELPA_R64 || dtype == ELPA_R32) && n >= 2000 &&
             (nev == 0 || nev >= 1024))
@@ -110,7 +111,7 @@ int auto_wy_k(int32_t dtype, int64_t nb, int64_t n, int64_t nev) {
 // choice).  Returns the table entry, or nullptr with *path = ELPA_PATH_REF for
 // the reference kernel; *rc = ELPA_ERR_PLAN if an explicit plan cannot run.
 // batched: the kernel must have a batched form, and the library choice
-// prefers the two-lane kernel (its one-launch batched schedule).
+// prefers path SPLIT (its one-launch batched schedule).
 const ehh::StripeEntry* resolve(int32_t dtype, int64_t nb, const elpa_hh_plan* plan, int* path,
                                 int* rc, bool batched = false, int64_t n = 0, int64_t nev = 0) {
   *rc = ELPA_OK;
@@ -146,7 +147,7 @@ const ehh::StripeEntry* resolve(int32_t dtype, int64_t nb, const elpa_hh_plan* p
           return e;
         }
       }
-      // the two-lane VALU kernel where one is compiled (fp64, fp32 and
+      // path SPLIT where a kernel of it is compiled (fp64, fp32 and
       // complex), then for fp32 the compact-WY MFMA path, then the one-lane
       // kernel
       const int order32[] = {ELPA_PATH_SPLIT, ELPA_PATH_WY, ELPA_PATH_STRIPE};
@@ -555,7 +556,7 @@ int elpa_hh_trafo_noalloc(int64_t n, int64_t nev, int64_t nbw, const void* hh, c
   if (rc != ELPA_OK) return rc;
   if (n <= 1 || nev == 0) return ELPA_OK;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // the library's default two-lane kernel, one stripe group on the caller's
+  // the library's default kernel of path SPLIT, one stripe group on the caller's
   // stream; no tuner lookup (a tuned plan may name a family without a
   // caller-workspace form)
   const elpa_hh_plan split{ELPA_PATH_SPLIT, 0, 0, 0, 1, 0};
@@ -567,7 +568,7 @@ int elpa_hh_trafo_noalloc(int64_t n, int64_t nev, int64_t nbw, const void* hh, c
   prof.on = false;
   hipError_t err;
   if (rc != ELPA_OK || !se || !se->with_ws) {
-    // no two-lane kernel for this nbw: the reference kernel works in place
+    // no kernel of that path for this nbw: the reference kernel works in place
     err = ehh::ref_launcher(dtype)(hh, tau, Q, ldq, n, nev, nbw, st);
   } else {
     void* ws = nullptr;

@@ -257,7 +257,7 @@ int elpa_hh_tune_batched(const elpa_hh_problem* probs, int64_t count, void* stre
     }
     for (int k : ks) {
       if (fam == ELPA_PATH_SPLIT) {
-        // the two-lane family's batched schedules: one launch, or the
+        // path SPLIT's batched schedules: one launch, or the
         // diagonal sequence at each tile height (one stream either way)
         const elpa_hh_plan one{fam, k, 0, 0, 1, ELPA_BATCH_ONE_LAUNCH};
         if (elpa_hh_workspace_bytes_batched(probs, count, &one) >= 0) cand.push_back(one);
