@@ -7,17 +7,16 @@
 //   H_c0 ... H_c0+w-1 = I - V T V^H
 // (V the m x w block of vectors from row c0+nbw down, unit lead on the
 // diagonal and zeros above it; T the upper triangular factor of the forward
-// accumulation).  T is never formed: its inverse is diag(1/tau) +
-// striu(V^H V), so
-//   T W = (I + diag(tau) striu(V^H V))^{-1} (diag(tau) W),
-// a row scaling and a unit upper triangular solve, with no division by tau
-// (tau = 0, an identity reflector, is fine).  The blocks are applied last
-// block first, each as
-//   G = V^H V,  W = V^H Q[c0+nbw:, :],  W <- T W,  Q[c0+nbw:, :] -= V W,
-// plain GEMMs and one triangular solve on the matrix cores through rocBLAS;
-// packing V (explicit zeros and unit lead, so the vectors may share storage
-// with anything above them), forming the unit triangle and scaling W are this
-// file's kernels.
+// accumulation, no division by tau: tau = 0, an identity reflector, is fine).
+// The factors depend on the vectors alone, so all blocks' G = V^H V come first,
+// then all T in two launches; then the blocks are applied, last block first, as
+//   W = V^H Q[c0+nbw:, :],  W <- T W,  Q[c0+nbw:, :] -= V W,
+// plain GEMMs on the matrix cores through rocBLAS.  Packing V (explicit zeros
+// and unit lead, so the vectors may share storage with anything above them) and
+// forming T are this file's kernels.  (A triangular solve per block in T's
+// place, a dozen dependent launches of its own, took 1.5 of 6.6 ms at n = 6000
+// with 3000 vectors, nbw = 64, fp64; the strips
+// take 54 us for all sixteen blocks and the call 5.6 ms.)
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
@@ -54,6 +53,144 @@ __global__ __launch_bounds__(256) void k_pack(const E* __restrict__ V, int64_t l
   }
 }
 
+// T's diagonal blocks of 64: workgroup (d, b) does block d of G_b, T_b (w x w,
+// column major); reflectors N in all, w per block.
+template <typename E>
+__global__ __launch_bounds__(256) void k_diag_factors(const E* __restrict__ Gall,
+                                                      const E* __restrict__ tau, int64_t N, int w,
+                                                      E* __restrict__ Tall) {
+  constexpr int PL = Planes<E>::PL, LD = 65;
+  __shared__ double G[PL][64 * LD], T[PL][64 * LD];
+  const int lane = (int)threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t b = blockIdx.y, left = N - b * w;
+  const int wb = (int)(left < w ? left : w), o = 64 * (int)blockIdx.x;
+  if (o >= wb) return;
+  const E* __restrict__ Gb = Gall + b * (int64_t)w * w;
+  E* __restrict__ Tb = Tall + b * (int64_t)w * w;
+#pragma unroll
+  for (int x = 0; x < 16; ++x) {
+    const int c = wave + 4 * x;
+    double g[2] = {0.0, 0.0};
+    if (o + lane < wb && o + c < wb) split(Gb[o + lane + (int64_t)(o + c) * wb], &g[0], &g[1]);
+#pragma unroll
+    for (int p = 0; p < PL; ++p) {
+      G[p][lane * LD + c] = g[p];
+      T[p][lane * LD + c] = 0.0;
+    }
+  }
+  double ty[2] = {0.0, 0.0};
+  if (o + lane < wb) split(tau[b * w + o + lane], &ty[0], &ty[1]);
+  __syncthreads();
+  tri_factor64<PL>(G, T, ty, wave, lane);
+#pragma unroll
+  for (int x = 0; x < 16; ++x) {
+    const int c = wave + 4 * x;
+    double t[PL];
+#pragma unroll
+    for (int p = 0; p < PL; ++p) t[p] = T[p][lane * LD + c];
+    if (o + lane < wb && o + c < wb) Tb[o + lane + (int64_t)(o + c) * wb] = join<E>(t);
+  }
+}
+
+// The rest of T: wave (s, b) does the columns 16 s .. of T_b, upwards from the
+// diagonal block j they lie in: T_ij = -T_ii sum_{i < l <= j} G_il T_lj, and the
+// zeros below.  The strip stays in LDS; G and T_ii come from memory, rows of a
+// tile together.  The columns of one block and all blocks run side by side:
+// the longest strip's chain of products, 64 per 64 x 64 x 16 block, bounds it,
+// with a product's operands all in flight before its first use (54 us for
+// sixteen blocks of 371 at n = 6000; 381 with four loads in flight).
+template <typename E>
+__global__ __launch_bounds__(64) void k_strip_factors(const E* __restrict__ Gall, int64_t N, int w,
+                                                      E* __restrict__ Tall) {
+  constexpr int PL = Planes<E>::PL, I = PL - 1;
+  extern __shared__ double strip[];  // [block][plane][64 rows][16 columns]
+  const int lane = (int)threadIdx.x, q = lane >> 4, c16 = lane & 15;
+  const int64_t b = blockIdx.y, left = N - b * w;
+  const int wb = (int)(left < w ? left : w), col = 16 * (int)blockIdx.x + c16;
+  if (16 * (int)blockIdx.x >= wb) return;
+  const int j = (int)blockIdx.x / 4;
+  const E* __restrict__ Gb = Gall + b * (int64_t)w * w;
+  E* __restrict__ Tb = Tall + b * (int64_t)w * w;
+  constexpr int KC = PL == 2 ? 8 : 16;  // k-steps loaded at a time
+  // (columns past the block meet zeros of the strip: any entry will do)
+  auto get = [&](const E* __restrict__ M, int r, int c) {
+    return M[r + (int64_t)(c < wb ? c : wb - 1) * wb];
+  };
+  auto at = [&](int l, int p, int row) { return ((l * PL + p) * 64 + row) * 16 + c16; };
+  for (int row = q; row < 64; row += 4) {
+    double t[2] = {0.0, 0.0};
+    if (64 * j + row < wb && col < wb) split(Tb[64 * j + row + (int64_t)col * wb], &t[0], &t[1]);
+#pragma unroll
+    for (int p = 0; p < PL; ++p) strip[at(j, p, row)] = t[p];
+  }
+  __builtin_amdgcn_wave_barrier();
+  for (int i = j - 1; i >= 0; --i) {
+    d4 x[4][PL], y[4][PL];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+      for (int p = 0; p < PL; ++p) x[rt][p] = y[rt][p] = d4{0, 0, 0, 0};
+    for (int l = i + 1; l <= j; ++l)
+#pragma unroll 1
+      for (int k0 = 0; k0 < 16; k0 += KC) {
+        E g[KC][4];
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk)
+#pragma unroll
+          for (int rt = 0; rt < 4; ++rt)
+            g[kk][rt] = get(Gb, 64 * i + 16 * rt + c16, 64 * l + 4 * (k0 + kk) + q);
+#pragma unroll
+        for (int kk = 0; kk < KC; ++kk) {
+          const double br = strip[at(l, 0, 4 * (k0 + kk) + q)];
+          const double bi = strip[at(l, I, 4 * (k0 + kk) + q)];
+#pragma unroll
+          for (int rt = 0; rt < 4; ++rt) {
+            double y2[2] = {0.0, 0.0};
+            split(g[kk][rt], &y2[0], &y2[1]);
+            mac(y2[0], y2[1], br, bi, x[rt]);
+          }
+        }
+      }
+#pragma unroll
+    for (int k0 = 0; k0 < 16; k0 += KC) {
+      E g[KC][4];
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk)
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt)
+          if ((k0 + kk) / 4 >= rt)  // T_ii is upper triangular
+            g[kk][rt] = get(Tb, 64 * i + 16 * rt + c16, 64 * i + 4 * (k0 + kk) + q);
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk)
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+          if ((k0 + kk) / 4 < rt) continue;
+          double y2[2] = {0.0, 0.0};
+          split(g[kk][rt], &y2[0], &y2[1]);
+          mac(y2[0], y2[1], x[(k0 + kk) / 4][0][kk % 4], x[(k0 + kk) / 4][I][kk % 4], y[rt]);
+        }
+    }
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * rt + q + 4 * r;
+        double v[PL];
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+          v[p] = -y[rt][p][r];
+          strip[at(i, p, row)] = v[p];
+        }
+        if (col < wb) Tb[64 * i + row + (int64_t)col * wb] = join<E>(v);
+      }
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (col < wb)
+    for (int row = 64 * (j + 1) + q; row < wb; row += 4)
+      Tb[row + (int64_t)col * wb] = Num<E>::zero();
+}
+
 int64_t default_block(int32_t dtype) { return dtype == ELPA_C64 ? 192 : 384; }
 
 struct Layout {
@@ -66,9 +203,10 @@ struct Layout {
     nev = nev_;
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     vp = al((size_t)mmax * w * es);
-    g = al((size_t)w * w * es);
-    t = al((size_t)w * w * es);
-    wbuf = al((size_t)w * nev * es);
+    const size_t blocks = (size_t)((N + w - 1) / w);
+    g = al(blocks * w * w * es);
+    t = g;
+    wbuf = al((size_t)2 * w * nev * es);
     // the largest set of partial products over all blocks
     size_t pe = 0;
     for (int64_t c0 = 0; c0 < N; c0 += w) {
@@ -98,7 +236,7 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
   if (hipMallocAsync((void**)&ws, L.total, st) != hipSuccess) return ELPA_ERR_NOMEM;
   E* Vp = (E*)ws;
   E* G = (E*)(ws + L.vp);
-  E* M = (E*)(ws + L.vp + L.g);
+  E* T = (E*)(ws + L.vp + L.g);
   E* W = (E*)(ws + L.vp + L.g + L.t);
   E* part = (E*)(ws + L.vp + L.g + L.t + L.wbuf);
   int rc = ELPA_OK;
@@ -106,31 +244,41 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
     std::lock_guard<std::mutex> lock(Handles::get().mu);
     rocblas_handle h = handle_for(st);
     if (!h) rc = ELPA_ERR_DEVICE;
-    const int64_t nblk = (L.N + L.w - 1) / L.w;
-    for (int64_t b = nblk - 1; rc == ELPA_OK && b >= 0; --b) {
-      const int64_t c0 = b * L.w;
-      const int64_t wb = std::min<int64_t>(L.w, L.N - c0);
-      const int64_t m = L.N - c0;  // rows c0+nbw .. n-1
+    const int64_t nblk = (L.N + L.w - 1) / L.w, w = L.w;
+    const auto N_ = rocblas_operation_none;
+    bool ok = rc == ELPA_OK;
+    auto pack = [&](int64_t c0, int64_t m, int64_t wb) {
       const unsigned gx = (unsigned)std::min<int64_t>((m + 255) / 256, 1024);
       hipLaunchKernelGGL(k_pack<E>, dim3(gx, (unsigned)wb), dim3(256), 0, st, V, ldv, nbw, c0, m,
                          Vp);
-      E* Qs = Q + c0 + nbw;
-      const auto N_ = rocblas_operation_none;
-      // G = V^H V, then M = I + diag(tau) striu(G)
-      bool ok = gemm_adj_splitk<E, S>(h, wb, wb, m, Vp, m, Vp, m,
-                                      ksplit(m, wb, wb, sizeof(E)), part, nullptr, G, st);
-      if (ok)
-        hipLaunchKernelGGL(k_unit_tri<E>, dim3((unsigned)((wb * wb + 255) / 256)), dim3(256), 0,
-                           st, G, tau + c0, wb, M);
-      // W = diag(tau) V^H Q[c0+nbw:, :], then W <- M^{-1} W (= T V^H Q)
-      ok = ok && gemm_adj_splitk<E, S>(h, wb, nev, m, Vp, m, Qs, ldq,
-                                       ksplit(m, wb, nev, sizeof(E)), part, tau + c0, W, st);
-      ok = ok && Blas<E>::trsm(h, rocblas_side_left, rocblas_operation_none, wb, nev, M, wb, W,
-                               wb) == rocblas_status_success;
-      ok = ok && Blas<E>::gemm(h, N_, N_, m, nev, wb, S(-1), Vp, m, W, wb, S(1), Qs, ldq) ==
-                     rocblas_status_success;
-      if (!ok || hipGetLastError() != hipSuccess) rc = ELPA_ERR_DEVICE;
+    };
+    // G of every block, the first to be applied last, so that its V stays packed
+    for (int64_t b = 0; ok && b < nblk; ++b) {
+      const int64_t c0 = b * w, wb = std::min<int64_t>(w, L.N - c0), m = L.N - c0;
+      pack(c0, m, wb);
+      ok = gemm_adj_splitk<E, S>(h, wb, wb, m, Vp, m, Vp, m, ksplit(m, wb, wb, sizeof(E)), part,
+                                 nullptr, G + b * w * w, st);
     }
+    if (ok) {
+      const int blocks = (int)((w + 63) / 64);
+      hipLaunchKernelGGL(k_diag_factors<E>, dim3((unsigned)blocks, (unsigned)nblk), dim3(256), 0,
+                         st, (const E*)G, tau, L.N, (int)w, T);
+      hipLaunchKernelGGL(k_strip_factors<E>, dim3((unsigned)((w + 15) / 16), (unsigned)nblk),
+                         dim3(64), (unsigned)(blocks * Planes<E>::PL * 64 * 16 * sizeof(double)),
+                         st, (const E*)G, L.N, (int)w, T);
+    }
+    for (int64_t b = nblk - 1; ok && b >= 0; --b) {
+      const int64_t c0 = b * w, wb = std::min<int64_t>(w, L.N - c0), m = L.N - c0;
+      if (b < nblk - 1) pack(c0, m, wb);
+      E* Qs = Q + c0 + nbw;
+      ok = gemm_adj_splitk<E, S>(h, wb, nev, m, Vp, m, Qs, ldq, ksplit(m, wb, nev, sizeof(E)),
+                                 part, nullptr, W, st);
+      ok = ok && Blas<E>::gemm(h, N_, N_, wb, nev, wb, S(1), T + b * w * w, wb, W, wb, S(0),
+                               W + w * nev, wb) == rocblas_status_success;
+      ok = ok && Blas<E>::gemm(h, N_, N_, m, nev, wb, S(-1), Vp, m, W + w * nev, wb, S(1), Qs,
+                               ldq) == rocblas_status_success;
+    }
+    if (rc == ELPA_OK && (!ok || hipGetLastError() != hipSuccess)) rc = ELPA_ERR_DEVICE;
   }
   const hipError_t e2 = hipFreeAsync(ws, st);
   if (rc == ELPA_OK && e2 != hipSuccess) rc = ELPA_ERR_DEVICE;

@@ -771,19 +771,6 @@ __global__ __launch_bounds__(256) void k_sum_z(const E* __restrict__ part, int64
   }
 }
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-template <typename E>
-struct Planes {
-  static constexpr int PL = std::is_same<E, double>::value ? 1 : 2;
-};
-__device__ __forceinline__ void split(double x, double* re, double*) { *re = x; }
-__device__ __forceinline__ void split(zc x, double* re, double* im) {
-  *re = x.re;
-  *im = x.im;
-}
-__device__ __forceinline__ double join(const double (&x)[1]) { return x[0]; }
-__device__ __forceinline__ zc join(const double (&x)[2]) { return zc{x[0], x[1]}; }
-
 // C (2 k x k) = [-Y / 2; T] for k <= 64, one workgroup.  T by halves: the
 // diagonal blocks of 16 by the forward recurrence, T_ii = tau_i, T[0:i, i] =
 // -tau_i T[0:i, 0:i] G[0:i, i], a lane to a row; a block beside two of them as
@@ -796,7 +783,8 @@ template <typename E>
 __global__ __launch_bounds__(256) void k_small_factors(const E* __restrict__ GS,
                                                        const E* __restrict__ tau, int k,
                                                        E* __restrict__ C) {
-  constexpr int PL = Planes<E>::PL, N = 64, LD = N + 1, I = PL - 1;
+  constexpr int PL = ebt::Planes<E>::PL, N = 64, LD = N + 1, I = PL - 1;
+  using ebt::d4;
   __shared__ double G[PL][N * LD], T[PL][N * LD];
   const int tid = (int)threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -813,7 +801,7 @@ __global__ __launch_bounds__(256) void k_small_factors(const E* __restrict__ GS,
 #pragma unroll
     for (int x = 0; x < 16; ++x) {
       double y[2];
-      split(v[x], &y[0], &y[1]);
+      ebt::split(v[x], &y[0], &y[1]);
 #pragma unroll
       for (int p = 0; p < PL; ++p) G[p][lane * LD + wave + 4 * x] = y[p];
     }
@@ -824,90 +812,12 @@ __global__ __launch_bounds__(256) void k_small_factors(const E* __restrict__ GS,
 #pragma unroll
     for (int x = 0; x < 16; ++x) T[p][lane * LD + wave + 4 * x] = 0.0;
   __syncthreads();
-  if (wave == 0) {  // row lane of its diagonal block
-    double t[PL][16], ty[2];
-    split(tk, &ty[0], &ty[1]);
-    const int o = lane & ~15;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      double a[2] = {0.0, 0.0};
-#pragma unroll
-      for (int l = 0; l < i; ++l) {
-        const double gr = G[0][(o + l) * LD + o + i];
-        if constexpr (PL == 1) {
-          a[0] += t[0][l] * gr;
-        } else {
-          const double gi = G[I][(o + l) * LD + o + i];
-          a[0] += t[0][l] * gr - t[I][l] * gi;
-          a[1] += t[0][l] * gi + t[I][l] * gr;
-        }
-      }
-      const double tr = __shfl(ty[0], o + i, 64);
-      if constexpr (PL == 1) {
-        t[0][i] = i == c16 ? tr : (i > c16 ? -(tr * a[0]) : 0.0);
-      } else {
-        const double ti = __shfl(ty[1], o + i, 64);
-        t[0][i] = i == c16 ? tr : (i > c16 ? -(tr * a[0] - ti * a[1]) : 0.0);
-        t[I][i] = i == c16 ? ti : (i > c16 ? -(tr * a[1] + ti * a[0]) : 0.0);
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < PL; ++p)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) T[p][lane * LD + o + i] = t[p][i];
-  }
-  __syncthreads();
-  // acc (tile, per plane) += (ar + i ai) (br + i bi)
-  auto mac = [&](double ar, double ai, double br, double bi, d4 (&acc)[PL]) {
-    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, acc[0], 0, 0, 0);
-    if constexpr (PL == 2) {
-      acc[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acc[I], 0, 0, 0);
-      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, acc[0], 0, 0, 0);
-      acc[I] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acc[I], 0, 0, 0);
-    }
-  };
-  // T12 = -T1 (G12 T2) of the S-wide blocks at o, o + S; this wave its columns
-  // 16 cs ..
-  auto beside = [&](auto tiles, int o, int cs) {
-    constexpr int NT = decltype(tiles)::value, S = 16 * NT;
-    d4 x[NT][PL], y[NT][PL];
-#pragma unroll
-    for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-      for (int p = 0; p < PL; ++p) x[rt][p] = y[rt][p] = d4{0, 0, 0, 0};
-    const int col = o + S + 16 * cs + c16;
-#pragma unroll
-    for (int kk = 0; kk < 4 * NT; ++kk) {
-      const int l = o + S + 4 * kk + q;
-      const double br = T[0][l * LD + col], bi = T[I][l * LD + col];
-#pragma unroll
-      for (int rt = 0; rt < NT; ++rt) {
-        const int at = (o + 16 * rt + c16) * LD + l;
-        mac(G[0][at], G[I][at], br, bi, x[rt]);
-      }
-    }
-#pragma unroll
-    for (int kk = 0; kk < 4 * NT; ++kk) {
-      const int l = o + 4 * kk + q;
-#pragma unroll
-      for (int rt = 0; rt < NT; ++rt) {
-        const int at = (o + 16 * rt + c16) * LD + l;
-        mac(T[0][at], T[I][at], x[kk / 4][0][kk % 4], x[kk / 4][I][kk % 4], y[rt]);
-      }
-    }
-#pragma unroll
-    for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-      for (int p = 0; p < PL; ++p)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) T[p][(o + 16 * rt + q + 4 * r) * LD + col] = -y[rt][p][r];
-  };
-  if (wave < 2) beside(std::integral_constant<int, 1>{}, 32 * wave, 0);
-  __syncthreads();
-  if (wave < 2) beside(std::integral_constant<int, 2>{}, 0, wave);
-  __syncthreads();
+  double ty[2];
+  ebt::split(tk, &ty[0], &ty[1]);
+  ebt::tri_factor64<PL>(G, T, ty, wave, lane);
   put(s);
   __syncthreads();
+  using ebt::mac;
   // this wave's 16 columns of U = S T, then of Y = T^H U
   d4 u[4][PL], y[4][PL];
 #pragma unroll
@@ -947,8 +857,8 @@ __global__ __launch_bounds__(256) void k_small_factors(const E* __restrict__ GS,
         a[p] = -0.5 * y[rt][p][r];
         t[p] = T[p][i * LD + col];
       }
-      C[i + (int64_t)col * 2 * k] = join(a);
-      C[k + i + (int64_t)col * 2 * k] = join(t);
+      C[i + (int64_t)col * 2 * k] = ebt::join<E>(a);
+      C[k + i + (int64_t)col * 2 * k] = ebt::join<E>(t);
     }
 }
 

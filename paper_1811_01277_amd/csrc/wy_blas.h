@@ -73,6 +73,124 @@ __global__ __launch_bounds__(256) void k_sum_parts(const E* __restrict__ part, i
   }
 }
 
+typedef double d4 __attribute__((ext_vector_type(4)));
+// Real and imaginary planes of a value, in double precision.
+template <typename E>
+struct Planes {
+  static constexpr int PL = std::is_same<E, zc>::value ? 2 : 1;
+};
+template <typename R>
+__device__ __forceinline__ void split(R x, double* re, double*) {
+  *re = (double)x;
+}
+__device__ __forceinline__ void split(zc x, double* re, double* im) {
+  *re = x.re;
+  *im = x.im;
+}
+template <typename E, int PL>
+__device__ __forceinline__ E join(const double (&x)[PL]) {
+  if constexpr (PL == 1)
+    return (E)x[0];
+  else
+    return zc{x[0], x[1]};
+}
+// acc (a 16 x 16 tile, per plane) += (ar + i ai) (br + i bi); an MFMA result is
+// the second operand of the next product as it lies in its registers (row q +
+// 4 r of lane quad q, register r)
+template <int PL>
+__device__ __forceinline__ void mac(double ar, double ai, double br, double bi, d4 (&acc)[PL]) {
+  acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, acc[0], 0, 0, 0);
+  if constexpr (PL == 2) {
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acc[1], 0, 0, 0);
+  }
+}
+
+// T (64 x 64, zero on entry) of up to 64 reflectors from the strictly upper G =
+// V^H V, both in LDS with rows 65 apart; ty: tau of row `lane`.  By halves: the
+// diagonal blocks of 16 by the forward recurrence, T_ii = tau_i, T[0:i, i] =
+// -tau_i T[0:i, 0:i] G[0:i, i], a lane to a row, and a block beside two of them
+// as -T1 (G12 T2) on the matrix cores.  256 threads; ends with a barrier.
+template <int PL>
+__device__ __forceinline__ void tri_factor64(double (&G)[PL][64 * 65], double (&T)[PL][64 * 65],
+                                             const double (&ty)[2], int wave, int lane) {
+  constexpr int LD = 65, I = PL - 1;
+  const int q = lane >> 4, c16 = lane & 15;
+  if (wave == 0) {  // row lane of its diagonal block
+    double t[PL][16];
+    const int o = lane & ~15;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      double a[2] = {0.0, 0.0};
+#pragma unroll
+      for (int l = 0; l < i; ++l) {
+        const double gr = G[0][(o + l) * LD + o + i];
+        if constexpr (PL == 1) {
+          a[0] += t[0][l] * gr;
+        } else {
+          const double gi = G[I][(o + l) * LD + o + i];
+          a[0] += t[0][l] * gr - t[I][l] * gi;
+          a[1] += t[0][l] * gi + t[I][l] * gr;
+        }
+      }
+      const double tr = __shfl(ty[0], o + i, 64);
+      if constexpr (PL == 1) {
+        t[0][i] = i == c16 ? tr : (i > c16 ? -(tr * a[0]) : 0.0);
+      } else {
+        const double ti = __shfl(ty[1], o + i, 64);
+        t[0][i] = i == c16 ? tr : (i > c16 ? -(tr * a[0] - ti * a[1]) : 0.0);
+        t[I][i] = i == c16 ? ti : (i > c16 ? -(tr * a[1] + ti * a[0]) : 0.0);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) T[p][lane * LD + o + i] = t[p][i];
+  }
+  __syncthreads();
+  // T12 = -T1 (G12 T2) of the S-wide blocks at o, o + S; this wave its columns
+  // 16 cs ..
+  auto beside = [&](auto tiles, int o, int cs) {
+    constexpr int NT = decltype(tiles)::value, S = 16 * NT;
+    d4 x[NT][PL], y[NT][PL];
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+      for (int p = 0; p < PL; ++p) x[rt][p] = y[rt][p] = d4{0, 0, 0, 0};
+    const int col = o + S + 16 * cs + c16;
+#pragma unroll
+    for (int kk = 0; kk < 4 * NT; ++kk) {
+      const int l = o + S + 4 * kk + q;
+      const double br = T[0][l * LD + col], bi = T[I][l * LD + col];
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) {
+        const int at = (o + 16 * rt + c16) * LD + l;
+        mac(G[0][at], G[I][at], br, bi, x[rt]);
+      }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4 * NT; ++kk) {
+      const int l = o + 4 * kk + q;
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) {
+        const int at = (o + 16 * rt + c16) * LD + l;
+        mac(T[0][at], T[I][at], x[kk / 4][0][kk % 4], x[kk / 4][I][kk % 4], y[rt]);
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+      for (int p = 0; p < PL; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T[p][(o + 16 * rt + q + 4 * r) * LD + col] = -y[rt][p][r];
+  };
+  if (wave < 2) beside(std::integral_constant<int, 1>{}, 32 * wave, 0);
+  __syncthreads();
+  if (wave < 2) beside(std::integral_constant<int, 2>{}, 0, wave);
+  __syncthreads();
+}
+
 // rocBLAS per element type
 template <typename E>
 struct Blas;

@@ -154,3 +154,22 @@ def test_bt2_full_size_sampled(torch_dev):
     torch.cuda.synchronize()
     got = q[:, cols].cpu().numpy()
     assert checks.max_rel_err(got, ref) <= TOL["r64"]
+
+
+@pytest.mark.parametrize("dt", ["r64", "r32", "c64"])
+def test_bt2_factor_tiles(torch_dev, dt):
+    """Blocks at the edges of the triangular factors' tiles of 16 and 64, the
+    largest block, each with a ragged last one."""
+    torch, dev = torch_dev
+    n, nbw, nev, seed = 540, 3, 21, 351
+    cplx = dt == "c64"
+    A = W.herm_gaussian(n, seed) if cplx else W.sym_gaussian(n, seed)
+    _, panels = stage1.full_to_band(A, nbw)
+    V, tau = panels_to_abi(panels, n, nbw, np.complex128 if cplx else np.float64)
+    Z = np.asfortranarray(W.gaussian_block(n, nev, complex_=cplx, seed=seed + 1))
+    ref = bt.bt_band_to_full(abi_to_panels(rounded(np.where(np.isnan(V), 0, V), dt),
+                                           rounded(tau, dt), n, nbw), rounded(Z, dt), nbw)
+    for block in (15, 16, 17, 63, 65, 79, 129, 192, 400, 449, 512):
+        print(f"bt2 factors dt={dt} block={block}", flush=True)
+        got = run_gpu(torch, dev, V, tau, Z, nbw, dt, block)
+        assert checks.max_rel_err(got.astype(ref.dtype), ref) <= TOL[dt], block
