@@ -195,7 +195,7 @@ int64_t default_block(int32_t dtype) { return dtype == ELPA_C64 ? 192 : 384; }
 
 struct Layout {
   int64_t N = 0, w = 0, mmax = 0, nev = 0;
-  size_t vp = 0, g = 0, t = 0, wbuf = 0, part = 0, total = 0;
+  size_t vp = 0, g = 0, t = 0, wbuf = 0, part = 0, total = 0, factors = 0;
   Layout(int64_t n, int64_t nev_, int64_t nbw, int64_t block, size_t es) {
     N = n > nbw ? n - nbw : 0;
     w = std::max<int64_t>(1, std::min<int64_t>(block, std::max<int64_t>(N, 1)));
@@ -203,10 +203,12 @@ struct Layout {
     nev = nev_;
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     vp = al((size_t)mmax * w * es);
+    g = al((size_t)w * w * es);
+    t = al((size_t)w * w * es);
+    wbuf = al((size_t)w * nev * es);
+    // G and T of several blocks take an allocation of their own
     const size_t blocks = (size_t)((N + w - 1) / w);
-    g = al(blocks * w * w * es);
-    t = g;
-    wbuf = al((size_t)2 * w * nev * es);
+    factors = blocks > 1 ? al(blocks * w * w * es) : 0;
     // the largest set of partial products over all blocks
     size_t pe = 0;
     for (int64_t c0 = 0; c0 < N; c0 += w) {
@@ -234,9 +236,14 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
   const Layout L(n, nev, nbw, block, sizeof(E));
   char* ws = nullptr;
   if (hipMallocAsync((void**)&ws, L.total, st) != hipSuccess) return ELPA_ERR_NOMEM;
+  char* fs = nullptr;
+  if (L.factors && hipMallocAsync((void**)&fs, 2 * L.factors, st) != hipSuccess) {
+    (void)hipFreeAsync(ws, st);
+    return ELPA_ERR_NOMEM;
+  }
   E* Vp = (E*)ws;
-  E* G = (E*)(ws + L.vp);
-  E* T = (E*)(ws + L.vp + L.g);
+  E* G = (E*)(fs ? fs : ws + L.vp);
+  E* T = (E*)(fs ? fs + L.factors : ws + L.vp + L.g);
   E* W = (E*)(ws + L.vp + L.g + L.t);
   E* part = (E*)(ws + L.vp + L.g + L.t + L.wbuf);
   int rc = ELPA_OK;
@@ -274,14 +281,15 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
       ok = gemm_adj_splitk<E, S>(h, wb, nev, m, Vp, m, Qs, ldq, ksplit(m, wb, nev, sizeof(E)),
                                  part, nullptr, W, st);
       ok = ok && Blas<E>::gemm(h, N_, N_, wb, nev, wb, S(1), T + b * w * w, wb, W, wb, S(0),
-                               W + w * nev, wb) == rocblas_status_success;
-      ok = ok && Blas<E>::gemm(h, N_, N_, m, nev, wb, S(-1), Vp, m, W + w * nev, wb, S(1), Qs,
+                               part, wb) == rocblas_status_success;  // (summed: free)
+      ok = ok && Blas<E>::gemm(h, N_, N_, m, nev, wb, S(-1), Vp, m, part, wb, S(1), Qs,
                                ldq) == rocblas_status_success;
     }
     if (rc == ELPA_OK && (!ok || hipGetLastError() != hipSuccess)) rc = ELPA_ERR_DEVICE;
   }
+  const hipError_t e3 = fs ? hipFreeAsync(fs, st) : hipSuccess;
   const hipError_t e2 = hipFreeAsync(ws, st);
-  if (rc == ELPA_OK && e2 != hipSuccess) rc = ELPA_ERR_DEVICE;
+  if (rc == ELPA_OK && (e2 != hipSuccess || e3 != hipSuccess)) rc = ELPA_ERR_DEVICE;
   return rc;
 }
 
