@@ -264,7 +264,7 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
       const int64_t c0 = b * w, wb = std::min<int64_t>(w, L.N - c0), m = L.N - c0;
       pack(c0, m, wb);
       ok = gemm_adj_splitk<E, S>(h, wb, wb, m, Vp, m, Vp, m, ksplit(m, wb, wb, sizeof(E)), part,
-                                 nullptr, G + b * w * w, st);
+                                 G + b * w * w, st);
     }
     if (ok) {
       const int blocks = (int)((w + 63) / 64);
@@ -279,7 +279,7 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
       if (b < nblk - 1) pack(c0, m, wb);
       E* Qs = Q + c0 + nbw;
       ok = gemm_adj_splitk<E, S>(h, wb, nev, m, Vp, m, Qs, ldq, ksplit(m, wb, nev, sizeof(E)),
-                                 part, nullptr, W, st);
+                                 part, W, st);
       ok = ok && Blas<E>::gemm(h, N_, N_, wb, nev, wb, S(1), T + b * w * w, wb, W, wb, S(0),
                                part, wb) == rocblas_status_success;  // (summed: free)
       ok = ok && Blas<E>::gemm(h, N_, N_, m, nev, wb, S(-1), Vp, m, part, wb, S(1), Qs,

@@ -999,8 +999,7 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
                                     part, k, 2 * k * k, chunks) == rocblas_status_success;
         if (ok) {
           hipLaunchKernelGGL(ebt::k_sum_parts<E>, dim3((unsigned)((2 * k * k + 255) / 256)),
-                             dim3(256), 0, st, (const E*)part, chunks, 2 * k * k,
-                             (const E*)nullptr, k, Gm);
+                             dim3(256), 0, st, (const E*)part, chunks, 2 * k * k, Gm);
           hipLaunchKernelGGL(k_small_factors<E>, dim3(1), dim3(256), 0, st, (const E*)Gm, tp,
                              (int)k, M);
         }
@@ -1016,7 +1015,7 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
                                            (unsigned)b),
                          dim3(256), 0, st, A, lda, r0, p, m, b);
       bool ok = ebt::gemm_adj_splitk<E, S>(h, k, k, m, Vp, ldv, Vp, ldv,
-                                           ebt::ksplit(m, k, k, es), part, nullptr, Gm, st);
+                                           ebt::ksplit(m, k, k, es), part, Gm, st);
       if (ok)
         hipLaunchKernelGGL(ebt::k_unit_tri<E>, dim3((unsigned)((k * k + 255) / 256)), dim3(256),
                            0, st, (const E*)Gm, tp, k, M);
@@ -1039,7 +1038,7 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
                            dim3(256), 0, st, Pw, m, m, k, tp, false);
       // Y = T^H V^H X = diag(conj tau) M^{-H} (V^H X), k x k (in Gm)
       ok = ok && ebt::gemm_adj_splitk<E, S>(h, k, k, m, Vp, ldv, Pw, m, ebt::ksplit(m, k, k, es),
-                                            part, nullptr, Gm, st);
+                                            part, Gm, st);
       ok = ok && Blas<E>::trsm(h, rocblas_side_left, C_, k, k, M, k, Gm, k) ==
                      rocblas_status_success;
       if (ok)

@@ -58,18 +58,16 @@ __global__ __launch_bounds__(256) void k_unit_tri(const E* __restrict__ G,
   M[e] = j < i ? Num<E>::mul(tau[j], G[e]) : (j == i ? Num<E>::one() : Num<E>::zero());
 }
 
-// out[e] = scale(e) * sum_s part[s][e] over cnt partial products of `total`
-// elements each (fixed order: the same bits on every call); scale is tau[e %
-// wb] when tau is given (the row scaling of W), else 1.
+// out[e] = sum_s part[s][e] over cnt partial products of `total` elements each
+// (fixed order: the same bits on every call).
 template <typename E>
 __global__ __launch_bounds__(256) void k_sum_parts(const E* __restrict__ part, int64_t cnt,
-                                                   int64_t total, const E* __restrict__ tau,
-                                                   int64_t wb, E* __restrict__ out) {
+                                                   int64_t total, E* __restrict__ out) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     E acc = part[e];
     for (int64_t k = 1; k < cnt; ++k) acc = Num<E>::add(acc, part[k * total + e]);
-    out[e] = tau ? Num<E>::mul(tau[e % wb], acc) : acc;
+    out[e] = acc;
   }
 }
 
@@ -311,11 +309,10 @@ inline int64_t ksplit(int64_t m, int64_t wb, int64_t N, size_t es) {
 }
 
 // C (wb x N) = A^H B over m rows (A m x wb, lda; B m x N, ldb) as `chunks`
-// K-chunk partial products in part, summed in a fixed order; rows of C
-// scaled by tau when given.
+// K-chunk partial products in part, summed in a fixed order.
 template <typename E, typename S>
 bool gemm_adj_splitk(rocblas_handle h, int64_t wb, int64_t N, int64_t m, const E* A, int64_t lda,
-                     const E* B, int64_t ldb, int64_t chunks, E* part, const E* tau, E* C,
+                     const E* B, int64_t ldb, int64_t chunks, E* part, E* C,
                      hipStream_t st) {
   const int64_t kc = (m + chunks - 1) / chunks;
   const int64_t full = m / kc, rem = m - full * kc;
@@ -331,7 +328,7 @@ bool gemm_adj_splitk(rocblas_handle h, int64_t wb, int64_t N, int64_t m, const E
   if (ok) {
     const int64_t total = wb * N;
     hipLaunchKernelGGL(k_sum_parts<E>, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 8192)),
-                       dim3(256), 0, st, part, full + (rem > 0 ? 1 : 0), total, tau, wb, C);
+                       dim3(256), 0, st, part, full + (rem > 0 ? 1 : 0), total, C);
   }
   return ok;
 }
