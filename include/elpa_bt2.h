@@ -50,9 +50,7 @@ int elpa_bt2_trafo(int64_t n, int64_t nev, int64_t nbw, const void *V, int64_t l
 
 /*
  * Device workspace (bytes) elpa_bt2_trafo allocates for these sizes and block
- * (0 = library choice); -1 for invalid arguments.  Calls of more than one block
- * also allocate, in the same way, the factors of all blocks: 2 block elements
- * per reflector (rounded up to whole blocks).
+ * (0 = library choice); -1 for invalid arguments.
  */
 int64_t elpa_bt2_workspace_bytes(int64_t n, int64_t nev, int64_t nbw, int32_t dtype,
                                  int64_t block);

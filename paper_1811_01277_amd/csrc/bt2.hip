@@ -9,7 +9,7 @@
 // diagonal and zeros above it; T the upper triangular factor of the forward
 // accumulation, no division by tau: tau = 0, an identity reflector, is fine).
 // The factors depend on the vectors alone, so all blocks' G = V^H V come first,
-// then all T in two launches; then the blocks are applied, last block first, as
+// then all T in three launches; then the blocks are applied, last block first, as
 //   W = V^H Q[c0+nbw:, :],  W <- T W,  Q[c0+nbw:, :] -= V W,
 // plain GEMMs on the matrix cores through rocBLAS.  Packing V (explicit zeros
 // and unit lead, so the vectors may share storage with anything above them) and
@@ -53,26 +53,30 @@ __global__ __launch_bounds__(256) void k_pack(const E* __restrict__ V, int64_t l
   }
 }
 
-// T's diagonal blocks of 64: workgroup (d, b) does block d of G_b, T_b (w x w,
-// column major); reflectors N in all, w per block.
+// G = V^H V and T share their storage: block b (w x w at F + b stride, column
+// major, ld its own width) holds G, whose upper triangle becomes T.  G is
+// Hermitian, so what T takes the place of is read from the lower triangle, and
+// that is cleared last.  N reflectors in all, w per block; the blocks are
+// numbered in the first grid dimension, as there may be as many as reflectors.
+
+// T's diagonal blocks of 64.
 template <typename E>
-__global__ __launch_bounds__(256) void k_diag_factors(const E* __restrict__ Gall,
-                                                      const E* __restrict__ tau, int64_t N, int w,
-                                                      E* __restrict__ Tall) {
+__global__ __launch_bounds__(256) void k_diag_factors(E* __restrict__ F, int64_t stride,
+                                                      const E* __restrict__ tau, int64_t N, int w) {
   constexpr int PL = Planes<E>::PL, LD = 65;
   __shared__ double G[PL][64 * LD], T[PL][64 * LD];
   const int lane = (int)threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int64_t b = blockIdx.y, left = N - b * w;
-  const int wb = (int)(left < w ? left : w), o = 64 * (int)blockIdx.x;
+  const int per = (w + 63) / 64, o = 64 * (int)(blockIdx.x % per);
+  const int64_t b = blockIdx.x / per, left = N - b * w;
+  const int wb = (int)(left < w ? left : w);
   if (o >= wb) return;
-  const E* __restrict__ Gb = Gall + b * (int64_t)w * w;
-  E* __restrict__ Tb = Tall + b * (int64_t)w * w;
+  E* __restrict__ Fb = F + b * stride;
 #pragma unroll
   for (int x = 0; x < 16; ++x) {
     const int c = wave + 4 * x;
     double g[2] = {0.0, 0.0};
-    if (o + lane < wb && o + c < wb) split(Gb[o + lane + (int64_t)(o + c) * wb], &g[0], &g[1]);
+    if (o + lane < wb && o + c < wb) split(Fb[o + lane + (int64_t)(o + c) * wb], &g[0], &g[1]);
 #pragma unroll
     for (int p = 0; p < PL; ++p) {
       G[p][lane * LD + c] = g[p];
@@ -89,38 +93,38 @@ __global__ __launch_bounds__(256) void k_diag_factors(const E* __restrict__ Gall
     double t[PL];
 #pragma unroll
     for (int p = 0; p < PL; ++p) t[p] = T[p][lane * LD + c];
-    if (o + lane < wb && o + c < wb) Tb[o + lane + (int64_t)(o + c) * wb] = join<E>(t);
+    if (o + lane < wb && o + c < wb) Fb[o + lane + (int64_t)(o + c) * wb] = join<E>(t);
   }
 }
 
-// The rest of T: wave (s, b) does the columns 16 s .. of T_b, upwards from the
-// diagonal block j they lie in: T_ij = -T_ii sum_{i < l <= j} G_il T_lj, and the
-// zeros below.  The strip stays in LDS; G and T_ii come from memory, rows of a
-// tile together.  The columns of one block and all blocks run side by side:
-// the longest strip's chain of products, 64 per 64 x 64 x 16 block, bounds it,
-// with a product's operands all in flight before its first use (54 us for
-// sixteen blocks of 371 at n = 6000; 381 with four loads in flight).
+// The rest of T: one wave does the columns 16 s .. of T_b, upwards from the
+// diagonal block j they lie in: T_ij = -T_ii sum_{i < l <= j} G_il T_lj.  The
+// strip stays in LDS; G_il = G_li^H and T_ii come from memory, rows of a tile
+// together.  The columns of one block and all blocks run side by side: the
+// longest strip's chain of products, 64 per 64 x 64 x 16 block, bounds it, with
+// a product's operands all in flight before its first use (54 us for sixteen
+// blocks of 371 at n = 6000; 381 with four loads in flight).
 template <typename E>
-__global__ __launch_bounds__(64) void k_strip_factors(const E* __restrict__ Gall, int64_t N, int w,
-                                                      E* __restrict__ Tall) {
+__global__ __launch_bounds__(64) void k_strip_factors(E* __restrict__ F, int64_t stride, int64_t N,
+                                                      int w) {
   constexpr int PL = Planes<E>::PL, I = PL - 1;
   extern __shared__ double strip[];  // [block][plane][64 rows][16 columns]
   const int lane = (int)threadIdx.x, q = lane >> 4, c16 = lane & 15;
-  const int64_t b = blockIdx.y, left = N - b * w;
-  const int wb = (int)(left < w ? left : w), col = 16 * (int)blockIdx.x + c16;
-  if (16 * (int)blockIdx.x >= wb) return;
-  const int j = (int)blockIdx.x / 4;
-  const E* __restrict__ Gb = Gall + b * (int64_t)w * w;
-  E* __restrict__ Tb = Tall + b * (int64_t)w * w;
+  const int per = (w + 15) / 16, s = (int)(blockIdx.x % per);
+  const int64_t b = blockIdx.x / per, left = N - b * w;
+  const int wb = (int)(left < w ? left : w), col = 16 * s + c16;
+  if (16 * s >= wb) return;
+  const int j = s / 4;
+  E* Fb = F + b * stride;
   constexpr int KC = PL == 2 ? 8 : 16;  // k-steps loaded at a time
-  // (columns past the block meet zeros of the strip: any entry will do)
-  auto get = [&](const E* __restrict__ M, int r, int c) {
-    return M[r + (int64_t)(c < wb ? c : wb - 1) * wb];
+  // (rows and columns past the block meet zeros of the strip: any entry will do)
+  auto get = [&](int r, int c) {
+    return Fb[(r < wb ? r : wb - 1) + (int64_t)(c < wb ? c : wb - 1) * wb];
   };
   auto at = [&](int l, int p, int row) { return ((l * PL + p) * 64 + row) * 16 + c16; };
   for (int row = q; row < 64; row += 4) {
     double t[2] = {0.0, 0.0};
-    if (64 * j + row < wb && col < wb) split(Tb[64 * j + row + (int64_t)col * wb], &t[0], &t[1]);
+    if (64 * j + row < wb && col < wb) split(Fb[64 * j + row + (int64_t)col * wb], &t[0], &t[1]);
 #pragma unroll
     for (int p = 0; p < PL; ++p) strip[at(j, p, row)] = t[p];
   }
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(64) void k_strip_factors(const E* __restrict__ Gall
         for (int kk = 0; kk < KC; ++kk)
 #pragma unroll
           for (int rt = 0; rt < 4; ++rt)
-            g[kk][rt] = get(Gb, 64 * i + 16 * rt + c16, 64 * l + 4 * (k0 + kk) + q);
+            g[kk][rt] = get(64 * l + 4 * (k0 + kk) + q, 64 * i + 16 * rt + c16);
 #pragma unroll
         for (int kk = 0; kk < KC; ++kk) {
           const double br = strip[at(l, 0, 4 * (k0 + kk) + q)];
@@ -148,7 +152,7 @@ __global__ __launch_bounds__(64) void k_strip_factors(const E* __restrict__ Gall
           for (int rt = 0; rt < 4; ++rt) {
             double y2[2] = {0.0, 0.0};
             split(g[kk][rt], &y2[0], &y2[1]);
-            mac(y2[0], y2[1], br, bi, x[rt]);
+            mac(y2[0], -y2[1], br, bi, x[rt]);
           }
         }
       }
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(64) void k_strip_factors(const E* __restrict__ Gall
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt)
           if ((k0 + kk) / 4 >= rt)  // T_ii is upper triangular
-            g[kk][rt] = get(Tb, 64 * i + 16 * rt + c16, 64 * i + 4 * (k0 + kk) + q);
+            g[kk][rt] = get(64 * i + 16 * rt + c16, 64 * i + 4 * (k0 + kk) + q);
 #pragma unroll
       for (int kk = 0; kk < KC; ++kk)
 #pragma unroll
@@ -182,20 +186,30 @@ __global__ __launch_bounds__(64) void k_strip_factors(const E* __restrict__ Gall
           v[p] = -y[rt][p][r];
           strip[at(i, p, row)] = v[p];
         }
-        if (col < wb) Tb[64 * i + row + (int64_t)col * wb] = join<E>(v);
+        if (col < wb) Fb[64 * i + row + (int64_t)col * wb] = join<E>(v);
       }
     __builtin_amdgcn_wave_barrier();
   }
-  if (col < wb)
-    for (int row = 64 * (j + 1) + q; row < wb; row += 4)
-      Tb[row + (int64_t)col * wb] = Num<E>::zero();
+}
+
+// Zeros below the diagonal blocks, a wave to a column.
+template <typename E>
+__global__ __launch_bounds__(256) void k_lower_zeros(E* __restrict__ F, int64_t stride, int64_t N,
+                                                     int w) {
+  const int per = (w + 3) / 4, c = 4 * (int)(blockIdx.x % per) + (int)(threadIdx.x >> 6);
+  const int64_t b = blockIdx.x / per, left = N - b * w;
+  const int wb = (int)(left < w ? left : w);
+  if (c >= wb) return;
+  for (int r = (c / 64 + 1) * 64 + (int)(threadIdx.x & 63); r < wb; r += 64)
+    F[b * stride + r + (int64_t)c * wb] = Num<E>::zero();
 }
 
 int64_t default_block(int32_t dtype) { return dtype == ELPA_C64 ? 192 : 384; }
 
 struct Layout {
   int64_t N = 0, w = 0, mmax = 0, nev = 0;
-  size_t vp = 0, g = 0, t = 0, wbuf = 0, part = 0, total = 0, factors = 0;
+  // packed V, one block's factor, all of them, W, partial products
+  size_t vp = 0, factor = 0, factors = 0, wbuf = 0, part = 0, total = 0;
   Layout(int64_t n, int64_t nev_, int64_t nbw, int64_t block, size_t es) {
     N = n > nbw ? n - nbw : 0;
     w = std::max<int64_t>(1, std::min<int64_t>(block, std::max<int64_t>(N, 1)));
@@ -203,12 +217,9 @@ struct Layout {
     nev = nev_;
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     vp = al((size_t)mmax * w * es);
-    g = al((size_t)w * w * es);
-    t = al((size_t)w * w * es);
+    factor = al((size_t)w * w * es);
+    factors = (size_t)((N + w - 1) / w) * factor;
     wbuf = al((size_t)w * nev * es);
-    // G and T of several blocks take an allocation of their own
-    const size_t blocks = (size_t)((N + w - 1) / w);
-    factors = blocks > 1 ? al(blocks * w * w * es) : 0;
     // the largest set of partial products over all blocks
     size_t pe = 0;
     for (int64_t c0 = 0; c0 < N; c0 += w) {
@@ -217,7 +228,7 @@ struct Layout {
       pe = std::max(pe, (size_t)ksplit(m, wb, wb, es) * wb * wb);
     }
     part = al(pe * es);
-    total = vp + g + t + wbuf + part;
+    total = vp + factors + wbuf + part;
   }
 };
 
@@ -236,16 +247,11 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
   const Layout L(n, nev, nbw, block, sizeof(E));
   char* ws = nullptr;
   if (hipMallocAsync((void**)&ws, L.total, st) != hipSuccess) return ELPA_ERR_NOMEM;
-  char* fs = nullptr;
-  if (L.factors && hipMallocAsync((void**)&fs, 2 * L.factors, st) != hipSuccess) {
-    (void)hipFreeAsync(ws, st);
-    return ELPA_ERR_NOMEM;
-  }
   E* Vp = (E*)ws;
-  E* G = (E*)(fs ? fs : ws + L.vp);
-  E* T = (E*)(fs ? fs + L.factors : ws + L.vp + L.g);
-  E* W = (E*)(ws + L.vp + L.g + L.t);
-  E* part = (E*)(ws + L.vp + L.g + L.t + L.wbuf);
+  E* F = (E*)(ws + L.vp);
+  E* W = (E*)(ws + L.vp + L.factors);
+  E* part = (E*)(ws + L.vp + L.factors + L.wbuf);
+  const int64_t stride = (int64_t)(L.factor / sizeof(E));
   int rc = ELPA_OK;
   {
     std::lock_guard<std::mutex> lock(Handles::get().mu);
@@ -264,15 +270,19 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
       const int64_t c0 = b * w, wb = std::min<int64_t>(w, L.N - c0), m = L.N - c0;
       pack(c0, m, wb);
       ok = gemm_adj_splitk<E, S>(h, wb, wb, m, Vp, m, Vp, m, ksplit(m, wb, wb, sizeof(E)), part,
-                                 G + b * w * w, st);
+                                 F + b * stride, st);
     }
     if (ok) {
       const int blocks = (int)((w + 63) / 64);
-      hipLaunchKernelGGL(k_diag_factors<E>, dim3((unsigned)blocks, (unsigned)nblk), dim3(256), 0,
-                         st, (const E*)G, tau, L.N, (int)w, T);
-      hipLaunchKernelGGL(k_strip_factors<E>, dim3((unsigned)((w + 15) / 16), (unsigned)nblk),
-                         dim3(64), (unsigned)(blocks * Planes<E>::PL * 64 * 16 * sizeof(double)),
-                         st, (const E*)G, L.N, (int)w, T);
+      hipLaunchKernelGGL(k_diag_factors<E>, dim3((unsigned)(nblk * blocks)), dim3(256), 0, st, F,
+                         stride, tau, L.N, (int)w);
+      if (blocks > 1) {
+        hipLaunchKernelGGL(k_strip_factors<E>, dim3((unsigned)(nblk * ((w + 15) / 16))), dim3(64),
+                           (unsigned)(blocks * Planes<E>::PL * 64 * 16 * sizeof(double)), st, F,
+                           stride, L.N, (int)w);
+        hipLaunchKernelGGL(k_lower_zeros<E>, dim3((unsigned)(nblk * ((w + 3) / 4))), dim3(256), 0,
+                           st, F, stride, L.N, (int)w);
+      }
     }
     for (int64_t b = nblk - 1; ok && b >= 0; --b) {
       const int64_t c0 = b * w, wb = std::min<int64_t>(w, L.N - c0), m = L.N - c0;
@@ -280,16 +290,15 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
       E* Qs = Q + c0 + nbw;
       ok = gemm_adj_splitk<E, S>(h, wb, nev, m, Vp, m, Qs, ldq, ksplit(m, wb, nev, sizeof(E)),
                                  part, W, st);
-      ok = ok && Blas<E>::gemm(h, N_, N_, wb, nev, wb, S(1), T + b * w * w, wb, W, wb, S(0),
+      ok = ok && Blas<E>::gemm(h, N_, N_, wb, nev, wb, S(1), F + b * stride, wb, W, wb, S(0),
                                part, wb) == rocblas_status_success;  // (summed: free)
       ok = ok && Blas<E>::gemm(h, N_, N_, m, nev, wb, S(-1), Vp, m, part, wb, S(1), Qs,
                                ldq) == rocblas_status_success;
     }
     if (rc == ELPA_OK && (!ok || hipGetLastError() != hipSuccess)) rc = ELPA_ERR_DEVICE;
   }
-  const hipError_t e3 = fs ? hipFreeAsync(fs, st) : hipSuccess;
   const hipError_t e2 = hipFreeAsync(ws, st);
-  if (rc == ELPA_OK && (e2 != hipSuccess || e3 != hipSuccess)) rc = ELPA_ERR_DEVICE;
+  if (rc == ELPA_OK && e2 != hipSuccess) rc = ELPA_ERR_DEVICE;
   return rc;
 }
 

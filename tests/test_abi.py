@@ -365,3 +365,20 @@ def test_library_choice_boundaries(dt, nbw, n, nev, path, k):
     got = P.chosen_plan(n, nev, nbw, code)
     want = {"split": P.PATH_SPLIT, "wy": P.PATH_WY}[path]
     assert (got["path"], got["k"]) == (want, k), got
+
+
+@pytest.mark.parametrize("n,nev,nbw,block,dt", [(100, 5, 32, 64, "r64"), (100, 5, 32, 16, "r32"),
+                                                (500, 7, 20, 100, "c64"), (500, 40, 20, 480, "r64"),
+                                                (90, 3, 1, 1, "r64")])
+def test_bt2_workspace_counts_every_block(n, nev, nbw, block, dt):
+    """Packed V of the first block, the triangular factor of every block, W and
+    the partial products, each 256-byte aligned.  (At these sizes a product's
+    rows are one K chunk, or two from 512 rows on.)"""
+    code, es = {"r64": (P.R64, 8), "r32": (P.R32, 4), "c64": (P.C64, 16)}[dt]
+    al = lambda x: -(-x // 256) * 256
+    N = n - nbw
+    assert N < 512
+    w = min(block, N)
+    want = (al(N * w * es) + -(-N // w) * al(w * w * es) + al(w * nev * es) +
+            al(w * max(w, nev) * es))
+    assert P.bt2_workspace_bytes(n, nev, nbw, code, block) == want

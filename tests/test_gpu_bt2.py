@@ -173,3 +173,46 @@ def test_bt2_factor_tiles(torch_dev, dt):
         print(f"bt2 factors dt={dt} block={block}", flush=True)
         got = run_gpu(torch, dev, V, tau, Z, nbw, dt, block)
         assert checks.max_rel_err(got.astype(ref.dtype), ref) <= TOL[dt], block
+
+
+def pool_high(torch):
+    """The current device's default memory pool: its high-water mark is reset by
+    the first function returned and read by the second."""
+    import ctypes as C
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = C.CDLL(path)
+    pool = C.c_void_p()
+    assert hip.hipDeviceGetDefaultMemPool(C.byref(pool), torch.cuda.current_device()) == 0
+    high = 8   # hipMemPoolAttrUsedMemHigh
+    val = C.c_uint64()
+
+    def reset():
+        val.value = 0
+        assert hip.hipMemPoolSetAttribute(pool, high, C.byref(val)) == 0
+
+    def read():
+        assert hip.hipMemPoolGetAttribute(pool, high, C.byref(val)) == 0
+        return val.value
+    return reset, read
+
+
+@pytest.mark.parametrize("n,nev,block", [(1200, 100, 0), (1200, 10, 64), (300, 10, 0)])
+def test_bt2_allocates_what_it_reports(torch_dev, n, nev, block):
+    """The memory pool's high-water mark over a call is the reported workspace
+    (to the pool's own rounding)."""
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    nbw = 32
+    V, tau = W.synthetic_stage1(n, nbw, seed=361)
+    vbuf, v = to_dev(torch, dev, V, "r64")
+    qbuf, q = to_dev(torch, dev, W.gaussian_block(n, nev, seed=362), "r64")
+    t = torch.from_numpy(tau).to(dev)
+    P.bt2_trafo(q, v, t, nbw, block=block)
+    torch.cuda.synchronize()
+    reset, read = pool_high(torch)
+    reset()
+    P.bt2_trafo(q, v, t, nbw, block=block)
+    torch.cuda.synchronize()
+    need = P.bt2_workspace_bytes(n, nev, nbw, P.R64, block)
+    print(f"pool high {read()}, reported {need}", flush=True)
+    assert need <= read() <= need + (1 << 16)
