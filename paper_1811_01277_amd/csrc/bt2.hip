@@ -97,98 +97,87 @@ __global__ __launch_bounds__(256) void k_diag_factors(E* __restrict__ F, int64_t
   }
 }
 
-// The rest of T: one wave does the columns 16 s .. of T_b, upwards from the
-// diagonal block j they lie in: T_ij = -T_ii sum_{i < l <= j} G_il T_lj.  The
-// strip stays in LDS; G_il = G_li^H and T_ii come from memory, rows of a tile
-// together.  The columns of one block and all blocks run side by side: the
-// longest strip's chain of products, 64 per 64 x 64 x 16 block, bounds it, with
-// a product's operands all in flight before its first use (54 us for sixteen
-// blocks of 371 at n = 6000; 381 with four loads in flight).
+// The rest of T: a workgroup does the columns 16 s .. of T_b, upwards from the
+// diagonal block j they lie in: T_ij = -T_ii sum_{i < l <= j} G_il T_lj, wave v
+// the rows 16 v .. of each.  The strip stays in LDS; G_il = G_li^H and T_ii come
+// from memory, rows of a tile together.  The columns of one block and all blocks
+// run side by side: the longest strip's chain of products, sixteen per wave and
+// 64 x 64 x 16 block, bounds it, with a product's operands all in flight before
+// its first use.  (One wave to a strip, four times the chain: complex n = 1000
+// in two blocks of up to 512 took 632 us instead of 455.)
 template <typename E>
-__global__ __launch_bounds__(64) void k_strip_factors(E* __restrict__ F, int64_t stride, int64_t N,
-                                                      int w) {
+__global__ __launch_bounds__(256) void k_strip_factors(E* __restrict__ F, int64_t stride,
+                                                       int64_t N, int w) {
   constexpr int PL = Planes<E>::PL, I = PL - 1;
   extern __shared__ double strip[];  // [block][plane][64 rows][16 columns]
-  const int lane = (int)threadIdx.x, q = lane >> 4, c16 = lane & 15;
+  const int lane = (int)threadIdx.x & 63, q = lane >> 4, c16 = lane & 15;
+  const int rt = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int per = (w + 15) / 16, s = (int)(blockIdx.x % per);
   const int64_t b = blockIdx.x / per, left = N - b * w;
   const int wb = (int)(left < w ? left : w), col = 16 * s + c16;
   if (16 * s >= wb) return;
   const int j = s / 4;
   E* Fb = F + b * stride;
-  constexpr int KC = PL == 2 ? 8 : 16;  // k-steps loaded at a time
-  // (rows and columns past the block meet zeros of the strip: any entry will do)
-  auto get = [&](int r, int c) {
-    return Fb[(r < wb ? r : wb - 1) + (int64_t)(c < wb ? c : wb - 1) * wb];
-  };
+  // (rows past the block meet zeros of the strip: any entry will do)
+  auto get = [&](int r, int c) { return Fb[(r < wb ? r : wb - 1) + (int64_t)c * wb]; };
   auto at = [&](int l, int p, int row) { return ((l * PL + p) * 64 + row) * 16 + c16; };
-  for (int row = q; row < 64; row += 4) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = 16 * rt + q + 4 * r;
     double t[2] = {0.0, 0.0};
     if (64 * j + row < wb && col < wb) split(Fb[64 * j + row + (int64_t)col * wb], &t[0], &t[1]);
 #pragma unroll
     for (int p = 0; p < PL; ++p) strip[at(j, p, row)] = t[p];
   }
-  __builtin_amdgcn_wave_barrier();
+  __syncthreads();
   for (int i = j - 1; i >= 0; --i) {
-    d4 x[4][PL], y[4][PL];
+    d4 x[PL], y[PL];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int p = 0; p < PL; ++p) x[p] = y[p] = d4{0, 0, 0, 0};
+    E g[16], t[16];
 #pragma unroll
-      for (int p = 0; p < PL; ++p) x[rt][p] = y[rt][p] = d4{0, 0, 0, 0};
-    for (int l = i + 1; l <= j; ++l)
-#pragma unroll 1
-      for (int k0 = 0; k0 < 16; k0 += KC) {
-        E g[KC][4];
+    for (int kk = 0; kk < 16; ++kk) g[kk] = get(64 * (i + 1) + 4 * kk + q, 64 * i + 16 * rt + c16);
 #pragma unroll
-        for (int kk = 0; kk < KC; ++kk)
+    for (int kk = 0; kk < 16; ++kk) t[kk] = get(64 * i + 16 * rt + c16, 64 * i + 4 * kk + q);
+    for (int l = i + 1; l <= j; ++l) {
+      E h[16];  // the next block's
+      const int ln = l < j ? l + 1 : j;
 #pragma unroll
-          for (int rt = 0; rt < 4; ++rt)
-            g[kk][rt] = get(64 * l + 4 * (k0 + kk) + q, 64 * i + 16 * rt + c16);
+      for (int kk = 0; kk < 16; ++kk) h[kk] = get(64 * ln + 4 * kk + q, 64 * i + 16 * rt + c16);
 #pragma unroll
-        for (int kk = 0; kk < KC; ++kk) {
-          const double br = strip[at(l, 0, 4 * (k0 + kk) + q)];
-          const double bi = strip[at(l, I, 4 * (k0 + kk) + q)];
-#pragma unroll
-          for (int rt = 0; rt < 4; ++rt) {
-            double y2[2] = {0.0, 0.0};
-            split(g[kk][rt], &y2[0], &y2[1]);
-            mac(y2[0], -y2[1], br, bi, x[rt]);
-          }
-        }
+      for (int kk = 0; kk < 16; ++kk) {
+        double a[2] = {0.0, 0.0};
+        split(g[kk], &a[0], &a[1]);
+        mac(a[0], -a[1], strip[at(l, 0, 4 * kk + q)], strip[at(l, I, 4 * kk + q)], x);
+        g[kk] = h[kk];
       }
-#pragma unroll
-    for (int k0 = 0; k0 < 16; k0 += KC) {
-      E g[KC][4];
-#pragma unroll
-      for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-        for (int rt = 0; rt < 4; ++rt)
-          if ((k0 + kk) / 4 >= rt)  // T_ii is upper triangular
-            g[kk][rt] = get(64 * i + 16 * rt + c16, 64 * i + 4 * (k0 + kk) + q);
-#pragma unroll
-      for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-          if ((k0 + kk) / 4 < rt) continue;
-          double y2[2] = {0.0, 0.0};
-          split(g[kk][rt], &y2[0], &y2[1]);
-          mac(y2[0], y2[1], x[(k0 + kk) / 4][0][kk % 4], x[(k0 + kk) / 4][I][kk % 4], y[rt]);
-        }
     }
+    // the sum passes between the waves in the place of T_ij
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * rt + q + 4 * r;
-        double v[PL];
+      for (int p = 0; p < PL; ++p) strip[at(i, p, 16 * rt + q + 4 * r)] = x[p][r];
+    __syncthreads();
 #pragma unroll
-        for (int p = 0; p < PL; ++p) {
-          v[p] = -y[rt][p][r];
-          strip[at(i, p, row)] = v[p];
-        }
-        if (col < wb) Fb[64 * i + row + (int64_t)col * wb] = join<E>(v);
+    for (int kk = 0; kk < 16; ++kk) {
+      if (kk / 4 < rt) continue;  // T_ii is upper triangular
+      double a[2] = {0.0, 0.0};
+      split(t[kk], &a[0], &a[1]);
+      mac(a[0], a[1], strip[at(i, 0, 4 * kk + q)], strip[at(i, I, 4 * kk + q)], y);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * rt + q + 4 * r;
+      double v[PL];
+#pragma unroll
+      for (int p = 0; p < PL; ++p) {
+        v[p] = -y[p][r];
+        strip[at(i, p, row)] = v[p];
       }
-    __builtin_amdgcn_wave_barrier();
+      if (col < wb) Fb[64 * i + row + (int64_t)col * wb] = join<E>(v);
+    }
+    __syncthreads();
   }
 }
 
@@ -277,7 +266,7 @@ int run(int64_t n, int64_t nev, int64_t nbw, const E* V, int64_t ldv, const E* t
       hipLaunchKernelGGL(k_diag_factors<E>, dim3((unsigned)(nblk * blocks)), dim3(256), 0, st, F,
                          stride, tau, L.N, (int)w);
       if (blocks > 1) {
-        hipLaunchKernelGGL(k_strip_factors<E>, dim3((unsigned)(nblk * ((w + 15) / 16))), dim3(64),
+        hipLaunchKernelGGL(k_strip_factors<E>, dim3((unsigned)(nblk * ((w + 15) / 16))), dim3(256),
                            (unsigned)(blocks * Planes<E>::PL * 64 * 16 * sizeof(double)), st, F,
                            stride, L.N, (int)w);
         hipLaunchKernelGGL(k_lower_zeros<E>, dim3((unsigned)(nblk * ((w + 3) / 4))), dim3(256), 0,

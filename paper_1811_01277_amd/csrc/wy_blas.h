@@ -309,7 +309,7 @@ inline int64_t ksplit(int64_t m, int64_t wb, int64_t N, size_t es) {
 }
 
 // C (wb x N) = A^H B over m rows (A m x wb, lda; B m x N, ldb) as `chunks`
-// K-chunk partial products in part, summed in a fixed order.
+// K-chunk partial products in part, summed in a fixed order (one chunk: into C).
 template <typename E, typename S>
 bool gemm_adj_splitk(rocblas_handle h, int64_t wb, int64_t N, int64_t m, const E* A, int64_t lda,
                      const E* B, int64_t ldb, int64_t chunks, E* part, E* C,
@@ -319,6 +319,9 @@ bool gemm_adj_splitk(rocblas_handle h, int64_t wb, int64_t N, int64_t m, const E
   const auto A_ = Blas<E>::adj;
   const auto N_ = rocblas_operation_none;
   bool ok = true;
+  if (chunks == 1)
+    return Blas<E>::gemm_sb(h, A_, N_, wb, N, m, S(1), A, lda, m, B, ldb, m, S(0), C, wb, wb * N,
+                            1) == rocblas_status_success;
   if (full > 0)
     ok = Blas<E>::gemm_sb(h, A_, N_, wb, N, kc, S(1), A, lda, kc, B, ldb, kc, S(0), part, wb,
                           wb * N, full) == rocblas_status_success;
