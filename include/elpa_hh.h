@@ -123,7 +123,8 @@ enum {
  * calls, ELPA_BATCH_* (single-problem calls ignore it).
  * Results do not depend on steps, order, streams or batch.
  * A single problem of ELPA_PATH_WY or, in fp64, of ELPA_PATH_SPLIT whose plan
- * sets neither steps nor several streams runs in one launch: the sweep blocks
+ * sets neither steps nor several streams runs in one launch (complex ones as
+ * long as the device has room to gain by it): the sweep blocks
  * of a stripe side by side, each a step or two behind the next, on workgroups
  * of the whole device or (ELPA_PATH_SPLIT, by a model of both) on the waves of
  * one workgroup.  The first form takes 32 bytes per stripe of 16 (ELPA_PATH_WY:

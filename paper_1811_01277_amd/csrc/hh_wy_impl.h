@@ -915,15 +915,21 @@ hipError_t run_wy(const void* hh, const void* tau, void* Q, int64_t ldq, int64_t
   if constexpr (WyUnit<E, NB, K>::kHas) {
     // One launch where the schedule is left open and the counts have room,
     // unless the diagonal schedule is one launch too.  Against the diagonal
-    // launches: fp32, n = 300 / 1000 / 2501 with 1251 columns / 6000 / 12000:
-    // 96 / 219 / 577 / 5630 / 38800 us against 166 / 396 / 995 / 6900 / 45000;
-    // complex, n = 300 / 1500 / 4000: 249 / 1186 / 12600 against 294 / 1711 /
-    // 13080; fp64, n = 3000 / 6000 with 3000 columns / 20000: 1.79 / 5.66 / 321
-    // ms against 2.86 / 7.35 / 338; n = 2 (one launch): 57 us against 50.
+    // launches: fp32, n = 300 / 1000 / 2501 with 1251 columns / 6000 / 20000:
+    // 96 / 219 / 562 / 5600 / 173800 us against 166 / 396 / 1015 / 6770 / 193600;
+    // fp64, n = 3000 / 6000 / 12000 / 20000: 1.80 / 10.6 / 72 / 317 ms against
+    // 2.88 / 11.5 / 77 / 338; n = 2 (one launch): 57 us against 50.
+    // Complex, one workgroup to a compute unit: up to about 28 units for each.
+    // Past that the diagonal launches fill the device, and their waves, which
+    // need no barriers, run 7 % faster: n = 3000 (12 units each) 5.65 ms against
+    // 6.96, 4000 (21) 12.6 / 13.2, 6000 with 3000 columns (23) 21.1 / 22.1, 5000
+    // (32) 25.1 / 24.7, 8000 with 4000 (41) 49.1 / 49.7, 6000 (46) 42.5 / 41.6,
+    // 20000 with 2000 (52) 158 / 155, 8000 (82) 99.9 / 94.6, 20000 1511 / 1407.
     const int64_t tiles = (nev + 15) / 16, H = (tiles + 3) / 4;
     const int64_t groups = std::min<int64_t>(opt.streams, pl.G);
     const int64_t nw = (int64_t)pipe_words(H * pl.M);
     if (opt.steps <= 0 && !opt.grouped && pl.T * groups > 1 &&
+        (WyElem<E>::PL == 1 || H * pl.M <= 28 * (int64_t)num_cu) &&
         H * pl.M < INT32_MAX / kPipeStride &&
         (ws_in == nullptr || opt.sync_bytes >= (size_t)nw * sizeof(int))) {
       int* words = opt.sync;

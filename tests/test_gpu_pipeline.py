@@ -133,3 +133,29 @@ def test_wy_units_equal_launch_schedule(torch_dev, dt, n, nbw, k, nev):
                                      np.asfortranarray(z.astype(wide)), n, nbw)
         assert checks.max_rel_err(q.cpu().numpy().astype(wide), want) <= (
             5e-5 if dt == "r32" else TOL)
+
+
+@pytest.mark.parametrize("many", [False, True])
+def test_complex_wy_leaves_large_calls_to_the_launch_schedule(torch_dev, many):
+    """Complex calls of path WY run in one launch up to 28 units (64 columns of
+    a sweep block) per compute unit; past that the diagonal launches, which are
+    faster there."""
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    n, nbw, k = 6000, 64, 48
+    blocks = -(-(n - 1) // k)
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    nev = 64 * (28 * cus // blocks) + (1 if many else 0)
+    q, hh, tau = drawn(torch, dev, n, nbw, nev, 7400)
+    hh, tau = hh.to(torch.complex128), tau.to(torch.complex128)
+    q = q.t().to(torch.complex128).t()
+    P.profile_enable(True)
+    try:
+        P.hh_trafo(q, hh, tau, nbw)
+        pr = P.profile_last()
+    finally:
+        P.profile_enable(False)
+    torch.cuda.synchronize()
+    print(f"complex n={n} nev={nev}: {pr}", flush=True)
+    assert (pr["path"], pr["k"]) == (P.PATH_WY, k)
+    assert (pr["launches"] > 1) == many
