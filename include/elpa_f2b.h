@@ -36,9 +36,23 @@ extern "C" {
  * library allocates a workspace in stream order.  Returns ELPA_OK or
  * ELPA_ERR_ARG / _DTYPE / _ALIGN / _NOMEM / _DEVICE (elpa_hh.h); arguments
  * are checked before anything is enqueued; n <= nbw leaves A as it is.
+ * Bands with nbw <= 64: the workgroups of a panel exchange sums while they run.
+ * A wait of more than 20 s (none is known to happen: they start only once all
+ * are there) is given up, and tau and A's diagonal are set to NaN.
  */
 int elpa_full_to_band(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int64_t ldv,
                       void *tau, int32_t dtype, void *stream);
+
+/*
+ * For tests: elpa_full_to_band with the time that a panel's workgroups have to
+ * come together, in ticks of the 100 MHz clock (negative: none comes together),
+ * and the limit of a wait (0: given up at the second look).
+ */
+int elpa_full_to_band_gather(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int64_t ldv,
+                             void *tau, int32_t dtype, void *stream, int64_t gather_ticks);
+int elpa_full_to_band_limits(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int64_t ldv,
+                             void *tau, int32_t dtype, void *stream, int64_t gather_ticks,
+                             int64_t wait_ticks);
 
 #ifdef __cplusplus
 }

@@ -271,6 +271,7 @@ __global__ __launch_bounds__(kRows) void k_update(E* __restrict__ A, int64_t lda
 // ---------------------------------------------------------------------------
 constexpr int kOpen = 0, kGo = 1, kAlone = 2;
 constexpr int64_t kSmall = 64;  // reflectors of k_small_factors
+constexpr int kCtl = 32;  // words before the slots
 constexpr int kMaxGroups = 256;                       // one per compute unit
 constexpr int64_t kGatherTicks = 10000000;            // 0.1 s of the 100 MHz clock
 constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // never reached once all are resident
@@ -381,16 +382,16 @@ struct Words {
     for (int i = 0; i < NWORD; ++i) ok = ok && (unsigned)(w[i] >> 32) == tag;
     return ok;
   }
-  __device__ __forceinline__ void wait(const u64* p, unsigned tag) {
+  // The wait is given up after `limit` ticks; the lane's later ones end at the
+  // first miss then (limit -1).
+  __device__ __forceinline__ void wait(const u64* p, unsigned tag, int64_t& limit) {
     if (has(tag)) return;
     const int64_t t0 = (int64_t)wall_clock64();
     do {
-#pragma unroll 1
-      for (int k = 0; k < 1024; ++k) {
-        load(p);
-        if (has(tag)) return;
-      }
-    } while ((int64_t)wall_clock64() - t0 < kWaitTicks);
+      load(p);
+      if (has(tag)) return;
+    } while ((int64_t)wall_clock64() - t0 < limit);
+    limit = -1;
   }
   __device__ __forceinline__ void get(double& x) const {
     x = __hiloint2double((int)(unsigned)w[1], (int)(unsigned)w[0]);
@@ -431,7 +432,8 @@ struct Panel {
   E* V;
   int64_t ldv;
   E* tau;
-  u64* slots;   // [2][groups + 1][4 CW][words]: the groups' sums, then the head row
+  u64* slots;   // [2][groups + 1][4 CW][words]: the groups' sums, then the head row;
+                // before them kCtl words: whether a wait was given up, their limit
   int* state;   // arrived, state
   int groups;
   unsigned tag0;
@@ -453,13 +455,31 @@ __device__ __forceinline__ u64* slot_of(const Panel<E>& P, unsigned tag, int g, 
 
 __global__ __launch_bounds__(256) void k_panel_clear(u64* __restrict__ slots, int64_t words,
                                                      int* __restrict__ state, int64_t states,
-                                                     int open) {
+                                                     int open, int64_t limit) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
        i += (int64_t)gridDim.x * blockDim.x)
     slots[i] = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < states;
        i += (int64_t)gridDim.x * blockDim.x)
     state[i] = (i & 1) ? open : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    slots[-kCtl] = 0;
+    slots[-kCtl + 1] = (u64)limit;
+  }
+}
+
+// A call in which a wait was given up has no result: tau and the band's diagonal
+// are set to NaN.
+template <typename E>
+__global__ __launch_bounds__(256) void k_failed_out(E* __restrict__ A, int64_t lda, int64_t n,
+                                                    E* __restrict__ tau, int64_t N,
+                                                    const u64* __restrict__ failed) {
+  if (*failed == 0) return;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    A[i + i * lda] = from_re<E>(__builtin_nan(""));
+    if (i < N) tau[i] = from_re<E>(__builtin_nan(""));
+  }
 }
 
 // One wave's share of a workgroup's sums for one column: x its rows of the
@@ -493,6 +513,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
   if (G > 1) {
     if (tid == 0) {
       int st = __hip_atomic_load(P.state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (P.slots[-kCtl] != 0) st = kAlone;  // an earlier panel failed: no more
       if (st == kOpen) {
         const int old = __hip_atomic_fetch_add(P.state, 1, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
@@ -527,6 +548,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
     }
 
   int gone = 0;  // of this wave's columns
+  int64_t limit = (int64_t)P.slots[-kCtl + 1];
   for (int i = 0; i < P.k; ++i) {
     const bool own = (i & 3) == wave;
     const unsigned tag = P.tag0 + (unsigned)i;
@@ -569,7 +591,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (g0 + u * SUB < G) {
-            w[u].wait(slot_of<E, CW>(P, tag, g0 + u * SUB, at), tag);
+            w[u].wait(slot_of<E, CW>(P, tag, g0 + u * SUB, at), tag, limit);
             E y;
             w[u].get(y);
             acc = Num<E>::add(acc, y);
@@ -577,7 +599,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
       }
       S = lane_sum<CW>(acc);
       if (grp != 0) {
-        hw.wait(slot_of<E, CW>(P, tag, G, at), tag);
+        hw.wait(slot_of<E, CW>(P, tag, G, at), tag, limit);
         hw.get(head);
       }
     }
@@ -629,6 +651,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
       }
     }
   }
+  if (limit < 0) P.slots[-kCtl] = 1;
   // zeros below the diagonal of the reduced columns; a panel with fewer rows
   // than columns has all its rows written above
   int first = lane;
@@ -650,6 +673,7 @@ __global__ __launch_bounds__(256, 1) void k_panel_alone(Panel<E> P) {
   constexpr int SUB = 64 / CW;
   __shared__ E sh[2];
   if (__hip_atomic_load(P.state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kGo) return;
+  if (P.slots[-kCtl] != 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cl = lane / SUB, part = lane % SUB;
@@ -888,7 +912,7 @@ __global__ __launch_bounds__(256) void k_scale(E* __restrict__ W, int64_t ld, in
 
 template <typename E>
 int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipStream_t st,
-        int64_t gather_ticks) {
+        int64_t gather_ticks, int64_t wait_ticks) {
   using S = typename std::conditional<std::is_same<E, float>::value, float, double>::type;
   const size_t es = sizeof(E);
   const int64_t mmax = n - b;
@@ -913,7 +937,7 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
   constexpr int ROWS = PanelTraits<E>::ROWS, NWORD = PanelTraits<E>::NWORD;
   const int64_t groups = b <= 64 ? std::min<int64_t>((mmax + ROWS - 1) / ROWS, kMaxGroups) : 0;
   const int64_t words = 2 * (groups + 1) * 64 * NWORD, panels = (n - 1) / b;
-  const size_t off_state = off_slot + al((size_t)words * 8), total = off_state + al((size_t)panels * 8);
+  const size_t off_state = off_slot + al((size_t)(kCtl + words) * 8), total = off_state + al((size_t)panels * 8);
   char* ws = nullptr;
   if (hipMallocAsync((void**)&ws, total, st) != hipSuccess) return ELPA_ERR_NOMEM;
   double* pn0 = (double*)(ws + off_pn);
@@ -924,12 +948,12 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
   E* W1 = (E*)(ws + off_w1);
   E* W2 = (E*)(ws + off_w2);
   E* part = (E*)(ws + off_part);
-  u64* slots = (u64*)(ws + off_slot);
+  u64* slots = (u64*)(ws + off_slot) + kCtl;
   int* states = (int*)(ws + off_state);
   if (groups > 0)
     hipLaunchKernelGGL(k_panel_clear, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 256)),
                        dim3(256), 0, st, slots, words, states, 2 * panels,
-                       gather_ticks < 0 ? kAlone : kOpen);
+                       gather_ticks < 0 ? kAlone : kOpen, wait_ticks);
   int rc = ELPA_OK;
   {
     std::lock_guard<std::mutex> lock(ebt::Handles::get().mu);
@@ -1054,6 +1078,11 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
       if (!ok || hipGetLastError() != hipSuccess) rc = ELPA_ERR_DEVICE;
     }
   }
+  if (groups > 1) {
+    hipLaunchKernelGGL(k_failed_out<E>, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)),
+                       dim3(256), 0, st, A, lda, n, tau, mmax, (const u64*)(slots - kCtl));
+    if (rc == ELPA_OK && hipGetLastError() != hipSuccess) rc = ELPA_ERR_DEVICE;
+  }
   const hipError_t e2 = hipFreeAsync(ws, st);
   if (rc == ELPA_OK && e2 != hipSuccess) rc = ELPA_ERR_DEVICE;
   return rc;
@@ -1063,12 +1092,9 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 }  // namespace ef2b
 
-// elpa_full_to_band with the time a one-launch panel's workgroups have to come
-// together, in ticks of the 100 MHz clock (negative: every panel that needs
-// several workgroups is done by one; the tests reach that path this way).
-extern "C" int elpa_full_to_band_gather(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
+extern "C" int elpa_full_to_band_limits(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
                                         int64_t ldv, void* tau, int32_t dtype, void* stream,
-                                        int64_t gather_ticks) {
+                                        int64_t gather_ticks, int64_t wait_ticks) {
   if (dtype != ELPA_R64 && dtype != ELPA_C64) return ELPA_ERR_DTYPE;
   if (n < 1 || nbw < 1 || nbw > ef2b::kMaxNb || lda < n || ldv < n) return ELPA_ERR_ARG;
   if (!A) return ELPA_ERR_ARG;
@@ -1080,9 +1106,16 @@ extern "C" int elpa_full_to_band_gather(int64_t n, int64_t nbw, void* A, int64_t
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (dtype == ELPA_R64)
     return ef2b::run<double>(n, nbw, (double*)A, lda, (double*)V, ldv, (double*)tau, st,
-                             gather_ticks);
+                             gather_ticks, wait_ticks);
   return ef2b::run<ebt::zc>(n, nbw, (ebt::zc*)A, lda, (ebt::zc*)V, ldv, (ebt::zc*)tau, st,
-                            gather_ticks);
+                            gather_ticks, wait_ticks);
+}
+
+extern "C" int elpa_full_to_band_gather(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
+                                        int64_t ldv, void* tau, int32_t dtype, void* stream,
+                                        int64_t gather_ticks) {
+  return elpa_full_to_band_limits(n, nbw, A, lda, V, ldv, tau, dtype, stream, gather_ticks,
+                                  ef2b::kWaitTicks);
 }
 
 extern "C" int elpa_full_to_band(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,

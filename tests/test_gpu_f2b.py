@@ -132,3 +132,37 @@ def test_f2b_panel_workgroups(torch_dev, n, b, alone, cplx):
     read = ~np.isnan(V0)  # the entries below the unit leads
     assert np.max(np.abs(v.cpu().numpy()[:, :n - b] - V0)[read], initial=0.0) <= 1e-10
     assert np.max(np.abs(tau.cpu().numpy() - t0)) <= 1e-10
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+def test_f2b_given_up_wait_is_marked(torch_dev, cplx):
+    """Waits between a panel's workgroups given up at the second look (a limit
+    that the host sets): the call ends, and tau and the diagonal are NaN; the
+    next call, with the usual limit, is whole."""
+    import ctypes as C
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    n, b = 2500, 64
+    fn = P.library().elpa_full_to_band_limits
+    fn.argtypes = [C.c_int64, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p,
+                   C.c_int32, C.c_void_p, C.c_int64, C.c_int64]
+    g = torch.Generator(device=dev)
+    g.manual_seed(540)
+    x = torch.randn((n, n), generator=g, device=dev, dtype=torch.float64)
+    if cplx:
+        x = torch.complex(x, torch.randn((n, n), generator=g, device=dev, dtype=torch.float64))
+    A = ((x + x.mH) / 2).t()
+    for limit in (0, 10 ** 9):
+        a = A.clone()
+        v = torch.zeros((n - b, n), dtype=a.dtype, device=dev).t()
+        tau = torch.zeros(n - b, dtype=a.dtype, device=dev)
+        print(f"f2b wait limit {limit} cplx={cplx}", flush=True)
+        rc = fn(n, b, a.data_ptr(), n, v.data_ptr(), n, tau.data_ptr(), P.C64 if cplx else P.R64,
+                None, 10 ** 7, limit)
+        torch.cuda.synchronize()
+        assert rc == 0, rc
+        bad = torch.isnan(tau.real), torch.isnan(a.diagonal().real)
+        if limit == 0:
+            assert bool(bad[0].all()) and bool(bad[1].all())
+        else:
+            assert not bool(bad[0].any()) and not bool(bad[1].any())
