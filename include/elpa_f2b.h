@@ -45,14 +45,18 @@ int elpa_full_to_band(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int
 
 /*
  * For tests: elpa_full_to_band with the time that a panel's workgroups have to
- * come together, in ticks of the 100 MHz clock (negative: none comes together),
- * and the limit of a wait (0: given up at the second look).
+ * come together, in ticks of the 100 MHz clock (negative: they do not), the
+ * limit of a wait (0: given up at the second look), and the most workgroups of a
+ * panel that did not come together (0: one per 256 rows, complex 128).
  */
 int elpa_full_to_band_gather(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int64_t ldv,
                              void *tau, int32_t dtype, void *stream, int64_t gather_ticks);
 int elpa_full_to_band_limits(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int64_t ldv,
                              void *tau, int32_t dtype, void *stream, int64_t gather_ticks,
                              int64_t wait_ticks);
+int elpa_full_to_band_crew(int64_t n, int64_t nbw, void *A, int64_t lda, void *V, int64_t ldv,
+                           void *tau, int32_t dtype, void *stream, int64_t gather_ticks,
+                           int64_t wait_ticks, int64_t crew);
 
 #ifdef __cplusplus
 }

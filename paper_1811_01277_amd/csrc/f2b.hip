@@ -258,10 +258,11 @@ __global__ __launch_bounds__(kRows) void k_update(E* __restrict__ A, int64_t lda
 //
 // Waiting ends because all workgroups of the launch are resident together:
 // each first registers, and only when all have done so does any of them start
-// (state kGo).  Should they not come together within the time limit (the
-// device full of others that wait in the same way), the launch leaves the
-// panel as it was (state kAlone) and k_panel_alone, next on the stream, does
-// it with one workgroup and the same arithmetic.
+// (state kGo).  Should they not come together within a millisecond (the device
+// full of other work), the launch leaves the panel as it was (state kApart) and
+// k_panel_crew, next on the stream, does it with as many workgroups as there is
+// room for and the same arithmetic.  Panels of more workgroups than the device
+// holds at all take the two launches per column.
 //
 // Bound: latency, about two microseconds a column for any number of rows up to
 // kMaxGroups workgroups, half of it the exchange.  Two launches per column (a
@@ -269,11 +270,13 @@ __global__ __launch_bounds__(kRows) void k_update(E* __restrict__ A, int64_t lda
 // reduction went from 22.6 to 4.7 ms at n = 1000 and from 100 to 28 ms at
 // n = 4000 (nbw = 64, fp64).
 // ---------------------------------------------------------------------------
-constexpr int kOpen = 0, kGo = 1, kAlone = 2;
+constexpr int kOpen = 0, kGo = 1, kApart = 2;
 constexpr int64_t kSmall = 64;  // reflectors of k_small_factors
 constexpr int kCtl = 32;  // words before the slots
-constexpr int kMaxGroups = 256;                       // one per compute unit
-constexpr int64_t kGatherTicks = 10000000;            // 0.1 s of the 100 MHz clock
+constexpr int kMaxGroups = 256;               // every workgroup reads every other's sums
+constexpr int64_t kGatherTicks = 100000;      // 1 ms of the 100 MHz clock, some five panels
+constexpr int64_t kCrewTicks = 10000;         // 0.1 ms
+constexpr int kClosed = 1 << 30;              // of a crew's count
 constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // never reached once all are resident
 
 template <int CTRL>
@@ -355,6 +358,25 @@ __device__ __forceinline__ zc read_lane(zc x, int l) {
   return zc{read_lane(x.re, l), read_lane(x.im, l)};
 }
 
+// Products with every rounding written out, so that all forms of a panel give the
+// same bits: acc + conj(x) a, y - v w, a b.
+__device__ __forceinline__ double dot_step(double x, double a, double acc) {
+  return __builtin_fma(x, a, acc);
+}
+__device__ __forceinline__ zc dot_step(zc x, zc a, zc acc) {
+  return zc{__builtin_fma(x.re, a.re, __builtin_fma(x.im, a.im, acc.re)),
+            __builtin_fma(x.re, a.im, __builtin_fma(-x.im, a.re, acc.im))};
+}
+__device__ __forceinline__ double update(double y, double v, double w) {
+  return __builtin_fma(-v, w, y);
+}
+__device__ __forceinline__ zc update(zc y, zc v, zc w) {
+  return zc{__builtin_fma(-v.re, w.re, __builtin_fma(v.im, w.im, y.re)),
+            __builtin_fma(-v.re, w.im, __builtin_fma(-v.im, w.re, y.im))};
+}
+__device__ __forceinline__ double times(double a, double b) { return a * b; }
+__device__ __forceinline__ zc times(zc a, zc b) { return update(zc{0.0, 0.0}, zc{-a.re, -a.im}, b); }
+
 typedef unsigned long long u64;
 // a value as tagged words (2 per double)
 __device__ __forceinline__ void send(u64* p, double x, unsigned tag) {
@@ -434,7 +456,7 @@ struct Panel {
   E* tau;
   u64* slots;   // [2][groups + 1][4 CW][words]: the groups' sums, then the head row;
                 // before them kCtl words: whether a wait was given up, their limit
-  int* state;   // arrived, state
+  int* state;   // arrived, state, crew's count
   int groups;
   unsigned tag0;
   int64_t gather_ticks;
@@ -461,7 +483,7 @@ __global__ __launch_bounds__(256) void k_panel_clear(u64* __restrict__ slots, in
     slots[i] = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < states;
        i += (int64_t)gridDim.x * blockDim.x)
-    state[i] = (i & 1) ? open : 0;
+    state[i] = (i & 3) == 1 ? open : 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     slots[-kCtl] = 0;
     slots[-kCtl + 1] = (u64)limit;
@@ -489,17 +511,48 @@ __device__ __forceinline__ E panel_sums(const E (&a)[RT][CW], const E (&x)[RT]) 
   E p[CW];
 #pragma unroll
   for (int c = 0; c < CW; ++c) {
-    p[c] = Num<E>::mul(conj_(x[0]), a[0][c]);
+    p[c] = from_re<E>(0.0);
 #pragma unroll
-    for (int t = 1; t < RT; ++t) p[c] = Num<E>::add(p[c], Num<E>::mul(conj_(x[t]), a[t][c]));
+    for (int t = 0; t < RT; ++t) p[c] = dot_step(x[t], a[t][c], p[c]);
   }
   return wave_sums<CW>(p);
+}
+
+// The sums of all groups and, for those without the head row, its entry: lane
+// (column, part) adds the groups part, part + SUB, ...; a batch of loads in flight
+// at once.
+template <typename E, int CW>
+__device__ __forceinline__ void panel_gather(const Panel<E>& P, unsigned tag, int at, int part,
+                                             bool far, E& S, E& head, int64_t& limit) {
+  constexpr int NWORD = PanelTraits<E>::NWORD, SUB = 64 / CW, U = 4;
+  const int G = P.groups;
+  Words<NWORD> hw;
+  if (far) hw.load(slot_of<E, CW>(P, tag, G, at));
+  E acc = from_re<E>(0.0);
+  for (int g0 = part; g0 < G; g0 += U * SUB) {
+    Words<NWORD> w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + u * SUB < G) w[u].load(slot_of<E, CW>(P, tag, g0 + u * SUB, at));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + u * SUB < G) {
+        w[u].wait(slot_of<E, CW>(P, tag, g0 + u * SUB, at), tag, limit);
+        E y;
+        w[u].get(y);
+        acc = Num<E>::add(acc, y);
+      }
+  }
+  S = lane_sum<CW>(acc);
+  if (far) {
+    hw.wait(slot_of<E, CW>(P, tag, G, at), tag, limit);
+    hw.get(head);
+  }
 }
 
 template <typename E, int CW>
 __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
   constexpr int RT = PanelTraits<E>::RT, ROWS = PanelTraits<E>::ROWS;
-  constexpr int NWORD = PanelTraits<E>::NWORD;
   constexpr int SUB = 64 / CW;  // lanes per column
   __shared__ E xs[ROWS];
   __shared__ E sh[2];
@@ -513,7 +566,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
   if (G > 1) {
     if (tid == 0) {
       int st = __hip_atomic_load(P.state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (P.slots[-kCtl] != 0) st = kAlone;  // an earlier panel failed: no more
+      if (P.slots[-kCtl] != 0) st = kApart;  // an earlier panel failed: no more
       if (st == kOpen) {
         const int old = __hip_atomic_fetch_add(P.state, 1, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
@@ -526,7 +579,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
                                        __HIP_MEMORY_SCOPE_AGENT)) == kOpen) {
           if ((int64_t)wall_clock64() - t0 > P.gather_ticks) {
             expect = kOpen;
-            __hip_atomic_compare_exchange_strong(P.state + 1, &expect, kAlone, __ATOMIC_RELAXED,
+            __hip_atomic_compare_exchange_strong(P.state + 1, &expect, kApart, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
@@ -577,31 +630,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
       const int at = wave * CW + cl;
       if (part == 0) send(slot_of<E, CW>(P, tag, grp, at), S, tag);
       if (grp == 0 && part == 1) send(slot_of<E, CW>(P, tag, G, at), head, tag);
-      // lane (cl, part) adds the groups part, part + SUB, ...; a batch of loads
-      // in flight at once
-      constexpr int U = 4;
-      Words<NWORD> hw;
-      if (grp != 0) hw.load(slot_of<E, CW>(P, tag, G, at));
-      E acc = from_re<E>(0.0);
-      for (int g0 = part; g0 < G; g0 += U * SUB) {
-        Words<NWORD> w[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (g0 + u * SUB < G) w[u].load(slot_of<E, CW>(P, tag, g0 + u * SUB, at));
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (g0 + u * SUB < G) {
-            w[u].wait(slot_of<E, CW>(P, tag, g0 + u * SUB, at), tag, limit);
-            E y;
-            w[u].get(y);
-            acc = Num<E>::add(acc, y);
-          }
-      }
-      S = lane_sum<CW>(acc);
-      if (grp != 0) {
-        hw.wait(slot_of<E, CW>(P, tag, G, at), tag, limit);
-        hw.get(head);
-      }
+      panel_gather<E, CW>(P, tag, at, part, grp != 0, S, head, limit);
     }
     if (own) {  // lane 0 holds column i's sum and head
       E tv, sc;
@@ -619,12 +648,12 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
     __syncthreads();
     const E tv = sh[0], sc = sh[1];
     // coefficient of this lane's column: conj(tau) v^H a_j
-    const E cw = Num<E>::mul(conj_(tv), Num<E>::add(head, Num<E>::mul(conj_(sc), S)));
+    const E cw = times(conj_(tv), dot_step(sc, S, head));
     E v[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const int64_t row = row0 + lane + 64 * t;
-      v[t] = row == i ? from_re<E>(1.0) : Num<E>::mul(x[t], sc);
+      v[t] = row == i ? from_re<E>(1.0) : times(x[t], sc);
       if (own && row < P.m) P.V[P.r0 + row + (P.p + i) * P.ldv] = v[t];
     }
     // row i of the result (v = 1 there), columns right of i
@@ -637,7 +666,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
       for (int c = 1; c < CW; ++c) {
         const E w = read_lane(cw, c * SUB);
 #pragma unroll
-        for (int t = 0; t < RT; ++t) a[t][c - 1] = sub(a[t][c], Num<E>::mul(v[t], w));
+        for (int t = 0; t < RT; ++t) a[t][c - 1] = update(a[t][c], v[t], w);
       }
 #pragma unroll
       for (int t = 0; t < RT; ++t) a[t][CW - 1] = from_re<E>(0.0);
@@ -647,7 +676,7 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
       for (int c = 0; c < CW; ++c) {
         const E w = read_lane(cw, c * SUB);
 #pragma unroll
-        for (int t = 0; t < RT; ++t) a[t][c] = sub(a[t][c], Num<E>::mul(v[t], w));
+        for (int t = 0; t < RT; ++t) a[t][c] = update(a[t][c], v[t], w);
       }
     }
   }
@@ -665,23 +694,60 @@ __global__ __launch_bounds__(256, 1) void k_panel(Panel<E> P) {
     }
 }
 
-// The panel by one workgroup, where k_panel's workgroups did not come together
-// (no work otherwise): the same sums in the same order, the panel in A.
+// The panel by a crew, where k_panel's workgroups did not come together (no work
+// otherwise): the workgroups that are there when the last of them or the first
+// whose time is up closes the count.  Later ones return, so all of the crew are
+// running and their waits end as above.  Workgroup w of c does the groups w,
+// w + c, ... with the panel in A: the same sums, sent and added in the same order.
+// Per column two passes over the rows.  The reduction at n = 4000 / 12000, nbw = 64,
+// fp64, with every panel done this way by as many workgroups as it has groups: 50 /
+// 252 ms, where panels together take 19.1 / 152; two launches per column took 100 /
+// 468, and all the panels' rows on one workgroup 245 ms at n = 4000.
 template <typename E, int CW>
-__global__ __launch_bounds__(256, 1) void k_panel_alone(Panel<E> P) {
+__global__ __launch_bounds__(256, 1) void k_panel_crew(Panel<E> P) {
   constexpr int RT = PanelTraits<E>::RT, ROWS = PanelTraits<E>::ROWS;
   constexpr int SUB = 64 / CW;
   __shared__ E sh[2];
+  __shared__ int sh_me, sh_crew;
   if (__hip_atomic_load(P.state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kGo) return;
   if (P.slots[-kCtl] != 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cl = lane / SUB, part = lane % SUB;
+  if (tid == 0) {
+    int* const count = P.state + 2;
+    int v = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), me = -1;
+    while (me < 0 && !(v & kClosed))
+      if (__hip_atomic_compare_exchange_strong(count, &v, v + 1, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        me = v;
+    if (me >= 0) {
+      const int64_t t0 = (int64_t)wall_clock64();
+      while (!((v = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) &
+               kClosed))
+        if (v == (int)gridDim.x || (int64_t)wall_clock64() - t0 > kCrewTicks)
+          __hip_atomic_fetch_or(count, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    sh_me = me;
+    sh_crew = v & ~kClosed;
+  }
+  __syncthreads();
+  const int me = __builtin_amdgcn_readfirstlane(sh_me);
+  const int crew = __builtin_amdgcn_readfirstlane(sh_crew);
+  if (me < 0) return;
+  const int at = wave * CW + cl;
+  int64_t limit = (int64_t)P.slots[-kCtl + 1];
   for (int i = 0; i < P.k; ++i) {
     const bool own = (i & 3) == wave;
     const int gone = i > wave ? (i - wave + 3) / 4 : 0;
-    E acc = from_re<E>(0.0);
-    for (int g = 0; g < P.groups; ++g) {
+    const unsigned tag = P.tag0 + (unsigned)i;
+    const int jl = 4 * (cl + gone) + wave;
+    E head = from_re<E>(0.0), S;
+    if (me == 0) {
+      if (jl < P.b) head = P.A[P.r0 + i + (P.p + jl) * P.lda];
+      if (part == 1) send(slot_of<E, CW>(P, tag, P.groups, at), head, tag);
+    }
+    for (int g = me; g < P.groups; g += crew) {
       E a[RT][CW], x[RT];
 #pragma unroll
       for (int t = 0; t < RT; ++t) {
@@ -694,12 +760,10 @@ __global__ __launch_bounds__(256, 1) void k_panel_alone(Panel<E> P) {
                                            : from_re<E>(0.0);
         }
       }
-      const E S = panel_sums<E, RT, CW>(a, x);
-      if (g % SUB == part) acc = Num<E>::add(acc, S);
+      S = panel_sums<E, RT, CW>(a, x);
+      if (part == 0) send(slot_of<E, CW>(P, tag, g, at), S, tag);
     }
-    const E S = lane_sum<CW>(acc);
-    const int jl = 4 * (cl + gone) + wave;
-    const E head = jl < P.b ? P.A[P.r0 + i + (P.p + jl) * P.lda] : from_re<E>(0.0);
+    panel_gather<E, CW>(P, tag, at, part, me != 0, S, head, limit);
     double beta = 0.0;
     if (own) {
       E tv, sc;
@@ -707,35 +771,48 @@ __global__ __launch_bounds__(256, 1) void k_panel_alone(Panel<E> P) {
       if (lane == 0) {
         sh[0] = tv;
         sh[1] = sc;
-        P.tau[P.p + i] = tv;
+        if (me == 0) P.tau[P.p + i] = tv;
       }
     }
     __syncthreads();
     const E tv = sh[0], sc = sh[1];
-    const E cw = Num<E>::mul(conj_(tv), Num<E>::add(head, Num<E>::mul(conj_(sc), S)));
+    const E cw = times(conj_(tv), dot_step(sc, S, head));
     E w[CW];
 #pragma unroll
     for (int c = 0; c < CW; ++c) w[c] = read_lane(cw, c * SUB);
-    for (int64_t row = lane; row < P.m; row += 64) {
-      const E x = P.A[P.r0 + row + (P.p + i) * P.lda];
-      const E v = row == i ? from_re<E>(1.0) : (row > i ? Num<E>::mul(x, sc) : from_re<E>(0.0));
-      if (own) P.V[P.r0 + row + (P.p + i) * P.ldv] = v;
+    for (int g = me; g < P.groups; g += crew)
+#pragma unroll 1
+      for (int t = 0; t < RT; ++t) {
+        const int64_t row = (int64_t)g * ROWS + lane + 64 * t;
+        if (row >= P.m) continue;
+        const E x = P.A[P.r0 + row + (P.p + i) * P.lda];
+        const E v = row == i ? from_re<E>(1.0) : (row > i ? times(x, sc) : from_re<E>(0.0));
+        if (own) P.V[P.r0 + row + (P.p + i) * P.ldv] = v;
+        if (row < i) continue;
+        E y[CW];
 #pragma unroll
-      for (int c = 0; c < CW; ++c) {
-        const int j = 4 * (c + gone) + wave;
-        if (j > i && j < P.b && row >= i) {
-          E& y = P.A[P.r0 + row + (P.p + j) * P.lda];
-          y = sub(y, Num<E>::mul(v, w[c]));
+        for (int c = 0; c < CW; ++c) {
+          const int j = 4 * (c + gone) + wave;
+          if (j > i && j < P.b) y[c] = P.A[P.r0 + row + (P.p + j) * P.lda];
+        }
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          const int j = 4 * (c + gone) + wave;
+          if (j > i && j < P.b)
+            P.A[P.r0 + row + (P.p + j) * P.lda] = update(y[c], v, w[c]);
         }
       }
-    }
     __syncthreads();
     if (own)
-      for (int64_t row = lane; row < P.m; row += 64)
-        if (row >= i)
-          P.A[P.r0 + row + (P.p + i) * P.lda] = from_re<E>(row == i ? beta : 0.0);
+      for (int g = me; g < P.groups; g += crew)
+        for (int t = 0; t < RT; ++t) {
+          const int64_t row = (int64_t)g * ROWS + lane + 64 * t;
+          if (row >= i && row < P.m)
+            P.A[P.r0 + row + (P.p + i) * P.lda] = from_re<E>(row == i ? beta : 0.0);
+        }
     __syncthreads();
   }
+  if (limit < 0) P.slots[-kCtl] = 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -912,7 +989,7 @@ __global__ __launch_bounds__(256) void k_scale(E* __restrict__ W, int64_t ld, in
 
 template <typename E>
 int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipStream_t st,
-        int64_t gather_ticks, int64_t wait_ticks) {
+        int64_t gather_ticks, int64_t wait_ticks, int64_t crew) {
   using S = typename std::conditional<std::is_same<E, float>::value, float, double>::type;
   const size_t es = sizeof(E);
   const int64_t mmax = n - b;
@@ -936,8 +1013,19 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
   // one-launch panels: their exchange slots and per-panel states
   constexpr int ROWS = PanelTraits<E>::ROWS, NWORD = PanelTraits<E>::NWORD;
   const int64_t groups = b <= 64 ? std::min<int64_t>((mmax + ROWS - 1) / ROWS, kMaxGroups) : 0;
+  // the most workgroups of a panel: what an idle device holds at once
+  int64_t most = std::min<int64_t>(groups, 1);
+  if (groups > 1) {
+    const auto panel = b > 32 ? k_panel<E, 16> : k_panel<E, 8>;
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void*>(panel), 256, 0) == hipSuccess)
+      most = std::max<int64_t>(1, std::min<int64_t>(groups, (int64_t)cus * per_cu));
+  }
   const int64_t words = 2 * (groups + 1) * 64 * NWORD, panels = (n - 1) / b;
-  const size_t off_state = off_slot + al((size_t)(kCtl + words) * 8), total = off_state + al((size_t)panels * 8);
+  const size_t off_state = off_slot + al((size_t)(kCtl + words) * 8), total = off_state + al((size_t)panels * 16);
   char* ws = nullptr;
   if (hipMallocAsync((void**)&ws, total, st) != hipSuccess) return ELPA_ERR_NOMEM;
   double* pn0 = (double*)(ws + off_pn);
@@ -952,8 +1040,8 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
   int* states = (int*)(ws + off_state);
   if (groups > 0)
     hipLaunchKernelGGL(k_panel_clear, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 256)),
-                       dim3(256), 0, st, slots, words, states, 2 * panels,
-                       gather_ticks < 0 ? kAlone : kOpen, wait_ticks);
+                       dim3(256), 0, st, slots, words, states, 4 * panels,
+                       gather_ticks < 0 ? kApart : kOpen, wait_ticks);
   int rc = ELPA_OK;
   {
     std::lock_guard<std::mutex> lock(ebt::Handles::get().mu);
@@ -964,9 +1052,9 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
     for (int64_t p = 0; rc == ELPA_OK && p + b < n; p += b) {
       const int64_t r0 = p + b, m = n - r0, k = std::min(b, m);
       const int64_t wide = (m + ROWS - 1) / ROWS;  // workgroups of a one-launch panel
-      if (b <= 64 && wide <= kMaxGroups) {
+      if (b <= 64 && wide <= most) {
         const Panel<E> P{A,     lda, r0,    p, m, (int)b, (int)k, V, ldv,
-                         tau,   slots, states + 2 * (p / b), (int)wide, (unsigned)(p + 1),
+                         tau,   slots, states + 4 * (p / b), (int)wide, (unsigned)(p + 1),
                          gather_ticks};
         const dim3 g((unsigned)wide), t(256);
         if (b > 32)
@@ -974,10 +1062,11 @@ int run(int64_t n, int64_t b, E* A, int64_t lda, E* V, int64_t ldv, E* tau, hipS
         else
           hipLaunchKernelGGL((k_panel<E, 8>), g, t, 0, st, P);
         if (wide > 1) {
+          const dim3 gc((unsigned)(crew > 0 ? std::min(crew, wide) : wide));
           if (b > 32)
-            hipLaunchKernelGGL((k_panel_alone<E, 16>), dim3(1), t, 0, st, P);
+            hipLaunchKernelGGL((k_panel_crew<E, 16>), gc, t, 0, st, P);
           else
-            hipLaunchKernelGGL((k_panel_alone<E, 8>), dim3(1), t, 0, st, P);
+            hipLaunchKernelGGL((k_panel_crew<E, 8>), gc, t, 0, st, P);
         }
       } else {
         const int G = (int)((m + kRows - 1) / kRows);
@@ -1092,9 +1181,9 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 }  // namespace ef2b
 
-extern "C" int elpa_full_to_band_limits(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
-                                        int64_t ldv, void* tau, int32_t dtype, void* stream,
-                                        int64_t gather_ticks, int64_t wait_ticks) {
+extern "C" int elpa_full_to_band_crew(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
+                                      int64_t ldv, void* tau, int32_t dtype, void* stream,
+                                      int64_t gather_ticks, int64_t wait_ticks, int64_t crew) {
   if (dtype != ELPA_R64 && dtype != ELPA_C64) return ELPA_ERR_DTYPE;
   if (n < 1 || nbw < 1 || nbw > ef2b::kMaxNb || lda < n || ldv < n) return ELPA_ERR_ARG;
   if (!A) return ELPA_ERR_ARG;
@@ -1106,9 +1195,16 @@ extern "C" int elpa_full_to_band_limits(int64_t n, int64_t nbw, void* A, int64_t
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (dtype == ELPA_R64)
     return ef2b::run<double>(n, nbw, (double*)A, lda, (double*)V, ldv, (double*)tau, st,
-                             gather_ticks, wait_ticks);
+                             gather_ticks, wait_ticks, crew);
   return ef2b::run<ebt::zc>(n, nbw, (ebt::zc*)A, lda, (ebt::zc*)V, ldv, (ebt::zc*)tau, st,
-                            gather_ticks, wait_ticks);
+                            gather_ticks, wait_ticks, crew);
+}
+
+extern "C" int elpa_full_to_band_limits(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,
+                                        int64_t ldv, void* tau, int32_t dtype, void* stream,
+                                        int64_t gather_ticks, int64_t wait_ticks) {
+  return elpa_full_to_band_crew(n, nbw, A, lda, V, ldv, tau, dtype, stream, gather_ticks,
+                                wait_ticks, 0);
 }
 
 extern "C" int elpa_full_to_band_gather(int64_t n, int64_t nbw, void* A, int64_t lda, void* V,

@@ -166,3 +166,37 @@ def test_f2b_given_up_wait_is_marked(torch_dev, cplx):
             assert bool(bad[0].all()) and bool(bad[1].all())
         else:
             assert not bool(bad[0].any()) and not bool(bad[1].any())
+
+
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("n,b,crew", [(1200, 64, 1), (1200, 64, 3), (1200, 64, 0), (700, 31, 2),
+                                      (530, 64, 2)])
+def test_f2b_crew_equals_panel(torch_dev, n, b, crew, cplx):
+    """Panels whose workgroups do not come together, by one, some and all of
+    them: the same bits as together (fp64: 256 rows to a workgroup, complex
+    128; the crew's sizes do not divide the panels' groups)."""
+    import ctypes as C
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    fn = P.library().elpa_full_to_band_crew
+    fn.argtypes = [C.c_int64, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p,
+                   C.c_int32, C.c_void_p, C.c_int64, C.c_int64, C.c_int64]
+    g = torch.Generator(device=dev)
+    g.manual_seed(550 + n)
+    x = torch.randn((n, n), generator=g, device=dev, dtype=torch.float64)
+    if cplx:
+        x = torch.complex(x, torch.randn((n, n), generator=g, device=dev, dtype=torch.float64))
+    A = ((x + x.mH) / 2).t()
+    out = []
+    for ticks, c in ((10 ** 8, 0), (-1, crew)):
+        a = A.clone()
+        v = torch.zeros((n - b, n), dtype=a.dtype, device=dev).t()
+        tau = torch.zeros(n - b, dtype=a.dtype, device=dev)
+        print(f"f2b n={n} b={b} cplx={cplx} gather={ticks} crew={c}", flush=True)
+        rc = fn(n, b, a.data_ptr(), n, v.data_ptr(), n, tau.data_ptr(), P.C64 if cplx else P.R64,
+                None, ticks, 10 ** 9, c)
+        torch.cuda.synchronize()
+        assert rc == 0, rc
+        out.append((a, v, tau))
+    for y, z in zip(*out):
+        assert torch.equal(y, z)
