@@ -835,7 +835,7 @@ hipError_t plan_split_batch(const elpa_hh_problem* probs, const int64_t* idx, in
   if (B.one_launch && opt.order != ELPA_ORDER_LINEAR) {
     // deal whole problems to the dies, longest first, each to the die with
     // the least work so far; die x runs workgroup ids x, x + dies, ...
-    constexpr int dies = 8;
+    constexpr int dies = kDies;
     std::vector<std::vector<int>> lists(dies);
     std::vector<double> load(dies, 0.0);
     for (size_t i = 0; i < B.d.size(); ++i) {

@@ -31,6 +31,7 @@
 // contraction rows are consecutive, in a reflector and in a column of Q.
 #pragma once
 
+#include "hh_batch_map.h"
 #include "hh_common.h"
 #include "hh_dispatch.h"
 #include "hh_layout.h"
@@ -605,11 +606,11 @@ __global__ __launch_bounds__(ONE ? 64 : 512, 2) void k_wyd_local_b(
     const ProblemDesc* __restrict__ d, int count, const int* __restrict__ umap) {
   __shared__ int cnt[8];
   extern __shared__ double lv[];
-  const int b = (int)(blockIdx.x >> 1);
-  const int u = umap ? umap[b] : b;
+  const HalfUnit hu = half_unit((int)blockIdx.x, umap != nullptr);
+  const int u = umap ? umap[hu.entry] : hu.entry;
   if (u < 0) return;
   const ProblemDesc& D = d[find_by<ProblemDesc, &ProblemDesc::unit0>(d, count, u)];
-  const int64_t h = 2 * (int64_t)(u - D.unit0) + (blockIdx.x & 1);
+  const int64_t h = 2 * (int64_t)(u - D.unit0) + hu.half;
   if (16 * h >= D.nev) return;
   if constexpr (ONE) {
     for (int64_t m = D.M - 1; m >= 0; --m)
