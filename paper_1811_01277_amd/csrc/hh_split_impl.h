@@ -477,12 +477,16 @@ struct WyDirect {
   static int64_t slots_b(int cu) { return wave_slots(k_wyd_b<NB, K>, cu) / 2; }
   static void pack(int64_t groups, const void* hh, const void* tau, int64_t n, int64_t Jmax,
                    E* P, int64_t* Bt, hipStream_t st) {
-    hipLaunchKernelGGL((k_wyd_prep<NB, K>), dim3((unsigned)(groups * (K / 16))), dim3(256), 0, st,
-                       (const E*)hh, (const E*)tau, n, Jmax, P, Bt);
+    for (int64_t g = 0; g < groups; g += kPrepGroups)
+      hipLaunchKernelGGL((k_wyd_prep<NB, K>),
+                         dim3((unsigned)(std::min(groups - g, kPrepGroups) * (K / 16))), dim3(256),
+                         0, st, (const E*)hh, (const E*)tau, n, Jmax, P, Bt, g);
   }
   static void pack_b(int64_t groups, const ProblemDesc* d, int count, hipStream_t st) {
-    hipLaunchKernelGGL((k_wyd_prep_b<NB, K>), dim3((unsigned)(groups * (K / 16))), dim3(256), 0,
-                       st, d, count);
+    for (int64_t g = 0; g < groups; g += kPrepGroups)
+      hipLaunchKernelGGL((k_wyd_prep_b<NB, K>),
+                         dim3((unsigned)(std::min(groups - g, kPrepGroups) * (K / 16))), dim3(256),
+                         0, st, d, count, (int)g);
   }
   static void tiles(int64_t tiles, const E* P, const int64_t* Bt, const void* hh, E*, int64_t,
                     E* Q, int64_t ldq, int64_t n, int64_t nev, int c0, int G, int M, int t,
@@ -578,6 +582,8 @@ hipError_t run_split(const void* hh, const void* tau, void* Q, int64_t ldq, int6
   E* Qs = (E*)(ws + pbytes);
   const unsigned gt = (unsigned)((nev + 63) / 64);
   F::pack(pl.M * Jmax, hh, tau, n, Jmax, Pk, Bt, st);
+  // the later launches go by what this one writes
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return release(e);
   if constexpr (F::kStripes)
     hipLaunchKernelGGL((k_to_rows_sw<E, Gm::SW>), dim3((unsigned)(pl.rows_pad / 64), gt),
                        dim3(256), 0, st, (const E*)Q, ldq, n, nev, Qs, pl.rows_pad, pl.G);
@@ -871,7 +877,7 @@ inline void bind_split_batch(SplitBatchPlan& B, char* ws) {
 // The launches of a bound plan whose descriptor and entry tables are in the
 // workspace: packing, layout conversion, the schedule, conversion back.
 template <typename F>
-void launch_split_batch(const SplitBatchPlan& B, const char* ws, int xcd, hipStream_t st) {
+hipError_t launch_split_batch(const SplitBatchPlan& B, const char* ws, int xcd, hipStream_t st) {
   using E = typename F::E;
   constexpr int NB = F::NB, K = F::K;
   using Gm = SplitGeom<NB, K>;
@@ -879,6 +885,8 @@ void launch_split_batch(const SplitBatchPlan& B, const char* ws, int xcd, hipStr
   const DiagEntry* de = (const DiagEntry*)(ws + B.dbytes);
   const int count = (int)B.d.size();
   F::pack_b((int64_t)B.ptiles, dd, count, st);
+  // the later launches go by what this one writes
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if constexpr (F::kStripes)
     hipLaunchKernelGGL((k_to_rows_sw_b<E, Gm::SW>), dim3((unsigned)B.tiles), dim3(256), 0, st,
                        dd, count);
@@ -903,6 +911,7 @@ void launch_split_batch(const SplitBatchPlan& B, const char* ws, int xcd, hipStr
   if constexpr (F::kStripes)
     hipLaunchKernelGGL((k_from_rows_sw_b<E, Gm::SW>), dim3((unsigned)B.otiles), dim3(256), 0, st,
                        dd, count);
+  return hipGetLastError();
 }
 
 // Batched call: plan, stream-ordered workspace, tables staged through pinned
@@ -929,8 +938,7 @@ hipError_t launch_split_batched(const elpa_hh_problem* probs, const int64_t* idx
     (void)ws_free(ws, st);
     return err;
   }
-  launch_split_batch<F>(B, ws, opt.xcd, st);
-  err = hipGetLastError();
+  err = launch_split_batch<F>(B, ws, opt.xcd, st);
   const hipError_t e2 = ws_free(ws, st);
   return err != hipSuccess ? err : e2;
 }
@@ -986,8 +994,7 @@ class SplitPrepared : public PreparedGroup {
     if (one_)
       return run_split<F>(single_.hh, single_.tau, single_.Q, single_.ldq,
                                           single_.n, single_.nev, opt_, st, num_cu_, ws_);
-    launch_split_batch<F>(B_, (const char*)ws_, opt_.xcd, st);
-    return hipGetLastError();
+    return launch_split_batch<F>(B_, (const char*)ws_, opt_.xcd, st);
   }
   size_t bytes() const override { return bytes_; }
 

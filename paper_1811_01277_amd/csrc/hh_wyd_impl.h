@@ -119,21 +119,28 @@ __device__ __forceinline__ void wyd_prep_group(const double* __restrict__ hh,
   P[((mb_ + j) * Gm::SG + u) * (16 * Gm::RS) + tid] = -T[lane & 15][(lane >> 4) + 4 * kk];
 }
 
+// Groups (block, step), existing or not, of one launch, a workgroup for each of
+// their sub-groups: a launch holds fewer than 2^32 threads, and a large problem
+// has more sub-groups than that (n = 131000 at K = 80).
+constexpr int64_t kPrepGroups = int64_t(1) << 16;
+
+// Groups g0 .. of a problem.
 template <int NB, int K>
 __global__ __launch_bounds__(256) void k_wyd_prep(const double* __restrict__ hh,
                                                   const double* __restrict__ tau, int64_t n,
                                                   int64_t Jmax, double* __restrict__ P,
-                                                  int64_t* __restrict__ Bt) {
+                                                  int64_t* __restrict__ Bt, int64_t g0) {
   constexpr int SG = K / 16;
-  const int64_t g = blockIdx.x / SG;
+  static_assert(kPrepGroups * SG * 256 < int64_t(1) << 32, "threads of a launch");
+  const int64_t g = g0 + blockIdx.x / SG;
   wyd_prep_group<NB, K>(hh, tau, n, g / Jmax, g % Jmax, (int)(blockIdx.x % SG), P, Bt);
 }
 
 template <int NB, int K>
 __global__ __launch_bounds__(256) void k_wyd_prep_b(const ProblemDesc* __restrict__ d,
-                                                    int count) {
+                                                    int count, int g0) {
   constexpr int SG = K / 16;
-  const int b = (int)(blockIdx.x / SG);
+  const int b = g0 + (int)(blockIdx.x / SG);
   const ProblemDesc& D = d[find_by<ProblemDesc, &ProblemDesc::ptile0>(d, count, b)];
   const int64_t g = b - D.ptile0;
   wyd_prep_group<NB, K>((const double*)D.hh, (const double*)D.tau, D.n, g / D.Jmax, g % D.Jmax,

@@ -159,3 +159,32 @@ def test_complex_wy_leaves_large_calls_to_the_launch_schedule(torch_dev, many):
     print(f"complex n={n} nev={nev}: {pr}", flush=True)
     assert (pr["path"], pr["k"]) == (P.PATH_WY, k)
     assert (pr["launches"] > 1) == many
+
+
+def test_factors_in_several_launches(torch_dev):
+    """Path SPLIT fp64 with more (block, step) groups than one factor launch
+    takes (2^16), single (n = 19000) and batched (60 problems of n = 2000 on one
+    set of reflectors): against path WY to the parity bar, and bitwise against
+    the single launch schedule."""
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    n = 19000
+    assert -(-(n - 1) // 80) * -(-(n - 1) // 64) > 1 << 16
+    q, hh, tau = drawn(torch, dev, n, 64, 1, 7500)
+    ref = q.clone()
+    print(f"factors n={n}", flush=True)
+    P.hh_trafo(ref, hh, tau, 64, path=P.PATH_WY, k=160)
+    P.hh_trafo(q, hh, tau, 64, path=P.PATH_SPLIT)
+    torch.cuda.synchronize()
+    assert float((q - ref).abs().max() / ref.abs().max()) <= TOL
+    del q, hh, tau, ref
+    n, count = 2000, 60
+    assert count * -(-(n - 1) // 96) * -(-(n - 1) // 32) > 1 << 16
+    q, hh, tau = drawn(torch, dev, n, 32, 3, 7501)
+    probs = [(q.t().clone().t(), hh, tau, 32) for _ in range(count)]
+    print(f"factors {count} x n={n}", flush=True)
+    P.hh_trafo(q, hh, tau, 32, path=P.PATH_SPLIT, k=96, steps=4)
+    P.hh_trafo_batched(probs)
+    torch.cuda.synchronize()
+    for p in probs:
+        assert torch.equal(p[0], q)
