@@ -188,3 +188,57 @@ def test_factors_in_several_launches(torch_dev):
     torch.cuda.synchronize()
     for p in probs:
         assert torch.equal(p[0], q)
+
+
+def test_one_launch_kernels_side_by_side(torch_dev):
+    """Kernels whose workgroups wait for one another, two of them in flight on
+    two streams at a time (panels, chase, WY and SPLIT units, the local form):
+    every result has the bits it has alone, also where the workgroups of one do
+    not find room beside the other."""
+    torch, dev = torch_dev
+    import paper_1811_01277_amd as P
+    g = torch.Generator(device=dev)
+    g.manual_seed(7600)
+    x = torch.randn((1500, 1500), generator=g, device=dev, dtype=torch.float64)
+    A = ((x + x.t()) / 2).t()
+    B = A.clone()
+    P.full_to_band(B, 64)
+    sets = {(n, nbw, nev): drawn(torch, dev, n, nbw, nev, 7601 + n)
+            for n, nbw, nev in [(3500, 64, 3500), (2600, 64, 700), (400, 32, 400)]}
+
+    def f2b():
+        a = A.clone()
+        return (a, *P.full_to_band(a, 64))
+
+    def b2t():
+        b = B.clone()
+        return (b, *P.band_to_tridiag(b, 64))
+
+    def trafo(key, path):
+        q, hh, tau = sets[key]
+        q = q.t().clone().t()
+        P.hh_trafo(q, hh, tau, key[1], path=path)
+        return (q,)
+
+    work = {"panels": f2b, "chase": b2t,
+            "wy units": lambda: trafo((3500, 64, 3500), P.PATH_WY),
+            "split units": lambda: trafo((2600, 64, 700), P.PATH_SPLIT),
+            "split local": lambda: trafo((400, 32, 400), P.PATH_SPLIT)}
+    alone = {}
+    for k, f in work.items():
+        alone[k] = f()
+        torch.cuda.synchronize()
+    s1, s2 = torch.cuda.Stream(dev), torch.cuda.Stream(dev)
+    names = list(work)
+    for i, a in enumerate(names):
+        for b in names[i:]:
+            print(f"side by side: {a}, {b}", flush=True)
+            got = []
+            for _ in range(2):
+                with torch.cuda.stream(s1):
+                    got.append((a, work[a]()))
+                with torch.cuda.stream(s2):
+                    got.append((b, work[b]()))
+            torch.cuda.synchronize()
+            for k, out in got:
+                assert all(torch.equal(y, z) for y, z in zip(out, alone[k])), (a, b, k)
