@@ -54,6 +54,15 @@ extern "C" {
 int elpa_band_to_tridiag(int64_t n, int64_t nbw, void *A, int64_t lda, double *d, double *e,
                          void *hh, void *tau, int32_t dtype, void *stream);
 
+/*
+ * For tests: elpa_band_to_tridiag with the time that the workgroups of all chase
+ * positions (nbw <= 64) have to come together, in ticks of the 100 MHz clock
+ * (negative: that form is not tried).
+ */
+int elpa_band_to_tridiag_gather(int64_t n, int64_t nbw, void *A, int64_t lda, double *d,
+                                double *e, void *hh, void *tau, int32_t dtype, void *stream,
+                                int64_t gather_ticks);
+
 #ifdef __cplusplus
 }
 #endif

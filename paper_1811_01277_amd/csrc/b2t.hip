@@ -35,6 +35,7 @@
 #include "../../include/elpa_hh.h"
 #include "hh_common.h"
 #include "hh_sched.h"
+#include "lane_ops.h"
 
 namespace eb2t {
 
@@ -297,30 +298,16 @@ constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // 20 s of the 100 MHz 
 constexpr int kProgStride = 16;                          // counts 64 bytes apart
 constexpr int64_t kGatherTicks = 100000;                 // 1 ms
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140, kRor8 = 0x128;
+using elane::dpp_mov;
+using elane::kHalfMirror;
+using elane::kMirror;
+using elane::kRor8;
+using elane::kXor1;
+using elane::kXor2;
+using elane::pair16;
+using elane::pair32;
+using elane::read_lane;
 
-// a, b -> (a over the lower half of each pair of lane groups) + (...): lanes of
-// even groups get a summed over the pair, lanes of odd groups b
-__device__ __forceinline__ double pair32(double a, double b) {
-  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a),
-                                                  (unsigned)__double2loint(b), false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a),
-                                                  (unsigned)__double2hiint(b), false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double pair16(double a, double b) {
-  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a),
-                                                  (unsigned)__double2loint(b), false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a),
-                                                  (unsigned)__double2hiint(b), false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
 // sum over the wave, the same bits in every lane
 __device__ __forceinline__ double wave_sum_dpp(double x) {
   x += dpp_mov<kXor1>(x);
@@ -350,10 +337,6 @@ __device__ __forceinline__ z64 wave_sum8(const z64 (&x)[8]) {
     b[i] = x[i].im;
   }
   return z64{wave_sum8(a), wave_sum8(b)};
-}
-__device__ __forceinline__ double read_lane(double x, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
-                          __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 __device__ __forceinline__ z64 read_lane(z64 x, int l) {
   return z64{read_lane(x.re, l), read_lane(x.im, l)};
@@ -1062,8 +1045,6 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 }  // namespace eb2t
 
-// (for tests: gather_ticks, of the 100 MHz clock, is how long the resident
-// form's workgroups wait for each other; negative: that form is not tried)
 extern "C" int elpa_band_to_tridiag_gather(int64_t n, int64_t nbw, void* A, int64_t lda,
                                            double* d, double* e, void* hh, void* tau,
                                            int32_t dtype, void* stream, int64_t gather_ticks) {

@@ -28,6 +28,7 @@
 
 #include "../../include/elpa_f2b.h"
 #include "../../include/elpa_hh.h"
+#include "lane_ops.h"
 #include "wy_blas.h"
 
 namespace ef2b {
@@ -279,31 +280,16 @@ constexpr int64_t kCrewTicks = 10000;         // 0.1 ms
 constexpr int kClosed = 1 << 30;              // of a crew's count
 constexpr int64_t kWaitTicks = int64_t(20) * 100000000;  // never reached once all are resident
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kRor8 = 0x128;
+using elane::dpp_mov;
+using elane::kHalfMirror;
+using elane::kRor8;
+using elane::kXor1;
+using elane::kXor2;
+using elane::pair16;
+using elane::pair32;
+using elane::read_lane;
 
-// lanes of even groups of 32 (16) lanes: a summed over the pair of groups, of
-// odd groups: b
-__device__ __forceinline__ double pair32(double a, double b) {
-  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a),
-                                                  (unsigned)__double2loint(b), false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a),
-                                                  (unsigned)__double2hiint(b), false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double pair16(double a, double b) {
-  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a),
-                                                  (unsigned)__double2loint(b), false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a),
-                                                  (unsigned)__double2hiint(b), false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-// the same for groups of 8 and of 4 lanes within a row of 16
+// pair32's sums for groups of 8 and of 4 lanes within a row of 16
 template <int CTRL, int BIT>
 __device__ __forceinline__ double pair_dpp(double a, double b) {
   const bool up = (threadIdx.x & BIT) != 0;
@@ -349,10 +335,6 @@ __device__ __forceinline__ double lane_sum(double t) {
 template <int CW>
 __device__ __forceinline__ zc lane_sum(zc t) {
   return zc{lane_sum<CW>(t.re), lane_sum<CW>(t.im)};
-}
-__device__ __forceinline__ double read_lane(double x, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
-                          __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 __device__ __forceinline__ zc read_lane(zc x, int l) {
   return zc{read_lane(x.re, l), read_lane(x.im, l)};

@@ -158,9 +158,6 @@ __device__ __forceinline__ float half_pair_sum(float s) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
 // Reflector pairs (A = odd offset o, applied first; B = o-1): the two dot
 // products wA = vA.x and wB = vB.x are taken together on the window as it is
 // before A, and B's is corrected for A's update with the pair coupling
@@ -169,38 +166,37 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // which is (I - tauB vB vB^T)(I - tauA vA vA^T) x.  Both reflectors start on
 // register o/2 of each lane half; one reduction across the halves serves the
 // pair.
-template <typename T>
 struct SplitPair {
-  T a0, a1, a2, ta, b0, b1, tb, c;
+  float a0, a1, a2, ta, b0, b1, tb, c;
 };
 
-template <int NB, int K, int o, typename T>
-__device__ __forceinline__ SplitPair<T> split_load_pair(const T* __restrict__ Pj, int voff,
-                                                        int z) {
+template <int NB, int K, int o>
+__device__ __forceinline__ SplitPair split_load_pair(const float* __restrict__ Pj, int voff,
+                                                     int z) {
   using Gm = SplitGeom<NB, K>;
   static_assert((o & 1) == 1, "A is the odd offset of a pair");
-  const T* __restrict__ ra = Pj + o * Gm::RS + z;
-  const T* __restrict__ rb = ra - Gm::RS;
-  SplitPair<T> s;
+  const float* __restrict__ ra = Pj + o * Gm::RS + z;
+  const float* __restrict__ rb = ra - Gm::RS;
+  SplitPair s;
   s.a0 = ra[voff];
-  s.a1 = (Gm::NG == 2) ? ra[voff + 16] : T(0);
+  s.a1 = (Gm::NG == 2) ? ra[voff + 16] : 0.0f;
   s.a2 = ra[voff + 16 * Gm::NG];
   s.ta = ra[Gm::HS - 1];
   s.b0 = rb[voff];
-  s.b1 = (Gm::NG == 2) ? rb[voff + 16] : T(0);
+  s.b1 = (Gm::NG == 2) ? rb[voff + 16] : 0.0f;
   s.tb = rb[Gm::HS - 1];
   s.c = rb[Gm::RS - 1];
   return s;
 }
 
-// T = double or float (the same blocks on 64- or 32-bit values)
-template <int NB, int K, int PD, typename T, int R>
-__device__ __forceinline__ void step_split_pair(T (&x)[R], const T* __restrict__ Pj, int voff) {
+template <int NB, int K, int PD, int R>
+__device__ __forceinline__ void step_split_pair(float (&x)[R], const float* __restrict__ Pj,
+                                                int voff) {
   using Gm = SplitGeom<NB, K>;
   constexpr int NP = K / 2, HN = Gm::HN, NG = Gm::NG;
   static_assert(R == Gm::R, "window register count");
   static_assert(PD >= 1 && PD <= 3 && PD < NP, "pair prefetch distance 1..3");
-  SplitPair<T> buf[PD];
+  SplitPair buf[PD];
   FwdFor<PD>::run([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     buf[i] = split_load_pair<NB, K, K - 1 - 2 * i>(Pj, voff, 0);
@@ -208,13 +204,13 @@ __device__ __forceinline__ void step_split_pair(T (&x)[R], const T* __restrict__
   RevFor<NP>::run([&](auto pc) {
     constexpr int pi = decltype(pc)::value;
     constexpr int p0 = pi;  // (2 pi + 1) >> 1
-    const SplitPair<T> c0 = buf[0];
-    T aA0 = T(0), aA1 = T(0), aB0 = T(0), aB1 = T(0);
+    const SplitPair c0 = buf[0];
+    float aA0 = 0.0f, aA1 = 0.0f, aB0 = 0.0f, aB1 = 0.0f;
     if constexpr (NG == 2)
       pdot2_a(aA0, aA1, aB0, aB1, c0.a0, c0.a1, c0.b0, c0.b1, &x[p0], &x[p0 + 16]);
     else
       pdot1_a(aA0, aA1, aB0, aB1, c0.a0, c0.b0, &x[p0]);
-    SplitPair<T> nn{};
+    SplitPair nn{};
     if constexpr (pi - PD >= 0)
       nn = split_load_pair<NB, K, 2 * (pi - PD) + 1>(Pj, voff, zero_after(aA0));
     if constexpr (NG == 2)
@@ -222,10 +218,10 @@ __device__ __forceinline__ void step_split_pair(T (&x)[R], const T* __restrict__
               &x[p0 + HN]);
     else
       pdot1_b(aA0, aA1, aB0, aB1, c0.a0, c0.b0, c0.a2, &x[p0 + 8], &x[p0 + HN]);
-    const T wA = half_pair_sum(aA0 + aA1);
-    const T wB = half_pair_sum(aB0 + aB1);
-    const T nwA = -(c0.ta * wA);
-    const T nwB = -(c0.tb * fma_t(c0.c, nwA, wB));
+    const float wA = half_pair_sum(aA0 + aA1);
+    const float wB = half_pair_sum(aB0 + aB1);
+    const float nwA = -(c0.ta * wA);
+    const float nwB = -(c0.tb * __builtin_fmaf(c0.c, nwA, wB));
     if constexpr (NG == 2) {
       pupd2_a(&x[p0], &x[p0 + 16], c0.a0, c0.a1, c0.b0, c0.b1, nwA, nwB);
       pupd2_b(&x[p0 + 8], &x[p0 + 24], &x[p0 + HN], c0.a0, c0.a1, c0.b0, c0.b1, c0.a2, nwA, nwB);
@@ -339,7 +335,7 @@ __device__ __forceinline__ void run_split_steps(const E* __restrict__ P,
 #pragma unroll
       for (int p = R - HN; p < R; ++p) x[p] = rp[p * 64 + lane];
     }
-    if constexpr (std::is_same<E, double>::value || std::is_same<E, float>::value)
+    if constexpr (std::is_same<E, float>::value)
       step_split_pair<NB, K, PD>(x, Pm + j * (K * Gm::RS), voff);
     else
       step_split_c<NB, K, PD>(x, Pm + j * (K * Gm::RS), voff);

@@ -684,8 +684,9 @@ __global__ __launch_bounds__(64, OCC) void k_wy_b(const ProblemDesc* __restrict_
 // 2501 with 1251 columns 0.70 instead of 0.57: a sub-group of fp32 products is
 // shorter than the latency of its fragments' loads.)
 //
-// Bound: large calls by the matrix cores (fp64, n = 4500: 80 % of the cycles,
-// at the 1.9 GHz that this load runs at); small ones by the chain of M + J
+// Bound: large calls by the matrix cores (fp64, n = 20000: busy in 84 % of the
+// cycles, at 2.37 GHz; n = 4500: 80 %, at the 1.9 GHz of a call that short);
+// small ones by the chain of M + J
 // steps, each a wave's products (3.2 us for fp32, K = 96; 14 us complex, K =
 // 48), six or three barriers and about 3 us for the rows to pass from block to
 // block through memory.  Rows loaded ahead where the block above is far enough
