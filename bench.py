@@ -468,8 +468,9 @@ def bt2_leg(args, nevs=None):
 def b2t_leg(args):
     """Band -> tridiagonal reduction (elpa_band_to_tridiag) on a random
     symmetric band matrix of the same n, nbw 64, real fp64, drawn on the
-    device.  Latency-bound (about 3 n launches of independent chase steps), so
-    the figures are time, chase steps per second and time per launch."""
+    device.  One launch for bands this wide; bound by the latency of a sweep's
+    hand-overs, so the figures are time, chase steps per second and time per
+    sweep."""
     import torch
     import paper_1811_01277_amd as P
     dev = torch.device("cuda:0")
@@ -482,7 +483,6 @@ def b2t_leg(args):
     i = torch.arange(n, device=dev)
     B.masked_fill_((i[:, None] - i[None, :]).abs() > b, 0.0)
     steps = P.num_reflectors(n, b)
-    launches = max(3 * s + -(-(n - 1 - s) // b) for s in range(n - 1))
     times = []
     for _ in range(2):
         a = B.clone().t()   # symmetric: the column-major view holds the same matrix
@@ -497,8 +497,8 @@ def b2t_leg(args):
     t = min(times)
     return {"workload": f"band->tridiagonal reduction, n={n}, nbw={b}, r64, random band "
                         f"matrix", "s": round(t, 3), "chase_steps": steps,
-            "steps_per_s": round(steps / t), "launches": launches,
-            "us_per_launch": round(t / launches * 1e6, 2)}
+            "steps_per_s": round(steps / t), "sweeps": n - 1,
+            "us_per_sweep": round(t / (n - 1) * 1e6, 2)}
 
 
 def f2b_leg(args):
@@ -851,8 +851,10 @@ def main():
     achieved = (flops / launches) / (avg_launch_ms * 1e-3) * in_flight / 1e12
     peak = PEAK_TFLOPS[dt]
     direct = prof["path"] == 3 and dt == "r64"
-    kname = {1: "k_ref", 2: "k_diag", 3: "k_wyd" if direct else "k_split",
-             4: "k_wy"}.get(prof["path"], "?")
+    one = prof["launches"] == 1 and prof["steps"] == 0   # the sweep blocks in one launch
+    kname = {1: "k_ref", 2: "k_diag",
+             3: ("k_wyd_local / k_wyd_units" if one else "k_wyd") if direct else "k_split",
+             4: "k_wy_units" if one else "k_wy"}.get(prof["path"], "?")
     # the compact-WY kernels run on the matrix cores and execute (nbw+16)/nbw
     # times the counted flops (their sub-groups' parallelograms padded to whole
     # 16-row tiles; path 3 applies T by itself, 8 more rows' worth); the VALU

@@ -127,9 +127,9 @@ enum {
  * long as the device has room to gain by it): the sweep blocks
  * of a stripe side by side, each a step or two behind the next, on workgroups
  * of the whole device or (ELPA_PATH_SPLIT, by a model of both) on the waves of
- * one workgroup.  The first form takes 32 bytes per stripe of 16 (ELPA_PATH_WY:
- * 64) columns and sweep block beside the
- * workspace that elpa_hh_workspace_bytes reports, from the same cache.
+ * one workgroup.  The first form takes 32 bytes per 64 columns and sweep block
+ * (1.3 MB at n = nev = 20000) beside the workspace that
+ * elpa_hh_workspace_bytes reports, from the same cache.
  * A plan that leaves the kernel open (path AUTO, k, steps and batch 0, or
  * NULL) runs the tuner's plan for the problem's size class when there is one
  * (elpa_hh_tune, elpa_hh_tuner_*), with the caller's order and streams where

@@ -407,7 +407,8 @@ def hh_trafo_batched(problems, stream=None, path=None, k=0, steps=0, order=0, st
     Each q is a column-major (n, nev) device tensor as in hh_trafo; problems
     may differ in n, nev and dtype.  The problems of one (dtype, nbw) group
     that run path SPLIT are back-transformed in one kernel launch
-    (one workgroup per 32-column stripe of a problem, largest problems first);
+    (a workgroup per stripe of 32 columns, fp64 16, of a problem, largest
+    problems first);
     groups run in order on one stream.  batch: BATCH_ONE_LAUNCH or
     BATCH_DIAGONAL forces that schedule of path SPLIT (default: the
     library's model picks).

@@ -73,28 +73,30 @@ int default_k(int path, int32_t dtype, int64_t nb, bool batched) {
   return 0;
 }
 
-// Library choice for a single problem of size n with semi-bandwidth 64, from
-// sweeps over n = 1000 .. 20000 (nev = n) on this GPU: the compact-WY MFMA
-// kernel for fp32 (k = 96, from n = 6000 k = 160) and complex fp64 (k = 48)
-// at every size, and for fp64 from n = 3000 on (k = 128, from n = 6000
-// k = 160): a larger k reuses every loaded row more but leaves fewer sweep
-// blocks to run side by side (fp32 at n = 20000: 82.2 TFLOP/s at k = 160,
-// 77.3 at 96; at n = 4000: 36.9 against 39.2);
-// 0 = path SPLIT (fp64 below n = 3000, complex at nbw = 32,
-// other nbw, batched calls).  fp64 with fewer than 1024 columns
-// also takes path SPLIT:
-// the compact-WY kernel's T-build, which does not shrink with nev, is then a
-// large part of the call (n = 8192, nev = 819: 4.2 ms, 4.8 ms WY;
-// nev = 2000 at n = 20000 is faster on WY).  nev = 0: not known, taken as
-// large.
+// Library choice for a single problem: k of the compact-WY MFMA kernel (path
+// WY), 0 = path SPLIT; nev = 0: not known, taken as large.  The lines were drawn
+// on the diagonal launch schedule (k_wy against the two-lane kernel) and are kept:
+// workspaces and saved plans follow them.  What the two sides take now, in one
+// launch, ms, nev = n unless given:
+//  * nbw 64, fp32: WY at every size, k = 160 from n = 6000.  A larger k reuses every
+//    loaded row more but leaves fewer sweep blocks to run side by side: n = 4000 /
+//    6000 / 8000 / 20000: 1.84 / 5.50 / 12.3 / 187 at k = 96, 1.93 / 5.56 / 11.8 /
+//    172 at 160; path SPLIT 3.5 / 9.8 / 18.8 / 250.
+//  * nbw 64, complex: WY at every size (k = 48): n = 1000 / 4000 / 20000: 0.72 / 12.6 /
+//    1402 against 1.31 / 15.6 / 1516.
+//  * nbw 64, fp64: WY from n = 3000, k = 160 from n = 6000: n = 3000 / 4000 / 6000 /
+//    8000 / 20000: 1.80 / 3.69 / 10.2 / 22.6 / 322 at k = 128, - / - / 10.5 / 23.0 /
+//    315 at 160; path SPLIT 1.71 / 3.45 / 10.9 / 30.2 / 374.  With fewer than 1024
+//    columns the T-build, which does not shrink with nev, weighs on WY: n = 8192
+//    with 819 / 1024 / 2048 columns 4.05 / 4.62 / 7.38 SPLIT, 4.71 / 5.06 / 7.77
+//    WY; n = 20000 with 1000 / 2000 columns 22.5 / 41.4 and 23.9 / 40.7.
+//  * nbw 32, real: WY (k = 96) from n = 2000 with 1024 columns, despite its 1.5x
+//    executed operations: fp64, n = 2000 / 4000 / 6000 / 12000: 0.84 / 4.04 / 11.9 /
+//    86 against 0.86 / 4.36 / 13.8 / 108; fp32, n = 1000 (SPLIT by this rule) /
+//    2000 / 6000: 0.24 / 0.52 / 7.2 against 0.69 / 1.28 / 10.6.
+//  * nbw 32, complex: SPLIT: n = 1000 / 2000 / 6000: 1.38 / 3.32 / 44.7, WY at k =
+//    32 0.59 / 2.36 / 54.3.
 int auto_wy_k(int32_t dtype, int64_t nb, int64_t n, int64_t nev) {
-  // nbw = 32, real: the compact-WY kernel from n = 2000 despite its 1.5x
-  // executed flops there (in diagonal launches, fp64, n = 2000 / 4000 / 6000 /
-  // 12000: 8.0 / 21.7 / 29.2 / 34.3 TFLOP/s against 6.1 / 17.1 / 25.1 / 31.7 for
-  // the two-lane kernel; fp32 at n = 2000 / 6000 / 12000: 10.6 / 44.3 / 54.4
-  // against 7.3 / 36.8 / 52.6; in one launch, fp64 at n = 2000: 835 us against
-  // 843 of path SPLIT); complex keeps the two-lane kernel (n = 6000: 37.5
-  // against 31.4 for WY k = 32)
   if (nb == 32)
     return ((dtype == ELPA_R64 || dtype == ELPA_R32) && n >= 2000 &&
             (nev == 0 || nev >= 1024))

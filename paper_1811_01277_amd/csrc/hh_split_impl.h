@@ -677,6 +677,11 @@ hipError_t launch_split_ws(const void* hh, const void* tau, void* Q, int64_t ldq
 //  * diagonal: launch t of N_t tiles takes ceil(N_t / slots) rounds of S + 1
 //    step-units (as in choose_steps), plus half a step per launch for its
 //    start.
+// The fp64 one-launch form puts several waves on a stripe where there are few,
+// which this does not count.  Default, one launch, diagonal, us: 4 problems of n =
+// 1000 672, 759, 666; 8 of 500 361, 361, 340; 8 of 1500 1978, 1977, 2538; 64 of 1000
+// 5988, 6014, 6536; 3 of 4000 12870, 27000, 12840; 32 of 3000 56500, 57600, 53400;
+// nbw 32, 16 of 700 1061, 1060, 1049; 100 of 200 904, 899, 1112.
 struct BatchModel {
   double seq = 0.0, diag = 0.0;
 };

@@ -685,8 +685,9 @@ __global__ __launch_bounds__(64, OCC) void k_wy_b(const ProblemDesc* __restrict_
 // shorter than the latency of its fragments' loads.)
 //
 // Bound: large calls by the matrix cores (fp64, n = 20000: busy in 84 % of the
-// cycles, at 2.37 GHz; n = 4500: 80 %, at the 1.9 GHz of a call that short);
-// small ones by the chain of M + J
+// cycles, at 2.34 GHz; n = 4500: 68 %, at 2.18 GHz); there the operand records are
+// read from memory once per 64 columns, 1.04 of the 1.24 TB that a call at n = 20000
+// reads (4.6 TB/s with its writes).  Small calls by the chain of M + J
 // steps, each a wave's products (3.2 us for fp32, K = 96; 14 us complex, K =
 // 48), six or three barriers and about 3 us for the rows to pass from block to
 // block through memory.  Rows loaded ahead where the block above is far enough

@@ -22,7 +22,7 @@
 // stripe's step is four times shorter.  With the one-launch schedules of
 // hh_pipe.h: n = 512, nbw = 32: 426 -> 152 us; n = 1000, nbw = 64: 637 -> 329
 // us; n = 8192 with 819 columns: 6.6 -> 4.1 ms; 256 problems of n = 200 ..
-// 2000, nbw = 32: 46.8 -> 41.4 ms.  A step of K = 80, NB = 64 takes about
+// 2000, nbw = 32: 46.8 -> 40.5 ms.  A step of K = 80, NB = 64 takes about
 // 10 us on a wave that has its SIMD to itself, 6.8 of them MFMAs (74 cycles
 // each from one wave, 65 with two waves per SIMD).
 //
@@ -423,7 +423,7 @@ __device__ __forceinline__ void run_wyd_steps(const double* __restrict__ P,
 // unit.  (One wave to a unit, each staging for itself: n = 8192 with 819
 // columns 4.45 ms instead of 4.06, n = 2900 1.9 instead of 1.6.  The same units
 // without hand-overs for a batch ran 256 problems in 53.8 ms, the one-wave
-// local form in 41.4: it loads the next rows ahead and has no barriers.)
+// local form in 41.4 then: it loads the next rows ahead and has no barriers.)
 // lds: 2 WydGeom::LDS doubles.
 template <int NB, int K>
 __device__ __forceinline__ void run_wyd_unit(const double* __restrict__ P,
