@@ -16,7 +16,7 @@
 // forming T are this file's kernels.  (A triangular solve per block in T's
 // place, a dozen dependent launches of its own, took 1.5 of 6.6 ms at n = 6000
 // with 3000 vectors, nbw = 64, fp64; the strips
-// take 54 us for all sixteen blocks and the call 5.6 ms.)
+// take 62 us for all sixteen blocks and the call 5.64 ms.)
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
